@@ -385,8 +385,10 @@ moe_status moe_attn_forward_group(moe_attn_ctx* ctx, int32_t layer, int32_t n_ba
         HIP_TRY(ctx, mark(2));
         for (int r = 0; r < reps; ++r) launch_qkv_finish(st, part, sp1, stride, ctx->dm, tab, (const double*)(w + ctx->o_freq), q);
         HIP_TRY(ctx, mark(3));
+        // the projection's partial sums are consumed: their buffer holds the attention's
+        const int max_ranges = (int)((size_t)ctx->part_rows * ctx->widest / ((size_t)rows * (dq + 2 * (size_t)c.n_q_heads)));
         for (int r = 0; r < reps; ++r)
-            if (launch_attention(st, q, ctx->dm, tab, w + ctx->o_ao) != 0)
+            if (launch_attention(st, q, ctx->dm, tab, part, max_ranges, w + ctx->o_ao) != 0)
                 return fail(ctx, MOE_ERR_SHAPE, "no attention kernel for this head shape");
         HIP_TRY(ctx, mark(4));
         const int sp2 = splits_for((int)dq, (int)d);

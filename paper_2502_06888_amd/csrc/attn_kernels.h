@@ -52,8 +52,12 @@ void launch_qkv_finish(hipStream_t st, const float* part, int splits, int64_t sp
                        const Dims& dm, const GroupTab& tab, const double* inv_freq, float* q);
 
 // Softmax attention of the new token of every sequence over its batch's cache positions 0..pos;
-// output as bf16 in fragment order ([rows, Hq*hd] as the A operand of the output projection).
-int launch_attention(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab, void* o_frag);
+// output as bf16 in fragment order ([rows, Hq*hd] as the A operand of the output projection).  The
+// positions may be cut into up to max_splits ranges (pick_attn_splits says how many); `scratch`
+// then holds splits * rows * Hq * (hd + 2) floats: sums, then (maximum, weight) pairs.
+int pick_attn_splits(const Dims& dm, const GroupTab& tab, int max_splits);
+int launch_attention(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab, float* scratch,
+                     int max_splits, void* o_frag);
 
 // y = x + sum of the split-K partials of the output projection, one rounding to bf16.
 void launch_out_finish(hipStream_t st, const float* part, int splits, int64_t split_stride,

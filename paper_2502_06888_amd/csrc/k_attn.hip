@@ -260,21 +260,51 @@ __device__ __forceinline__ void merge(Soft& a, float m2, float l2, const float (
 
 constexpr float kEmpty = -1.0e30f;  // finite stand-in for "no position seen yet"
 
-// One workgroup (4 wavefronts, four workgroups per compute unit) per (sequence, key-value head); G query heads share the rows.
-// A row of HD elements is read by HD/8 lanes (16 bytes each); a wavefront covers 512/HD rows per
-// load, issues the K and V loads of kChunk such row groups together, and keeps one running
-// softmax per row slot (rescaled once per chunk), merged at the end.
+// Normalised output of 8 elements (16-byte chunk `chunk` of the row) as bf16 in fragment order.
+template <int HD>
+__device__ __forceinline__ void write_head(u32x4* __restrict__ o_frag, int row, int chunk, int Hq, const Soft& t) {
+    const float inv = 1.0f / t.l;  // position pos is always valid, so l > 0
+    u32x4 o;
+    o.x = pack2(t.acc[0] * inv, t.acc[1] * inv);
+    o.y = pack2(t.acc[2] * inv, t.acc[3] * inv);
+    o.z = pack2(t.acc[4] * inv, t.acc[5] * inv);
+    o.w = pack2(t.acc[6] * inv, t.acc[7] * inv);
+    o_frag[frag_piece(row, chunk, Hq * HD / 16)] = o;
+}
+
+// One workgroup (4 wavefronts) per (sequence, key-value head, part of the cached positions); G query
+// heads share the rows.  A row of HD elements is read by HD/8 lanes (16 bytes each); a wavefront
+// covers 512/HD rows per load, issues the K and V loads of kChunk such row groups together, and keeps
+// one running softmax per row slot (rescaled once per chunk), merged at the end.
+//
+// Bound by the cache bytes as long as the chip has loads in flight.  A few sequences with long
+// caches do not fill it with one workgroup per (sequence, head): 4 sequences x 8 heads x 8000
+// positions (6 query heads each) ran 32 workgroups for 920 us (0.14 TB/s; 284 bytes of scratch per
+// lane came on top), so the positions are cut into `splits` equal ranges (pick_attn_splits): 23
+// ranges take 36 us (3.6 TB/s) and 5 us for the merge.  With one range the workgroup writes the
+// attention output itself; with several each writes its unnormalised sums and attn_merge_kernel adds
+// them up.  512 sequences x 8 heads x 513 positions keep one range: 173 us, 6.3 TB/s.
 constexpr int kAttnWaves = 4, kChunk = 2;
+
+// Wavefronts per SIMD: query and output slices of a lane take 16 * G registers.  Up to four heads
+// fit the 128 registers that four wavefronts leave; more would spill, so those run with fewer
+// wavefronts and keep their loads in flight by requesting the next chunk before using this one.
+constexpr int attn_waves_per_simd(int G) { return G <= 4 ? 4 : G <= 6 ? 3 : 2; }
+
 template <int HD, int G>
-__global__ __launch_bounds__(kAttnWaves * 64, 4) void attn_decode_kernel(const float* __restrict__ q,
-                                                                     Dims dm, GroupTab tab,
-                                                                     u32x4* __restrict__ o_frag) {
+__global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_decode_kernel(
+    const float* __restrict__ q, Dims dm, GroupTab tab, int splits, float* __restrict__ part_acc,
+    float2* __restrict__ part_ml, u32x4* __restrict__ o_frag) {
     constexpr int LPR = HD / 8, RPW = 64 / LPR;
+    constexpr bool AHEAD = G > 4;
     __shared__ float sm[kAttnWaves][G * LPR][10];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row_g = blockIdx.x / dm.Hkv, hk = blockIdx.x % dm.Hkv;
+    const int sp = blockIdx.x % splits, pair = blockIdx.x / splits;
+    const int row_g = pair / dm.Hkv, hk = pair % dm.Hkv;
     const int bt = find_batch(tab, row_g);
-    const int s = row_g - tab.row0[bt], pos = tab.pos[bt];
+    const int s = row_g - tab.row0[bt], len = tab.pos[bt] + 1;  // positions 0..pos
+    const int per = (len + splits - 1) / splits;
+    const int first = sp * per, end = min(first + per, len);  // empty for the last ranges of a short cache
     const int sub = lane % LPR, slot = lane / LPR;
     float qr[G][8];
 #pragma unroll
@@ -292,17 +322,33 @@ __global__ __launch_bounds__(kAttnWaves * 64, 4) void attn_decode_kernel(const f
 #pragma unroll
         for (int j = 0; j < 8; ++j) st[g].acc[j] = 0.f;
     }
-    for (int p0 = wave * RPW * kChunk; p0 <= pos; p0 += kAttnWaves * RPW * kChunk) {
-        u32x4 kraw[kChunk], vraw[kChunk];
-        bool valid[kChunk];
+    // rows past the end re-read the range's last row (in bounds, weight 0)
+    auto load = [&](u32x4(&kr)[kChunk], u32x4(&vr)[kChunk], int p0) {
 #pragma unroll
         for (int c = 0; c < kChunk; ++c) {
-            const int p = p0 + c * RPW + slot;
-            valid[c] = p <= pos;
-            const int pc = valid[c] ? p : pos;
-            kraw[c] = __builtin_nontemporal_load(K + (size_t)pc * LPR);
-            vraw[c] = __builtin_nontemporal_load(V + (size_t)pc * LPR);
+            const int p = min(p0 + c * RPW + slot, end - 1);
+            kr[c] = __builtin_nontemporal_load(K + (size_t)p * LPR);
+            vr[c] = __builtin_nontemporal_load(V + (size_t)p * LPR);
         }
+    };
+    constexpr int STEP = kAttnWaves * RPW * kChunk;
+    int p0 = first + wave * RPW * kChunk;
+    u32x4 kraw[kChunk], vraw[kChunk], knext[kChunk], vnext[kChunk];
+    if (AHEAD && p0 < end) load(knext, vnext, p0);
+    for (; p0 < end; p0 += STEP) {
+        if (AHEAD) {
+#pragma unroll
+            for (int c = 0; c < kChunk; ++c) {
+                kraw[c] = knext[c];
+                vraw[c] = vnext[c];
+            }
+            load(knext, vnext, p0 + STEP);
+        } else {
+            load(kraw, vraw, p0);
+        }
+        bool valid[kChunk];
+#pragma unroll
+        for (int c = 0; c < kChunk; ++c) valid[c] = p0 + c * RPW + slot < end;
         float sc[G][kChunk];
 #pragma unroll
         for (int c = 0; c < kChunk; ++c) {
@@ -383,15 +429,64 @@ __global__ __launch_bounds__(kAttnWaves * 64, 4) void attn_decode_kernel(const f
             for (int j = 0; j < 8; ++j) a2[j] = e[2 + j];
             merge(t, e[0], e[1], a2);
         }
-        const float inv = 1.0f / t.l;  // position pos is always valid, so l > 0
-        u32x4 o;
-        o.x = pack2(t.acc[0] * inv, t.acc[1] * inv);
-        o.y = pack2(t.acc[2] * inv, t.acc[3] * inv);
-        o.z = pack2(t.acc[4] * inv, t.acc[5] * inv);
-        o.w = pack2(t.acc[6] * inv, t.acc[7] * inv);
-        const int chunk = ((hk * G + g) * HD) / 8 + sb;
-        o_frag[frag_piece(row_g, chunk, dm.Hq * HD / 16)] = o;
+        if (splits > 1) {
+            const size_t at = ((size_t)sp * tab.row0[tab.n] + row_g) * dm.Hq + hk * G + g;
+            float4* pa = reinterpret_cast<float4*>(part_acc + at * HD + sb * 8);
+            pa[0] = make_float4(t.acc[0], t.acc[1], t.acc[2], t.acc[3]);
+            pa[1] = make_float4(t.acc[4], t.acc[5], t.acc[6], t.acc[7]);
+            if (sb == 0) part_ml[at] = make_float2(t.m, t.l);
+            return;
+        }
+        write_head<HD>(o_frag, row_g, (hk * G + g) * LPR + sb, dm.Hq, t);
     }
+}
+
+// Adds up the ranges of one (row, query head): one wavefront, HD/8 lanes per range, so that 512/HD
+// ranges are summed side by side (kMergeAhead of them requested before the first is used) and then
+// merged over the lanes.  Latency-bound: with one thread per 8 elements walking all ranges 23 ranges
+// took 10.4 us.
+constexpr int kMergeAhead = 4;
+template <int HD>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_acc,
+                                                         const float2* __restrict__ part_ml, int splits,
+                                                         int rows, int Hq, u32x4* __restrict__ o_frag) {
+    constexpr int LPR = HD / 8, SIDE = 64 / LPR;
+    const int lane = threadIdx.x & 63, sub = lane % LPR;
+    const int rh = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (rh >= rows * Hq) return;  // uniform over the wavefront
+    const size_t stride = (size_t)rows * Hq;
+    Soft t;
+    t.m = kEmpty;
+    t.l = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t.acc[j] = 0.f;
+    for (int s0 = lane / LPR; s0 < splits; s0 += SIDE * kMergeAhead) {
+        float2 ml[kMergeAhead];
+        float4 lo[kMergeAhead], hi[kMergeAhead];
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) {  // past the end: the last range again, unused
+            const size_t at = (size_t)min(s0 + u * SIDE, splits - 1) * stride + rh;
+            const float4* pa = reinterpret_cast<const float4*>(part_acc + at * HD + sub * 8);
+            ml[u] = part_ml[at];
+            lo[u] = pa[0];
+            hi[u] = pa[1];
+        }
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) {
+            if (s0 + u * SIDE >= splits) break;
+            const float a2[8] = {lo[u].x, lo[u].y, lo[u].z, lo[u].w, hi[u].x, hi[u].y, hi[u].z, hi[u].w};
+            merge(t, ml[u].x, ml[u].y, a2);
+        }
+    }
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1) {
+        const float m2 = __shfl_xor(t.m, off, 64), l2 = __shfl_xor(t.l, off, 64);
+        float a2[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a2[j] = __shfl_xor(t.acc[j], off, 64);
+        merge(t, m2, l2, a2);
+    }
+    if (lane < LPR) write_head<HD>(o_frag, rh / Hq, (rh % Hq) * LPR + sub, Hq, t);
 }
 
 __global__ __launch_bounds__(256) void out_finish_kernel(const float* __restrict__ part, int splits,
@@ -471,25 +566,56 @@ void launch_qkv_finish(hipStream_t st, const float* part, int splits, int64_t sp
                        splits, split_stride, dm, tab, inv_freq, q);
 }
 
-template <int HD>
-static int launch_attention_hd(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab,
-                               void* o_frag) {
-    const dim3 grid(tab.row0[tab.n] * dm.Hkv), block(kAttnWaves * 64);
-    u32x4* O = (u32x4*)o_frag;
-    switch (dm.Hq / dm.Hkv) {
-#define KATTN_CASE(G) \
-    case G: hipLaunchKernelGGL((attn_decode_kernel<HD, G>), grid, block, 0, st, q, dm, tab, O); return 0;
-        KATTN_CASE(1) KATTN_CASE(2) KATTN_CASE(3) KATTN_CASE(4) KATTN_CASE(5) KATTN_CASE(6) KATTN_CASE(7) KATTN_CASE(8)
-#undef KATTN_CASE
+// Ranges the cached positions of every (sequence, key-value head) are cut into.  A range costs its
+// loop passes plus a fixed part (query load, slot merge, partial sums written and read: about
+// four passes, kRangeCost); the chip holds `slots` workgroups at a time, so the launch costs
+// ceil(pairs * n / slots) rounds of that.  The merge launch counts as kMergeCost passes.
+int pick_attn_splits(const Dims& dm, const GroupTab& tab, int max_splits) {
+    constexpr int kRangeCost = 4, kMergeCost = 8;
+    const int G = dm.Hq / dm.Hkv, rpw = 512 / dm.hd;
+    const long pairs = (long)tab.row0[tab.n] * dm.Hkv, slots = 256L * attn_waves_per_simd(G);
+    int len = 0;
+    for (int b = 0; b < tab.n; ++b) len = tab.pos[b] + 1 > len ? tab.pos[b] + 1 : len;
+    const int step = kAttnWaves * rpw * kChunk;
+    long best = 0;
+    int splits = 1;
+    for (int n = 1; n <= max_splits && (n - 1) * step < len; ++n) {
+        const long passes = ((len + n - 1) / n + step - 1) / step;
+        const long cost = (pairs * n + slots - 1) / slots * (passes + kRangeCost) + (n > 1 ? kMergeCost : 0);
+        if (n == 1 || cost < best) {
+            best = cost;
+            splits = n;
+        }
     }
-    return -1;
+    return splits;
 }
 
-int launch_attention(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab, void* o_frag) {
+template <int HD>
+static int launch_attention_hd(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab,
+                               float* scratch, int max_splits, void* o_frag) {
+    const int splits = pick_attn_splits(dm, tab, max_splits), rows = tab.row0[tab.n];
+    const dim3 grid(rows * dm.Hkv * splits), block(kAttnWaves * 64);
+    u32x4* O = (u32x4*)o_frag;
+    float2* ml = (float2*)(scratch + (size_t)splits * rows * dm.Hq * HD);
+    switch (dm.Hq / dm.Hkv) {
+#define KATTN_CASE(G) \
+    case G: hipLaunchKernelGGL((attn_decode_kernel<HD, G>), grid, block, 0, st, q, dm, tab, splits, scratch, ml, O); break;
+        KATTN_CASE(1) KATTN_CASE(2) KATTN_CASE(3) KATTN_CASE(4) KATTN_CASE(5) KATTN_CASE(6) KATTN_CASE(7) KATTN_CASE(8)
+#undef KATTN_CASE
+        default: return -1;
+    }
+    if (splits > 1)
+        hipLaunchKernelGGL(attn_merge_kernel<HD>, dim3((rows * dm.Hq + 3) / 4), dim3(256), 0, st,
+                           scratch, ml, splits, rows, dm.Hq, O);
+    return 0;
+}
+
+int launch_attention(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab, float* scratch,
+                     int max_splits, void* o_frag) {
     switch (dm.hd) {
-        case 32: return launch_attention_hd<32>(st, q, dm, tab, o_frag);
-        case 64: return launch_attention_hd<64>(st, q, dm, tab, o_frag);
-        case 128: return launch_attention_hd<128>(st, q, dm, tab, o_frag);
+        case 32: return launch_attention_hd<32>(st, q, dm, tab, scratch, max_splits, o_frag);
+        case 64: return launch_attention_hd<64>(st, q, dm, tab, scratch, max_splits, o_frag);
+        case 128: return launch_attention_hd<128>(st, q, dm, tab, scratch, max_splits, o_frag);
     }
     return -1;
 }

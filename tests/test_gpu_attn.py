@@ -108,6 +108,19 @@ def test_head_shapes(hd, hq, hkv):
     run_group(w, on_host=True)
 
 
+@pytest.mark.parametrize("hd,hq,hkv,seqs,pos,on_host", [
+    (128, 6, 1, (1,), (4000,), False),           # one sequence: as many ranges as pay off
+    (128, 8, 1, (2, 1), (1023, 30), False),      # a short cache next to a long one: its last ranges are empty
+    (64, 20, 4, (3,), (2047,), True),            # whole loop passes, caches streamed
+    (32, 4, 4, (1, 2, 1), (1500, 0, 255), False),
+    (128, 5, 1, (1,), (64, ), False),            # a range of one row at the end
+    (128, 14, 2, (7,), (321,), False)])
+def test_long_caches_of_few_sequences_are_cut_into_ranges(hd, hq, hkv, seqs, pos, on_host):
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=hd, n_q_heads=hq, n_kv_heads=hkv,
+                 d_model=256, batch_seqs=seqs, batch_pos=pos, max_len=max(pos) + 2, seed=17)
+    run_group(w, on_host=on_host)
+
+
 def test_ragged_rows_and_several_row_tiles():
     # 130 sequences: five row blocks -> two row tiles of four blocks, the last one ragged
     w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=64,
