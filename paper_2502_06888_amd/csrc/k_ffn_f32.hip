@@ -1,104 +1,290 @@
-// fp32 expert FFN (SwiGLU) on the vector ALUs, for the fp32 configuration.
+// fp32 expert FFN (SwiGLU) for the fp32 configuration, on the fp32 matrix instruction.
 //
 // Each expert is an FFN applied to the tokens routed to it (paper Section 2.1); rows follow
-// the same padded per-expert row space as the bf16 path.  One workgroup serves one row and a
-// slab of output features; a wavefront computes one dot product at a time (lanes stride the
-// reduction axis, xor-butterfly sum), fp32 fused multiply-adds throughout, accurate expf.
+// the same padded per-expert row space and the same tiles as the bf16 path.  A workgroup takes up
+// to 64 rows of one expert (two row blocks of a tile) and UN units of 32 weight rows; a unit of the
+// up projection stacks 16 rows of W1 on the same 16 of W3, so that the gate and the up value of a
+// feature meet in one lane.  The four wavefronts are NB row blocks x UN units x KS parts of the
+// reduction.  fp32 operands and accumulation throughout (32x32x2 MFMA, one fused multiply-add per
+// product, summed in three levels, which keeps the error of a wavefront's dot product over 64 lanes: one
+// chain per accumulator gave 6e-7 of the result at 1024 x 2048, this 2e-7), accurate expf.
+//
+// What bounds it: the matrix instruction, and with few rows per expert the expert weights.  A
+// workgroup per row with a dot product per wavefront read every weight once per row: the layer of
+// 256 tokens, top-2 of 8 experts, 1024 x 2048 took 844 (up) + 774 us (down); in tiles it takes 71 + 51 us
+// (60 and 42 TFLOP/s, padding rows not counted).  Both operands pass through LDS (straight from the
+// row-major matrices, 32 bytes of 32 rows per load, they took twice as long): whole 128-byte lines from memory, double buffered, the 16-byte pieces
+// of a row permuted by the row's number so that the reads of 16 rows spread over the 64 banks.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace kmoe {
 namespace {
 
-constexpr int kWaves = 4;
-constexpr int kSlab = 64;  // output features per workgroup
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Rows are read through pointers marked as global memory: activations and weights come from
+// different bases, and loads of an unknown address space (flat) would count as LDS traffic too, so
+// that every wait for LDS also waited for the stages in flight.
+typedef const __attribute__((address_space(1))) f32x4* gvec;
 
-__device__ __forceinline__ float wave_sum(float v) {
+constexpr int kWaves = 4, kThr = kWaves * 64;
+constexpr int kSliceK = 32;           // reduction elements of one wavefront and stage: a 128-byte line per row
+constexpr int kPieces = kSliceK / 4;  // 16-byte pieces of a row's slice
+constexpr int kPairBlks = 2;          // row blocks per workgroup, at most
+constexpr int kPairsPerTile = kTileBlks / kPairBlks;
+
+template <int NB, int UN>
+struct Geo {
+    static constexpr int KS = kWaves / (NB * UN);         // parts of the reduction
+    static constexpr int ROWS = (NB + UN) * 32;           // operand rows of a stage: activations, then weights
+    static constexpr int LOADS = ROWS * kPieces * KS / kThr;  // 16-byte loads per thread and stage
+    static constexpr int STAGE = ROWS * kPieces * KS;     // 16-byte pieces of a stage
+};
+
+// Sums over the whole reduction (K elements, a multiple of 4) of one workgroup.  row(r) is operand
+// row r (activations 0 .. NB*32-1, then weights).  Valid on return for wavefronts with ks == 0:
+// register i holds, of the wavefront's unit and row block, weight row 8 (i / 4) + 4 (lane / 32) + i % 4
+// and activation row lane % 32 (WFIRST) or the other way round.
+template <int NB, int UN, bool WFIRST, typename RowFn>
+__device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
+    using G = Geo<NB, UN>;
+    static_assert(NB * UN * G::KS == kWaves && G::ROWS * kPieces * G::KS % kThr == 0, "geometry");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int b = wave % NB, u = wave / NB % UN, ks = wave / (NB * UN);
+    // a thread's loads: piece threadIdx % 8 of rows threadIdx / 8 + 32 i, slice by slice
+    const int piece = threadIdx.x % kPieces, r0 = threadIdx.x / kPieces;
+    constexpr int RL = NB + UN;  // loads of a slice
+    gvec src[RL];
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
+    for (int i = 0; i < RL; ++i) src[i] = (gvec)(uintptr_t)(row(r0 + 32 * i)) + piece;
+    typedef f32x4 Regs[G::LOADS];
+    constexpr int kStageK = kSliceK * G::KS;
+    // Loads never branch (the waits below count them); pieces past the end read the row's start and
+    // are replaced by zeros when they go to LDS.  whole: the stage has no such piece.
+    auto load = [&](Regs& x, int k0, auto whole) {
+#pragma unroll
+        for (int sl = 0; sl < G::KS; ++sl) {
+            const int k = k0 + sl * kSliceK;
+            const int at = decltype(whole)::value || k + piece * 4 < K ? k / 4 : -piece;  // -piece: the row's start
+#pragma unroll
+            for (int i = 0; i < RL; ++i) x[sl * RL + i] = src[i][at];
+        }
+    };
+    auto slot = [](int sl, int r, int pc) { return (sl * G::ROWS + r) * kPieces + (pc ^ ((r >> 1) & (kPieces - 1))); };
+    auto store = [&](const Regs& x, int k0, int buf, auto whole) {
+#pragma unroll
+        for (int sl = 0; sl < G::KS; ++sl) {
+            const bool in = decltype(whole)::value || k0 + sl * kSliceK + piece * 4 < K;
+#pragma unroll
+            for (int i = 0; i < RL; ++i)
+                lds[buf * G::STAGE + slot(sl, r0 + 32 * i, piece)] = in ? x[sl * RL + i] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    // three levels of sums: 16 products in an accumulator, four stages in `part`, the parts in `total`
+    f32x16 total, part, acc[2];
+    int parted = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) total[i] = part[i] = 0.f;
+    // Stage k0 from LDS buffer `buf`; the next one goes from x to the other buffer, and x is filled with
+    // the third.  Two stages are in flight because one stage's 1024 cycles of MFMA are shorter than
+    // the memory latency.  steady: all of that exists and is whole, so there is no branch and the
+    // wait before the stores leaves the younger loads in flight.
+    auto stage = [&](Regs& x, int k0, int buf, auto steady) {
+        if (decltype(steady)::value || k0 + kStageK < K) store(x, k0 + kStageK, buf ^ 1, steady);
+        if (decltype(steady)::value || k0 + 3 * kStageK < K) load(x, k0 + 3 * kStageK, steady);
+        const f32x4* L = lds + buf * G::STAGE;
+        f32x4 xa[kPieces / 2], wa[kPieces / 2];
+#pragma unroll
+        for (int st = 0; st < kPieces / 2; ++st) {  // the lane's half of a step of eight elements
+            const int pc = 2 * st + (lane >> 5);
+            xa[st] = L[slot(ks, b * 32 + (lane & 31), pc)];
+            wa[st] = L[slot(ks, (NB + u) * 32 + (lane & 31), pc)];
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
+#pragma unroll
+        for (int st = 0; st < kPieces / 2; ++st)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[j & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(WFIRST ? wa[st][j] : xa[st][j],
+                                                                  WFIRST ? xa[st][j] : wa[st][j], acc[j & 1], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part[i] += acc[0][i] + acc[1][i];
+        if (++parted == 4) {
+            parted = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                total[i] += part[i];
+                part[i] = 0.f;
+            }
+        }
+        __syncthreads();
+    };
+    Regs xa, xb;
+    load(xa, 0, std::false_type{});
+    store(xa, 0, 0, std::false_type{});
+    load(xa, kStageK, std::false_type{});
+    load(xb, 2 * kStageK, std::false_type{});
+    __syncthreads();
+    int k0 = 0;
+    for (; k0 + 5 * kStageK <= K; k0 += 2 * kStageK) {
+        stage(xa, k0, 0, std::true_type{});
+        stage(xb, k0 + kStageK, 1, std::true_type{});
+    }
+    for (; k0 < K; k0 += 2 * kStageK) {
+        stage(xa, k0, 0, std::false_type{});
+        if (k0 + kStageK < K) stage(xb, k0 + kStageK, 1, std::false_type{});  // uniform over the workgroup
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) total[i] += part[i];
+    if (G::KS > 1) {  // the parts of the reduction are added in order (LDS: behind the last barrier)
+        float* red = reinterpret_cast<float*>(lds);
+        const int tile = wave % (NB * UN);
+        if (ks > 0)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[(((ks - 1) * NB * UN + tile) * 16 + i) * 64 + lane] = total[i];
+        __syncthreads();
+        if (ks == 0)
+#pragma unroll
+            for (int p = 0; p < G::KS - 1; ++p)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) total[i] += red[((p * NB * UN + tile) * 16 + i) * 64 + lane];
+    }
+    return total;
 }
 
-// Which expert and which source token does padded row `row` belong to?  token < 0: padding.
-__device__ __forceinline__ void row_owner(const Shape& s, const PlanPtrs& p, int row, int& e,
-                                          int& token) {
-    const int routed_rows = p.meta[2] * kRowBlk;
-    token = -1;
-    e = -1;
-    if (row < routed_rows) {
-        e = p.blk_expert[row / kRowBlk];
-        const int rank = row - p.poff[e];
-        if (rank < p.counts[e]) token = p.perm[p.offsets[e] + rank] / s.k;
-    } else {
-        const int stride = (s.N + kRowBlk - 1) / kRowBlk * kRowBlk;
-        const int r = row - routed_rows;
-        if (stride > 0 && r < s.S * stride) {
-            e = s.E + r / stride;
-            const int t = r % stride;
-            if (t < s.N) token = t;
-        }
+// Grid: (groups of output features, row parts, the parts beyond kGridY in z).  Features come first, so
+// that the workgroups of a row part spread over all XCDs and those that share weight rows (the parts of
+// an expert) tend to meet on one: parts first left half of the XCDs without live workgroups (a tile
+// has four parts, of which one or two exist) and took 1.8 times as long.
+constexpr int kGridY = 32768;
+
+struct Part {
+    int e, hblk, nblk;  // expert, first row block of H and O, live row blocks (1 or 2; 0: nothing here)
+    int xblk;           // first row block in the token space of the expert
+};
+
+// Which expert and row blocks does this workgroup serve?
+__device__ __forceinline__ Part locate(const PlanPtrs& p, int only_expert) {
+    Part w{0, 0, 0, 0};
+    const int part = (int)blockIdx.z * kGridY + (int)blockIdx.y;
+    const int i = part / kPairsPerTile, pair = part % kPairsPerTile;
+    if (i >= (only_expert >= 0 ? p.exp_ntiles[only_expert] : p.meta[1])) return w;
+    const int tile = only_expert >= 0 ? p.exp_tile0[only_expert] + i : i;
+    w.e = p.tile_expert[tile];
+    w.hblk = p.tile_hblk[tile] + pair * kPairBlks;
+    w.xblk = p.tile_xblk[tile] + pair * kPairBlks;
+    w.nblk = max(0, min(kPairBlks, p.tile_nblk[tile] - pair * kPairBlks));
+    return w;
+}
+
+// Token of row r of the workgroup's rows, -1 for padding.
+__device__ __forceinline__ int token_of(const Shape& s, const PlanPtrs& p, const Part& w, int r) {
+    if (w.e < s.E) {
+        const int rank = w.xblk * kRowBlk + r - p.poff[w.e];
+        return rank < p.counts[w.e] ? p.perm[p.offsets[w.e] + rank] / s.k : -1;
     }
+    const int t = (w.xblk - p.meta[2]) * kRowBlk + r;  // shared experts: the tokens in order
+    return t < s.N ? t : -1;
 }
 
 // h[row, n] = silu(W1[n,:] . x) * (W3[n,:] . x)
-__global__ __launch_bounds__(kWaves * 64) void ffn_up_f32_kernel(
-    const float* __restrict__ x, Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
-    const uint8_t* __restrict__ w_single, int only_expert, float* __restrict__ h) {
-    int e, token;
-    row_owner(s, p, blockIdx.x, e, token);
-    if (token < 0 || (only_expert >= 0 && e != only_expert)) return;
-    const float* blob = reinterpret_cast<const float*>(w_single ? w_single : wtab[e]);
-    const float* w1 = blob;
-    const float* w3 = blob + (size_t)s.f * s.d;
-    const float* xr = x + (size_t)token * s.d;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n0 = blockIdx.y * kSlab;
-    for (int n = n0 + wave; n < min(n0 + kSlab, s.f); n += kWaves) {
-        float g = 0.f, u = 0.f;
-        for (int i = lane; i < s.d; i += 64) {
-            const float xv = xr[i];
-            g = __builtin_fmaf(w1[(size_t)n * s.d + i], xv, g);
-            u = __builtin_fmaf(w3[(size_t)n * s.d + i], xv, u);
+constexpr int kUpUnits = 2, kUpFeat = 16 * kUpUnits;
+template <int NB>
+__device__ __forceinline__ void up_rows(const float* __restrict__ x, const Shape& s, const PlanPtrs& p,
+                                        const Part& w, const float* blob, f32x4* lds, float* __restrict__ h) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n0 = (int)blockIdx.x * kUpFeat;
+    auto row = [&](int r) -> const float* {  // padding rows read token 0, features past the end the last one
+        if (r < NB * 32) return x + (size_t)max(0, token_of(s, p, w, r)) * s.d;
+        const int i = (r - NB * 32) % 32, n = min(n0 + (r - NB * 32) / 32 * 16 + i % 16, s.f - 1);
+        return blob + ((size_t)(i / 16) * s.f + n) * s.d;
+    };
+    const f32x16 acc = reduce_tile<NB, kUpUnits, true>(row, s.d, lds);
+    if (wave / (NB * kUpUnits) != 0) return;
+    const int r = wave % NB * 32 + (lane & 31), f0 = n0 + wave / NB % kUpUnits * 16 + 4 * (lane >> 5);
+    if (token_of(s, p, w, r) < 0) return;
+    float* dst = h + ((size_t)w.hblk * kRowBlk + r) * s.f;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {  // registers 4q .. 4q+3: features f0 + 8q .. +3; the up values 8 registers on
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float g = acc[4 * q + j];
+            v[j] = g / (1.f + expf(-g)) * acc[4 * q + j + 8];
         }
-        g = wave_sum(g);
-        u = wave_sum(u);
-        if (lane == 0) h[(size_t)blockIdx.x * s.f + n] = g / (1.f + expf(-g)) * u;
+        if (f0 + 8 * q < s.f)  // f is a multiple of 4
+            *reinterpret_cast<float4*>(dst + f0 + 8 * q) = make_float4(v[0], v[1], v[2], v[3]);
     }
 }
 
+__global__ __launch_bounds__(kThr) void ffn_up_f32_kernel(
+    const float* __restrict__ x, Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
+    const uint8_t* __restrict__ w_single, int only_expert, float* __restrict__ h) {
+    __shared__ f32x4 lds[2 * Geo<1, kUpUnits>::STAGE];
+    static_assert(Geo<1, kUpUnits>::STAGE >= Geo<2, kUpUnits>::STAGE, "LDS of the larger stage");
+    const Part w = locate(p, only_expert);
+    if (w.nblk == 0) return;
+    const float* blob = reinterpret_cast<const float*>(w_single ? w_single : wtab[w.e]);
+    if (w.nblk == 1)
+        up_rows<1>(x, s, p, w, blob, lds, h);
+    else
+        up_rows<2>(x, s, p, w, blob, lds, h);
+}
+
 // o[row, m] = W2[m,:] . h[row,:]
-__global__ __launch_bounds__(kWaves * 64) void ffn_down_f32_kernel(
+constexpr int kDownUnits = 1, kDownFeat = 32 * kDownUnits;
+template <int NB>
+__device__ __forceinline__ void down_rows(const Shape& s, const Part& w, const float* w2, f32x4* lds,
+                                          const float* __restrict__ h, float* __restrict__ o) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int m0 = (int)blockIdx.x * kDownFeat;
+    auto row = [&](int r) -> const float* {  // padding rows hold whatever is there: a row only reaches its own sums
+        if (r < NB * 32) return h + ((size_t)w.hblk * kRowBlk + r) * s.f;
+        return w2 + (size_t)min(m0 + r - NB * 32, s.d - 1) * s.f;
+    };
+    const f32x16 acc = reduce_tile<NB, kDownUnits, false>(row, s.f, lds);
+    if (wave / (NB * kDownUnits) != 0) return;
+    const int col = m0 + wave / NB % kDownUnits * 32 + (lane & 31);
+    if (col >= s.d) return;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const size_t r = (size_t)w.hblk * kRowBlk + wave % NB * 32 + 8 * (i / 4) + 4 * (lane >> 5) + i % 4;
+        o[r * s.d + col] = acc[i];
+    }
+}
+
+__global__ __launch_bounds__(kThr) void ffn_down_f32_kernel(
     Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
     const uint8_t* __restrict__ w_single, int only_expert, const float* __restrict__ h,
     float* __restrict__ o) {
-    int e, token;
-    row_owner(s, p, blockIdx.x, e, token);
-    if (token < 0 || (only_expert >= 0 && e != only_expert)) return;
-    const float* blob = reinterpret_cast<const float*>(w_single ? w_single : wtab[e]);
-    const float* w2 = blob + 2 * (size_t)s.f * s.d;
-    const float* hr = h + (size_t)blockIdx.x * s.f;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = blockIdx.y * kSlab;
-    for (int m = m0 + wave; m < min(m0 + kSlab, s.d); m += kWaves) {
-        float acc = 0.f;
-        for (int i = lane; i < s.f; i += 64) acc = __builtin_fmaf(w2[(size_t)m * s.f + i], hr[i], acc);
-        acc = wave_sum(acc);
-        if (lane == 0) o[(size_t)blockIdx.x * s.d + m] = acc;
-    }
+    __shared__ f32x4 lds[2 * Geo<1, kDownUnits>::STAGE];
+    static_assert(Geo<1, kDownUnits>::STAGE >= Geo<2, kDownUnits>::STAGE, "LDS of the larger stage");
+    const Part w = locate(p, only_expert);
+    if (w.nblk == 0) return;
+    const float* w2 = reinterpret_cast<const float*>(w_single ? w_single : wtab[w.e]) + 2 * (size_t)s.f * s.d;
+    if (w.nblk == 1)
+        down_rows<1>(s, w, w2, lds, h, o);
+    else
+        down_rows<2>(s, w, w2, lds, h, o);
 }
 
 }  // namespace
 
 void launch_ffn_f32(hipStream_t st, const float* x, const Shape& s, const PlanPtrs& p,
                     const uint8_t* const* wtab, const uint8_t* w_single, int32_t only_expert,
-                    float* h, float* o) {
-    if (s.N <= 0) return;
-    const int rows = s.max_rowblks * kRowBlk + s.S * ((s.N + kRowBlk - 1) / kRowBlk * kRowBlk);
-    // rows beyond the routed padded space of this call shift the shared rows down; bound by the
-    // capacity and let row_owner() reject what is not there.
-    hipLaunchKernelGGL(ffn_up_f32_kernel, dim3(rows, (s.f + kSlab - 1) / kSlab), dim3(kWaves * 64),
-                       0, st, x, s, p, wtab, w_single, only_expert, h);
-    hipLaunchKernelGGL(ffn_down_f32_kernel, dim3(rows, (s.d + kSlab - 1) / kSlab),
-                       dim3(kWaves * 64), 0, st, s, p, wtab, w_single, only_expert, h, o);
+                    int32_t max_tiles, float* h, float* o) {
+    if (s.N <= 0 || max_tiles <= 0) return;
+    auto grid = [&](int features, int per_group) {
+        const int parts = max_tiles * kPairsPerTile;
+        return dim3((features + per_group - 1) / per_group, parts < kGridY ? parts : kGridY, (parts + kGridY - 1) / kGridY);
+    };
+    hipLaunchKernelGGL(ffn_up_f32_kernel, grid(s.f, kUpFeat), dim3(kThr), 0, st, x, s, p, wtab, w_single,
+                       only_expert, h);
+    hipLaunchKernelGGL(ffn_down_f32_kernel, grid(s.d, kDownFeat), dim3(kThr), 0, st, s, p, wtab, w_single,
+                       only_expert, h, o);
 }
 
 }  // namespace kmoe

@@ -133,8 +133,9 @@ void launch_combine(hipStream_t st, int out_dtype, const Shape& s, const PlanPtr
 // ---- f32 path (plain row-major blobs: W1 | W3 | W2) ------------------------------------------
 void launch_pack_expert_f32(hipStream_t st, const void* w1, const void* w3, const void* w2, int d,
                             int f, void* blob);
+// max_tiles: tiles of the call at most (of only_expert, if that is not negative).
 void launch_ffn_f32(hipStream_t st, const float* x, const Shape& s, const PlanPtrs& p,
                     const uint8_t* const* wtab, const uint8_t* w_single, int32_t only_expert,
-                    float* h, float* o);
+                    int32_t max_tiles, float* h, float* o);
 
 }  // namespace kmoe

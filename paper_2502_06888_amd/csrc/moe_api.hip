@@ -944,14 +944,14 @@ moe_status moe_layer_forward(moe_ctx* ctx, int32_t layer, const void* x_dev, voi
     if (prof) (void)hipEventRecord(ctx->pev[4], st);
 
     if (all_resident) {
+        const int64_t A = (int64_t)N * s.k;
+        a.max_tiles = (int)std::min<int64_t>(ctx->L.max_tiles,
+                                             (A / kRowBlk + E) / kTileBlks + std::min<int64_t>(E, A) +
+                                                 (int64_t)S * ((N + kTileRows - 1) / kTileRows) + 1);
         if (bf16) {
             a.w_single = nullptr;
             a.tile_first = nullptr;
             a.tile_count = p.meta + 1;
-            const int64_t A = (int64_t)N * s.k;
-            a.max_tiles = (int)std::min<int64_t>(ctx->L.max_tiles,
-                                                 (A / kRowBlk + E) / kTileBlks + std::min<int64_t>(E, A) +
-                                                     (int64_t)S * ((N + kTileRows - 1) / kTileRows) + 1);
             a.est_tiles = (int)(std::max<int64_t>(std::min<int64_t>(E, A), (A + kTileRows - 1) / kTileRows) +
                                 (int64_t)S * ((N + kTileRows - 1) / kTileRows));
             a.act = w + ctx->L.xp;
@@ -965,7 +965,7 @@ moe_status moe_layer_forward(moe_ctx* ctx, int32_t layer, const void* x_dev, voi
             launch_ffn_down_bf16(st, a);
         } else {
             if (prof) (void)hipEventRecord(ctx->pev[5], st);
-            launch_ffn_f32(st, (const float*)x_dev, s, p, wtab, nullptr, -1, (float*)(w + ctx->L.h), o);
+            launch_ffn_f32(st, (const float*)x_dev, s, p, wtab, nullptr, -1, a.max_tiles, (float*)(w + ctx->L.h), o);
         }
         if (prof) (void)hipEventRecord(ctx->pev[6], st);
     } else {
@@ -1011,7 +1011,7 @@ moe_status moe_layer_forward(moe_ctx* ctx, int32_t layer, const void* x_dev, voi
                     launch_ffn_down_bf16(st, a);
                 }
             } else {
-                launch_ffn_f32(st, (const float*)x_dev, s, p, wtab, blob, e, (float*)(w + ctx->L.h), o);
+                launch_ffn_f32(st, (const float*)x_dev, s, p, wtab, blob, e, ctx->h_tiles[e].count, (float*)(w + ctx->L.h), o);
             }
             span_close(ctx, st, sp);
         };

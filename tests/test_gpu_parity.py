@@ -411,6 +411,16 @@ def test_maximum_experts_topk_shared_and_batches():
     assert (got["counts"] == 0).any() and got["counts"].sum() == w.n_tokens * 8
 
 
+@pytest.mark.parametrize("d,f,E,k,S,batches", [
+    (4, 4, 2, 1, 0, (1,)),                 # the reduction is one half step
+    (260, 36, 3, 2, 1, (65, 0, 32)),       # d and f = 4 mod 8, ragged feature group, 32 and 33 rows
+    (64, 128, 2, 2, 0, (257,)),            # more than one tile per expert, one row in the last block
+    (1024, 2048, 8, 2, 0, (64, 64, 64, 64))])
+def test_f32_tiles_steps_and_remainders(d, f, E, k, S, batches):
+    run_case(I.Workload(f"f32_{d}x{f}", "f32", d, f, E, k, n_shared=S, batch_tokens=batches, seed=23,
+                        w_std=0.08 if d < 1024 else 0.02))
+
+
 def test_f32_maximum_topk_and_many_experts():
     w = I.Workload("maxima_f32", "f32", 64, 128, 128, 8, n_shared=2, batch_tokens=(7, 0, 11, 2, 30),
                    w_std=0.1)
