@@ -29,6 +29,30 @@ __device__ __forceinline__ int batch_of(const int32_t* sbo, int n, int t) {
     return lo;
 }
 
+// Lanes of the wavefront whose assignment goes to the same expert as this lane's (0 for lanes without
+// one, e < 0): one ballot per bit of the expert id.
+__device__ __forceinline__ unsigned long long same_expert(int e, int ebits) {
+    unsigned long long m = __ballot(e >= 0);
+    for (int b = 0; b < ebits; ++b) {
+        const bool bit = (e >> b) & 1;
+        const unsigned long long ones = __ballot(bit);
+        m &= bit ? ones : ~ones;
+    }
+    return e >= 0 ? m : 0ull;
+}
+__device__ __forceinline__ int bits_for(int E) { return 32 - __clz(E - 1 > 0 ? E - 1 : 1); }  // ids 0 .. E-1
+__device__ __forceinline__ unsigned long long lanes_below() { return (1ull << (threadIdx.x & 63)) - 1ull; }
+
+// Adds batch b of assignments to expert e to the expert's batch mask.  Consecutive lanes with the
+// same expert mostly come from the same batch: a lane whose predecessor in `same` does leaves the
+// (serialising) LDS atomic to it.
+__device__ __forceinline__ void add_batch(unsigned long long* msk, int e, int b, unsigned long long same) {
+    const unsigned long long before = same & lanes_below();
+    const int prev = before ? 63 - __clzll((long long)before) : (int)(threadIdx.x & 63);
+    const int bp = __shfl(b, prev, 64);
+    if (e >= 0 && (before == 0ull || bp != b)) atomicOr(&msk[e], 1ull << b);
+}
+
 // P1: per chunk of assignments, tokens per expert and the set of batches touching each expert.
 __global__ __launch_bounds__(kThreads) void plan_count_kernel(const int32_t* __restrict__ idx,
                                                               int A, int E, int k, BatchOffsets bo,
@@ -37,20 +61,26 @@ __global__ __launch_bounds__(kThreads) void plan_count_kernel(const int32_t* __r
     __shared__ int32_t cnt[kMaxExperts];
     __shared__ unsigned long long msk[kMaxExperts];
     __shared__ int32_t sbo[kMaxBatches + 1];
+    const int base = blockIdx.x * kPlanChunk;
+    int mine[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int a = base + r * kThreads + threadIdx.x;
+        mine[r] = a < A ? idx[a] : -1;
+    }
     stage_offsets(bo, sbo);
     for (int e = threadIdx.x; e < E; e += kThreads) {
         cnt[e] = 0;
         msk[e] = 0ull;
     }
     __syncthreads();
-    const int base = blockIdx.x * kPlanChunk;
+    const int ebits = bits_for(E);
+#pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int a = base + r * kThreads + threadIdx.x;
-        if (a < A) {
-            const int e = idx[a];
-            atomicAdd(&cnt[e], 1);
-            atomicOr(&msk[e], 1ull << batch_of(sbo, bo.n, a / k));
-        }
+        const int a = base + r * kThreads + threadIdx.x, e = mine[r];
+        const unsigned long long same = same_expert(e, ebits);
+        if (e >= 0 && (same & lanes_below()) == 0ull) atomicAdd(&cnt[e], __popcll(same));
+        add_batch(msk, e, a < A ? batch_of(sbo, bo.n, a / k) : 0, same);
     }
     __syncthreads();
     for (int e = threadIdx.x; e < E; e += kThreads) {
@@ -59,94 +89,148 @@ __global__ __launch_bounds__(kThreads) void plan_count_kernel(const int32_t* __r
     }
 }
 
-// Totals -> scans, execution order, tile tables, host mail.  cnt[] and nbt[] hold the tokens
-// and the batches of every expert on entry; off[], pof[], ord[] and nact are LDS scratch.
-__device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int max_tiles,
-                                          int32_t* cnt, int32_t* nbt, int32_t* off, int32_t* pof,
-                                          int32_t* ord, int32_t* nact_p) {
+// LDS of the scans: one entry per expert.
+struct ScanLds {
+    int32_t cnt[kMaxExperts];  // tokens (set by the caller)
+    int32_t nbt[kMaxExperts];  // batches (set by the caller)
+    int32_t off[kMaxExperts + 1], pof[kMaxExperts + 1];
+    int32_t ord[kMaxExperts];
+    unsigned long long key[kMaxExperts];
+    int32_t wsum[2][kMaxExperts / 64];
+};
+
+// Exclusive sums over the first kMaxExperts threads of the workgroup (whole wavefronts) of two
+// values at once; every thread calls it.
+__device__ __forceinline__ void scan2(int& a, int& b, int& total_a, int& total_b, int32_t (*wsum)[kMaxExperts / 64]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int sa = a, sb = b;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const int ua = __shfl_up(sa, m, 64), ub = __shfl_up(sb, m, 64);
+        if (lane >= m) {
+            sa += ua;
+            sb += ub;
+        }
+    }
+    __syncthreads();  // wsum of an earlier call has been read
+    if (lane == 63 && wave < kMaxExperts / 64) {
+        wsum[0][wave] = sa;
+        wsum[1][wave] = sb;
+    }
+    __syncthreads();
+    total_a = total_b = 0;
+    int before_a = 0, before_b = 0;
+#pragma unroll
+    for (int w = 0; w < kMaxExperts / 64; ++w) {
+        if (w == wave) {
+            before_a = total_a;
+            before_b = total_b;
+        }
+        total_a += wsum[0][w];
+        total_b += wsum[1][w];
+    }
+    a = sa - a + before_a;
+    b = sb - b + before_b;
+}
+
+// Totals -> scans, execution order, tile tables, host mail.  L.cnt[] and L.nbt[] hold the tokens and
+// the batches of every expert on entry (behind a barrier).  Latency-bound (one workgroup): one
+// thread per expert, prefix sums over the threads, and the tables written by 2^lt threads per
+// expert.  (Thread 0 walking experts and tiles one by one made the scan of 64 experts take 27 us; this 7.)
+template <int T>
+__device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int max_tiles, ScanLds& L) {
+    static_assert(T >= kMaxExperts && T % 64 == 0, "one thread per expert");
     const int E = s.E, tid = threadIdx.x;
-    if (tid == 0) {
-        *nact_p = 0;
-        int o = 0, po = 0;
-        for (int e = 0; e < E; ++e) {
-            off[e] = o;
-            pof[e] = po;
-            o += cnt[e];
-            po += (cnt[e] + kRowBlk - 1) / kRowBlk * kRowBlk;
-        }
-        off[E] = o;
-        pof[E] = po;
+    const int c = tid < E ? L.cnt[tid] : 0;
+    // order of execution: batches desc, tokens desc, index asc; 0 = not activated
+    const unsigned long long key =
+        c > 0 ? ((unsigned long long)L.nbt[tid] << 40) | ((unsigned long long)c << 8) | (unsigned)(255 - tid) : 0ull;
+    if (tid < E) {
+        L.key[tid] = key;
+        L.ord[tid] = -1;
     }
-    for (int e = tid; e < E; e += kThreads) ord[e] = -1;
-    __syncthreads();
-    // execution order: rank of e among the activated experts by (nbatch desc, count desc, e asc)
-    for (int e = tid; e < E; e += kThreads) {
-        if (cnt[e] > 0) {
-            int rank = 0;
-            for (int q = 0; q < E; ++q) {
-                if (q == e || cnt[q] == 0) continue;
-                const bool q_first = nbt[q] > nbt[e] ||
-                                     (nbt[q] == nbt[e] && (cnt[q] > cnt[e] || (cnt[q] == cnt[e] && q < e)));
-                rank += q_first ? 1 : 0;
-            }
-            ord[rank] = e;
-            atomicAdd(nact_p, 1);
-        }
+    int o = c, po = (c + kRowBlk - 1) / kRowBlk * kRowBlk, total, ptotal;
+    scan2(o, po, total, ptotal, L.wsum);
+    if (tid < E) {
+        L.off[tid] = o;
+        L.pof[tid] = po;
+    }
+    if (tid == 0) {
+        L.off[E] = total;
+        L.pof[E] = ptotal;
     }
     __syncthreads();
-    const int nact = *nact_p;
-    for (int e = tid; e < E; e += kThreads) {
-        p.counts[e] = cnt[e];
-        p.offsets[e] = off[e];
-        p.poff[e] = pof[e];
-        p.nbatch[e] = nbt[e];
-        p.exec_order[e] = ord[e];
-        p.mail[e] = cnt[e];
-        p.mail[E + e] = ord[e];
-        p.exp_tile0[e] = 0;
-        p.exp_ntiles[e] = 0;
-        const int b0 = pof[e] / kRowBlk, nb = (cnt[e] + kRowBlk - 1) / kRowBlk;
-        for (int b = 0; b < nb; ++b) p.blk_expert[b0 + b] = e;
+    if (c > 0) {
+        int rank = 0;
+#pragma unroll 8
+        for (int q = 0; q < E; ++q) rank += L.key[q] > key ? 1 : 0;
+        L.ord[rank] = tid;
     }
-    __syncthreads();  // exp_tile0 / exp_ntiles are zeroed before thread 0 fills them
+    __syncthreads();
+    // tiles: shared experts first (they serve every batch), then routed in execution order
+    const int routed_blks = ptotal / kRowBlk, nblk_tok = (s.N + kRowBlk - 1) / kRowBlk;
+    const int per_shared = (nblk_tok + kTileBlks - 1) / kTileBlks, shared_tiles = s.S * per_shared;
+    const int mine = tid < E ? L.ord[tid] : -1;  // expert at place tid of the order
+    const int nb = mine >= 0 ? (L.cnt[mine] + kRowBlk - 1) / kRowBlk : 0;
+    int t0 = (nb + kTileBlks - 1) / kTileBlks, place = mine >= 0 ? 1 : 0, routed_tiles, nact;
+    scan2(t0, place, routed_tiles, nact, L.wsum);
+    t0 += shared_tiles;
+    const int nt = min(shared_tiles + routed_tiles, max_tiles);
+    if (tid < E) {
+        p.counts[tid] = c;
+        p.offsets[tid] = o;
+        p.poff[tid] = po;
+        p.nbatch[tid] = L.nbt[tid];
+        p.exec_order[tid] = mine;
+        p.mail[tid] = c;
+        p.mail[E + tid] = mine;
+        if (mine >= 0) {
+            p.exp_tile0[mine] = t0;
+            p.exp_ntiles[mine] = max(0, min((nb + kTileBlks - 1) / kTileBlks, max_tiles - t0));
+        }
+        if (c == 0) {
+            p.exp_tile0[tid] = 0;
+            p.exp_ntiles[tid] = 0;
+        }
+    }
+    if (tid < s.S) {
+        p.exp_tile0[E + tid] = tid * per_shared;
+        p.exp_ntiles[E + tid] = max(0, min(per_shared, max_tiles - tid * per_shared));
+    }
     if (tid == 0) {
-        p.offsets[E] = off[E];
-        p.poff[E] = pof[E];
+        p.offsets[E] = total;
+        p.poff[E] = ptotal;
         p.mail[2 * E] = nact;
-        // tiles: shared experts first (they serve every batch), then routed in execution order
-        int nt = 0;
-        const int routed_blks = pof[E] / kRowBlk;
-        const int nblk_tok = (s.N + kRowBlk - 1) / kRowBlk;
-        for (int sh = 0; sh < s.S; ++sh) {
-            const int first = nt;  // kept in a register: reading exp_tile0 back would wait on the store
-            p.exp_tile0[E + sh] = first;
-            for (int b = 0; b < nblk_tok && nt < max_tiles; b += kTileBlks) {
-                p.tile_expert[nt] = E + sh;
-                p.tile_xblk[nt] = routed_blks + b;
-                p.tile_hblk[nt] = routed_blks + sh * nblk_tok + b;
-                p.tile_nblk[nt] = min(kTileBlks, nblk_tok - b);
-                ++nt;
-            }
-            p.exp_ntiles[E + sh] = nt - first;
-        }
-        for (int i = 0; i < nact; ++i) {
-            const int e = ord[i];
-            const int b0 = pof[e] / kRowBlk, nb = (cnt[e] + kRowBlk - 1) / kRowBlk;
-            const int first = nt;
-            p.exp_tile0[e] = first;
-            for (int b = 0; b < nb && nt < max_tiles; b += kTileBlks) {
-                p.tile_expert[nt] = e;
-                p.tile_xblk[nt] = b0 + b;
-                p.tile_hblk[nt] = b0 + b;
-                p.tile_nblk[nt] = min(kTileBlks, nb - b);
-                ++nt;
-            }
-            p.exp_ntiles[e] = nt - first;
-        }
         p.meta[0] = nact;
         p.meta[1] = nt;
         p.meta[2] = routed_blks;
         p.meta[3] = s.N;
+    }
+    // 2^lt threads write the row blocks of an expert and the tiles of a place of the order
+    const int lt = 31 - __clz(T / E), part = tid & ((1 << lt) - 1), owner = tid >> lt;
+    // the order's first tiles: handed over through LDS (key[] has been read by all)
+    if (tid < E) L.key[tid] = (unsigned long long)t0;
+    __syncthreads();
+    if (owner < E) {
+        const int b0 = L.pof[owner] / kRowBlk, blocks = (L.cnt[owner] + kRowBlk - 1) / kRowBlk;
+        for (int b = part; b < blocks; b += 1 << lt) p.blk_expert[b0 + b] = owner;
+        const int e = L.ord[owner];
+        if (e >= 0) {
+            const int x0 = L.pof[e] / kRowBlk, n = (L.cnt[e] + kRowBlk - 1) / kRowBlk, first = (int)L.key[owner];
+            for (int i = part; i * kTileBlks < n && first + i < max_tiles; i += 1 << lt) {
+                p.tile_expert[first + i] = e;
+                p.tile_xblk[first + i] = x0 + i * kTileBlks;
+                p.tile_hblk[first + i] = x0 + i * kTileBlks;
+                p.tile_nblk[first + i] = min(kTileBlks, n - i * kTileBlks);
+            }
+        }
+    }
+    for (int i = tid; i < shared_tiles && i < max_tiles; i += T) {
+        const int sh = i / per_shared, b = (i - sh * per_shared) * kTileBlks;
+        p.tile_expert[i] = E + sh;
+        p.tile_xblk[i] = routed_blks + b;
+        p.tile_hblk[i] = routed_blks + sh * nblk_tok + b;
+        p.tile_nblk[i] = min(kTileBlks, nblk_tok - b);
     }
 }
 
@@ -158,18 +242,13 @@ __device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int
 constexpr int kScanPanel = 4096;
 __global__ __launch_bounds__(kThreads) void plan_scan_kernel(Shape s, int nchunks, PlanPtrs p,
                                                              int max_tiles) {
-    __shared__ int32_t cnt[kMaxExperts];
-    __shared__ int32_t nbt[kMaxExperts];
-    __shared__ int32_t off[kMaxExperts + 1];
-    __shared__ int32_t pof[kMaxExperts + 1];
-    __shared__ int32_t ord[kMaxExperts];
-    __shared__ int32_t nact;
+    __shared__ ScanLds L;
     __shared__ int32_t panel[kScanPanel];
     __shared__ unsigned long long pmask[kMaxExperts];
     static_assert(kScanPanel >= kMaxExperts, "a panel holds at least one chunk");
     const int E = s.E;
     for (int e = threadIdx.x; e < E; e += kThreads) {
-        cnt[e] = 0;
+        L.cnt[e] = 0;
         pmask[e] = 0ull;
     }
     __syncthreads();
@@ -185,58 +264,51 @@ __global__ __launch_bounds__(kThreads) void plan_scan_kernel(Shape s, int nchunk
         }
         __syncthreads();
         for (int e = threadIdx.x; e < E; e += kThreads) {
-            int run = cnt[e];
+            int run = L.cnt[e];
             for (int c = 0; c < nc; ++c) {
                 const int v = panel[c * E + e];
                 panel[c * E + e] = run;
                 run += v;
             }
-            cnt[e] = run;
+            L.cnt[e] = run;
         }
         __syncthreads();
         for (int i = threadIdx.x; i < nc * E; i += kThreads) p.blk_base[g0 + i] = panel[i];
         __syncthreads();
     }
-    for (int e = threadIdx.x; e < E; e += kThreads) nbt[e] = __popcll(pmask[e]);
+    for (int e = threadIdx.x; e < E; e += kThreads) L.nbt[e] = __popcll(pmask[e]);
     __syncthreads();
-    scan_body(s, p, max_tiles, cnt, nbt, off, pof, ord, &nact);
+    scan_body<kThreads>(s, p, max_tiles, L);
 }
 
-// Stable position of every assignment of one chunk inside its expert's group.  off[] are the
-// exclusive expert offsets, base[] (may be null = zeros) the tokens of earlier chunks.
-__device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A, int E,
-                                          const PlanPtrs& p, int chunk, int32_t (*seg)[kMaxExperts],
-                                          const int32_t* off, const int32_t* base_of_chunk,
-                                          const int32_t* preloaded = nullptr) {
-    for (int i = threadIdx.x; i < kSegs * kMaxExperts; i += kThreads) (&seg[0][0])[i] = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int base = chunk * kPlanChunk;
+// P3: one block per chunk: stable position of every assignment of the chunk inside its expert's group.
+__global__ __launch_bounds__(kThreads) void plan_rank_kernel(const int32_t* __restrict__ idx, int A,
+                                                             int E, PlanPtrs p) {
+    __shared__ int32_t seg[kSegs][kMaxExperts];  // tokens of expert e in (round, wave) segment
+    __shared__ int32_t base[kMaxExperts];        // position of the chunk's first token of expert e
+    const int wave = threadIdx.x >> 6, a0 = blockIdx.x * kPlanChunk;
     int my_e[kRounds], my_rank[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int a = base + r * kThreads + threadIdx.x;
-        const int e = preloaded ? preloaded[r] : (a < A ? idx[a] : -1);
-        my_e[r] = e;
-        my_rank[r] = 0;
-        bool done = e < 0;
-        // group the wavefront's lanes by expert; every pass retires the leader's group
-        while (true) {
-            const unsigned long long pending = __ballot(!done);
-            if (pending == 0ull) break;
-            const int leader = __ffsll((long long)pending) - 1;
-            const int ev = __shfl(e, leader, 64);
-            const unsigned long long same = __ballot(e == ev);
-            if (e == ev) {
-                my_rank[r] = __popcll(same & ((1ull << lane) - 1ull));
-                if (lane == leader) seg[r * (kThreads / 64) + wave][ev] = __popcll(same);
-                done = true;
-            }
-        }
+        const int a = a0 + r * kThreads + threadIdx.x;
+        my_e[r] = a < A ? idx[a] : -1;
+    }
+    for (int e = threadIdx.x; e < E; e += kThreads) {
+        base[e] = p.offsets[e] + p.blk_base[(size_t)blockIdx.x * E + e];
+#pragma unroll
+        for (int sg = 0; sg < kSegs; ++sg) seg[sg][e] = 0;
+    }
+    __syncthreads();
+    const int ebits = bits_for(E);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const unsigned long long same = same_expert(my_e[r], ebits);
+        my_rank[r] = __popcll(same & lanes_below());
+        if (my_e[r] >= 0 && my_rank[r] == 0) seg[r * (kThreads / 64) + wave][my_e[r]] = __popcll(same);
     }
     __syncthreads();
     for (int e = threadIdx.x; e < E; e += kThreads) {  // exclusive scan over the 16 segments
-        int run = 0;
+        int run = base[e];
 #pragma unroll
         for (int sg = 0; sg < kSegs; ++sg) {
             const int c = seg[sg][e];
@@ -247,64 +319,73 @@ __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int a = base + r * kThreads + threadIdx.x;
-        const int e = my_e[r];
-        if (e >= 0) {
-            const int pos = off[e] + (base_of_chunk ? base_of_chunk[e] : 0) +
-                            seg[r * (kThreads / 64) + wave][e] + my_rank[r];
+        if (my_e[r] >= 0) {
+            const int a = a0 + r * kThreads + threadIdx.x;
+            const int pos = seg[r * (kThreads / 64) + wave][my_e[r]] + my_rank[r];
             p.inv_perm[a] = pos;
             p.perm[pos] = a;
         }
     }
 }
 
-// P3: one block per chunk.
-__global__ __launch_bounds__(kThreads) void plan_rank_kernel(const int32_t* __restrict__ idx, int A,
-                                                             int E, PlanPtrs p) {
-    __shared__ int32_t seg[kSegs][kMaxExperts];  // tokens of expert e in (round, wave) segment
-    rank_body(idx, A, E, p, blockIdx.x, seg, p.offsets, p.blk_base + (size_t)blockIdx.x * E);
-}
-
-// All three phases in one block, for batch groups of at most one chunk of assignments.
-__global__ __launch_bounds__(kThreads) void plan_fused_kernel(const int32_t* __restrict__ idx,
-                                                              Shape s, BatchOffsets bo, PlanPtrs p,
-                                                              int max_tiles) {
-    __shared__ int32_t cnt[kMaxExperts];
+// All three phases in one block of 16 wavefronts, for batch groups of up to kFusedMax assignments.
+// The counts are the sums of the wavefront segments that the ranks need anyway, so nothing but the
+// batch masks goes through LDS atomics.
+constexpr int kFusedThreads = 1024, kFusedRounds = 4, kFusedMax = kFusedThreads * kFusedRounds;
+constexpr int kFusedWaves = kFusedThreads / 64;
+__global__ __launch_bounds__(kFusedThreads) void plan_fused_kernel(const int32_t* __restrict__ idx,
+                                                                   Shape s, BatchOffsets bo, PlanPtrs p,
+                                                                   int max_tiles, int rounds) {
+    __shared__ ScanLds L;
     __shared__ unsigned long long msk[kMaxExperts];
-    __shared__ int32_t nbt[kMaxExperts];
-    __shared__ int32_t off[kMaxExperts + 1];
-    __shared__ int32_t pof[kMaxExperts + 1];
-    __shared__ int32_t ord[kMaxExperts];
-    __shared__ int32_t nact;
-    __shared__ int32_t seg[kSegs][kMaxExperts];
+    __shared__ uint16_t seg[kFusedRounds * kFusedWaves][kMaxExperts];  // tokens of expert e in (round, wave) segment
     __shared__ int32_t sbo[kMaxBatches + 1];
-    const int A = s.N * s.k;
-    int32_t mine[kRounds];  // this thread's assignments, loaded once for both phases
+    const int A = s.N * s.k, E = s.E, wave = threadIdx.x >> 6, segs = rounds * kFusedWaves;
+    int my_e[kFusedRounds], my_rank[kFusedRounds];
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const int a = r * kThreads + threadIdx.x;
-        mine[r] = a < A ? idx[a] : -1;
+    for (int r = 0; r < kFusedRounds; ++r) {
+        const int a = r * kFusedThreads + threadIdx.x;
+        my_e[r] = a < A ? idx[a] : -1;
     }
-    stage_offsets(bo, sbo);
-    for (int e = threadIdx.x; e < s.E; e += kThreads) {
-        cnt[e] = 0;
-        msk[e] = 0ull;
-    }
+    if (threadIdx.x <= kMaxBatches) sbo[threadIdx.x] = bo.v[threadIdx.x];
+    for (int i = threadIdx.x; i < segs * E; i += kFusedThreads) seg[i / E][i % E] = 0;
+    if (threadIdx.x < E) msk[threadIdx.x] = 0ull;
     __syncthreads();
+    const int ebits = bits_for(E);
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const int a = r * kThreads + threadIdx.x;
-        if (mine[r] >= 0) {
-            atomicAdd(&cnt[mine[r]], 1);
-            atomicOr(&msk[mine[r]], 1ull << batch_of(sbo, bo.n, a / s.k));
+    for (int r = 0; r < kFusedRounds; ++r) {
+        my_rank[r] = 0;
+        if (r < rounds) {  // uniform
+            const int a = r * kFusedThreads + threadIdx.x, e = my_e[r];
+            const unsigned long long same = same_expert(e, ebits);
+            my_rank[r] = __popcll(same & lanes_below());
+            if (e >= 0 && my_rank[r] == 0) seg[r * kFusedWaves + wave][e] = (uint16_t)__popcll(same);
+            add_batch(msk, e, a < A ? batch_of(sbo, bo.n, a / s.k) : 0, same);
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < s.E; e += kThreads) nbt[e] = __popcll(msk[e]);
+    if (threadIdx.x < E) {  // exclusive scan over the segments, its total the expert's tokens
+        int run = 0;
+#pragma unroll 8
+        for (int sg = 0; sg < segs; ++sg) {
+            const int c = seg[sg][threadIdx.x];
+            seg[sg][threadIdx.x] = (uint16_t)run;
+            run += c;
+        }
+        L.cnt[threadIdx.x] = run;
+        L.nbt[threadIdx.x] = __popcll(msk[threadIdx.x]);
+    }
     __syncthreads();
-    scan_body(s, p, max_tiles, cnt, nbt, off, pof, ord, &nact);
-    __syncthreads();
-    rank_body(idx, A, s.E, p, 0, seg, off, nullptr, mine);
+    scan_body<kFusedThreads>(s, p, max_tiles, L);
+#pragma unroll
+    for (int r = 0; r < kFusedRounds; ++r) {
+        if (my_e[r] >= 0) {
+            const int a = r * kFusedThreads + threadIdx.x;
+            const int pos = L.off[my_e[r]] + seg[r * kFusedWaves + wave][my_e[r]] + my_rank[r];
+            p.inv_perm[a] = pos;
+            p.perm[pos] = a;
+        }
+    }
 }
 
 // Correlation table update (paper Section 6.2, path length 1): one thread per token adds its
@@ -334,21 +415,16 @@ void launch_corr_update(hipStream_t st, const int32_t* idx_prev, const int32_t* 
 void launch_plan(hipStream_t st, const Shape& s, const BatchOffsets& bo, const PlanPtrs& p,
                  int max_tiles) {
     const int A = s.N * s.k;
-    const int nchunks = (A + kPlanChunk - 1) / kPlanChunk;
-    if (nchunks <= 1) {
-        hipLaunchKernelGGL(plan_fused_kernel, dim3(1), dim3(kThreads), 0, st, p.topk_idx, s, bo, p,
-                           max_tiles);
+    if (A <= kFusedMax) {
+        hipLaunchKernelGGL(plan_fused_kernel, dim3(1), dim3(kFusedThreads), 0, st, p.topk_idx, s, bo, p,
+                           max_tiles, (A + kFusedThreads - 1) / kFusedThreads);
         return;
     }
-    if (nchunks > 0) {
-        hipLaunchKernelGGL(plan_count_kernel, dim3(nchunks), dim3(kThreads), 0, st, p.topk_idx, A,
-                           s.E, s.k, bo, p.blk_counts, p.blk_mask);
-    }
+    const int nchunks = (A + kPlanChunk - 1) / kPlanChunk;
+    hipLaunchKernelGGL(plan_count_kernel, dim3(nchunks), dim3(kThreads), 0, st, p.topk_idx, A, s.E, s.k, bo,
+                       p.blk_counts, p.blk_mask);
     hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(kThreads), 0, st, s, nchunks, p, max_tiles);
-    if (nchunks > 0) {
-        hipLaunchKernelGGL(plan_rank_kernel, dim3(nchunks), dim3(kThreads), 0, st, p.topk_idx, A,
-                           s.E, p);
-    }
+    hipLaunchKernelGGL(plan_rank_kernel, dim3(nchunks), dim3(kThreads), 0, st, p.topk_idx, A, s.E, p);
 }
 
 }  // namespace kmoe

@@ -514,3 +514,30 @@ def test_seeded_sweep_of_small_configurations(seed):
                    batch_tokens=tuple(sizes), zipf_s=1.1 if seed % 2 else 0.0, seed=seed,
                    w_std=float(1.1 / (d * f) ** 0.25))
     run_case(w)
+
+
+@pytest.mark.parametrize("E,k,batches", [
+    (1, 1, (1,)), (2, 2, (511, 1)),                # one expert; 1024 assignments: one round of the fused plan
+    (256, 8, (1, 0, 127)),                         # as many experts as threads per scan, 1024 assignments
+    (64, 6, (31,) * 22 + (0,)),                    # 4092: four rounds, the last one short
+    (7, 4, (1024,)), (7, 4, (1, 1024)),            # 4096 and 4100 assignments: fused and chunked
+    (256, 8, (40,) * 64), (3, 1, (5000, 3))])      # 20 chunks over all experts, 64 batches; few experts
+def test_plan_at_the_edges_of_its_kernels(E, k, batches):
+    """Routing arrays bit for bit where the dispatch kernels change shape (no expert is computed)."""
+    w = I.Workload(f"plan{E}x{k}", "bf16", 64, 64, E, k, batch_tokens=batches, seed=29, w_std=0.2)
+    data, _ = I.gen_layer(w, with_experts=False)
+    ctx = H.make_ctx(w)
+    ctx.set_gate(0, data.wg.to(ctx.device))
+    x, out = data.x.to(ctx.device), H.alloc_route_outputs(w, w.n_tokens, ctx.device)
+    torch.cuda.synchronize()
+    ctx.route(0, x, w.batch_offsets, out)
+    counts, order, n_active = ctx.route_wait()
+    torch.cuda.synchronize()
+    want = H.oracle_layer(w, data, w.batch_offsets, with_output=False)
+    got = {n: getattr(out, n).cpu().numpy() for n in ("logits", "counts", "offsets", "perm", "inv_perm", "exec_order")}
+    got["idx"] = out.topk_idx.cpu().numpy().reshape(w.n_tokens, k)
+    got["w"] = out.topk_w.cpu().numpy().reshape(w.n_tokens, k)
+    H.check_routing(got, want, E)
+    assert counts == list(want.disp.counts) and order == list(want.disp.exec_order)
+    assert n_active == int((want.disp.counts > 0).sum())
+    ctx.close()
