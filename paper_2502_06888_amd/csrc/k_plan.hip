@@ -184,6 +184,9 @@ __device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int
         p.exec_order[tid] = mine;
         p.mail[tid] = c;
         p.mail[E + tid] = mine;
+        if (p.out_counts) p.out_counts[tid] = c;
+        if (p.out_offsets) p.out_offsets[tid] = o;
+        if (p.out_exec_order) p.out_exec_order[tid] = mine;
         if (mine >= 0) {
             p.exp_tile0[mine] = t0;
             p.exp_ntiles[mine] = max(0, min((nb + kTileBlks - 1) / kTileBlks, max_tiles - t0));
@@ -199,6 +202,7 @@ __device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int
     }
     if (tid == 0) {
         p.offsets[E] = total;
+        if (p.out_offsets) p.out_offsets[E] = total;
         p.poff[E] = ptotal;
         p.mail[2 * E] = nact;
         p.meta[0] = nact;
@@ -281,6 +285,13 @@ __global__ __launch_bounds__(kThreads) void plan_scan_kernel(Shape s, int nchunk
     scan_body<kThreads>(s, p, max_tiles, L);
 }
 
+__device__ __forceinline__ void put_rank(const PlanPtrs& p, int a, int pos) {
+    p.inv_perm[a] = pos;
+    p.perm[pos] = a;
+    if (p.out_inv_perm) p.out_inv_perm[a] = pos;
+    if (p.out_perm) p.out_perm[pos] = a;
+}
+
 // P3: one block per chunk: stable position of every assignment of the chunk inside its expert's group.
 __global__ __launch_bounds__(kThreads) void plan_rank_kernel(const int32_t* __restrict__ idx, int A,
                                                              int E, PlanPtrs p) {
@@ -322,8 +333,7 @@ __global__ __launch_bounds__(kThreads) void plan_rank_kernel(const int32_t* __re
         if (my_e[r] >= 0) {
             const int a = a0 + r * kThreads + threadIdx.x;
             const int pos = seg[r * (kThreads / 64) + wave][my_e[r]] + my_rank[r];
-            p.inv_perm[a] = pos;
-            p.perm[pos] = a;
+            put_rank(p, a, pos);
         }
     }
 }
@@ -382,8 +392,7 @@ __global__ __launch_bounds__(kFusedThreads) void plan_fused_kernel(const int32_t
         if (my_e[r] >= 0) {
             const int a = r * kFusedThreads + threadIdx.x;
             const int pos = L.off[my_e[r]] + seg[r * kFusedWaves + wave][my_e[r]] + my_rank[r];
-            p.inv_perm[a] = pos;
-            p.perm[pos] = a;
+            put_rank(p, a, pos);
         }
     }
 }

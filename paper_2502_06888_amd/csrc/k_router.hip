@@ -60,11 +60,17 @@ __device__ __forceinline__ bool better(const Cand& a, const Cand& b) {
     return a.v > b.v || (a.v == b.v && a.e < b.e);
 }
 
+__device__ __forceinline__ void put_winner(const RouterOut& out, size_t at, int e, float w) {
+    out.idx[at] = e;
+    out.w[at] = w;
+    if (out.idx2) out.idx2[at] = e;
+    if (out.w2) out.w2[at] = w;
+}
+
 // Top-k by (logit desc, index asc) and the routing weights of one token; every lane holds in
 // mine[s] the logit of expert lane + 64 s.  One wavefront.
 __device__ __forceinline__ void select_and_write(const float (&mine)[4], int lane, int t, int E, int k,
-                                                 int renorm, int32_t* __restrict__ idx_out,
-                                                 float* __restrict__ w_out) {
+                                                 int renorm, const RouterOut& out) {
     bool taken[4] = {false, false, false, false};
     float selv[kMaxTopK];
     int sele[kMaxTopK];
@@ -113,11 +119,39 @@ __device__ __forceinline__ void select_and_write(const float (&mine)[4], int lan
 #pragma unroll
         for (int j = 0; j < kMaxTopK; ++j) {
             if (j < k) {
-                idx_out[(size_t)t * k + j] = sele[j];
-                w_out[(size_t)t * k + j] = expf(selv[j] - mx) / den;
+                put_winner(out, (size_t)t * k + j, sele[j], expf(selv[j] - mx) / den);
             }
         }
     }
+}
+
+// The same for at most 64 experts with renormalised weights (v = the logit of expert `lane`): the rank
+// of every expert is counted instead of selecting k times with a wavefront arg-max (12 dependent
+// cross-lane moves through LDS per winner: at k = 6 half of the time of a 64-expert router).  Ranks
+// come from a total order on (logit, index): the logit's bits mapped to an unsigned integer that
+// grows with it, zeros of both signs alike.
+__device__ __forceinline__ void rank_and_write(float v, int lane, int t, int E, int k, const RouterOut& out) {
+    const uint32_t u = __float_as_uint(v + 0.f);  // -0 -> +0
+    // lanes without an expert: below every key, and behind every expert on a tie
+    const uint32_t key = lane >= E ? 0u : u & 0x80000000u ? ~u : u | 0x80000000u;
+    int rank = 0;
+    for (int e0 = 0; e0 < E; e0 += 8) {
+#pragma unroll
+        for (int e = e0; e < e0 + 8; ++e) {
+            const uint32_t o = __builtin_amdgcn_readlane(key, e);
+            rank += o > key || (o == key && e < lane) ? 1 : 0;
+        }
+    }
+    if (lane >= E) rank = 64;
+    const unsigned long long first = __ballot(rank == 0);
+    const float mx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), __ffsll((long long)first) - 1));
+    const float ex = expf(v - mx);
+    float den = 0.f;
+    for (int j = 0; j < k; ++j) {  // in order of rank
+        const unsigned long long w = __ballot(rank == j);
+        den += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ex), __ffsll((long long)w) - 1));
+    }
+    if (rank < k) put_winner(out, (size_t)t * k + rank, lane, ex / den);
 }
 
 // Sum over the 64 lanes of eight values at once, in the order of the xor butterfly (32, 16, ..., 1)
@@ -157,8 +191,7 @@ __device__ __forceinline__ void butterfly8(const float (&a)[kEG], int lane, floa
 // writes.  Same order (logit descending, index ascending) and the same weight arithmetic as
 // select_and_write with renorm set.
 __device__ __forceinline__ void select_uniform_and_write(const float (&lg)[kEG], int E, int lane, int t,
-                                                         int k, int32_t* __restrict__ idx_out,
-                                                         float* __restrict__ w_out) {
+                                                         int k, const RouterOut& out) {
     unsigned taken = 0u;
     float selv[kMaxTopK];
     int sele[kMaxTopK];
@@ -191,8 +224,7 @@ __device__ __forceinline__ void select_uniform_and_write(const float (&lg)[kEG],
 #pragma unroll
         for (int j = 0; j < kMaxTopK; ++j) {
             if (j < k) {
-                idx_out[(size_t)t * k + j] = sele[j];
-                w_out[(size_t)t * k + j] = expf(selv[j] - mx) / den;
+                put_winner(out, (size_t)t * k + j, sele[j], expf(selv[j] - mx) / den);
             }
         }
     }
@@ -201,7 +233,7 @@ __device__ __forceinline__ void select_uniform_and_write(const float (&lg)[kEG],
 template <typename T>
 __global__ __launch_bounds__(kRouterWaves * 64) void router_kernel(
     const T* __restrict__ X, const T* __restrict__ Wg, int N, int d, int E, int k, int renorm,
-    float* __restrict__ logits_out, int32_t* __restrict__ idx_out, float* __restrict__ w_out) {
+    RouterOut out) {
     constexpr int V = Chunk<T>::V;
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * kRouterWaves + (threadIdx.x >> 6);
@@ -258,7 +290,7 @@ __global__ __launch_bounds__(kRouterWaves * 64) void router_kernel(
         for (int j = 0; j < kEG; ++j) {
             const int e = e0 + j;
             if (e < E) {
-                if (logits_out != nullptr && lane == 0) logits_out[(size_t)t * E + e] = tot[j];
+                if (out.logits != nullptr && lane == 0) out.logits[(size_t)t * E + e] = tot[j];
                 if ((e & 63) == lane) {
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
@@ -267,12 +299,12 @@ __global__ __launch_bounds__(kRouterWaves * 64) void router_kernel(
             }
         }
         if (E <= kEG && renorm) {  // one group holds every expert: select in registers
-            select_uniform_and_write(tot, E, lane, t, k, idx_out, w_out);
+            select_uniform_and_write(tot, E, lane, t, k, out);
             return;
         }
     }
 
-    select_and_write(mine, lane, t, E, k, renorm, idx_out, w_out);
+    select_and_write(mine, lane, t, E, k, renorm, out);
 }
 
 
@@ -287,7 +319,7 @@ constexpr int kMCB = 2;  // vectors per lane loaded together
 template <typename T>
 __global__ __launch_bounds__(kRouterWaves * 64) void router_multi_kernel(
     const T* __restrict__ X, const T* __restrict__ Wg, int N, int d, int E, int k, int renorm,
-    float* __restrict__ logits_out, int32_t* __restrict__ idx_out, float* __restrict__ w_out) {
+    RouterOut out) {
     constexpr int V = Chunk<T>::V;
     const int lane = threadIdx.x & 63;
     const int t0 = (blockIdx.x * kRouterWaves + (threadIdx.x >> 6)) * kMT;
@@ -346,7 +378,7 @@ __global__ __launch_bounds__(kRouterWaves * 64) void router_multi_kernel(
 #pragma unroll
             for (int j = 0; j < kEG; ++j) {
                 const int e = e0 + j;
-                if (logits_out != nullptr && lane == 0 && t0 + q < N) logits_out[(size_t)(t0 + q) * E + e] = tot[j];
+                if (out.logits != nullptr && lane == 0 && t0 + q < N) out.logits[(size_t)(t0 + q) * E + e] = tot[j];
                 if ((e & 63) == lane) {
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
@@ -354,15 +386,92 @@ __global__ __launch_bounds__(kRouterWaves * 64) void router_multi_kernel(
                 }
             }
             if (E <= kEG && renorm && t0 + q < N)  // one group holds every expert: select in registers
-                select_uniform_and_write(tot, E, lane, t0 + q, k, idx_out, w_out);
+                select_uniform_and_write(tot, E, lane, t0 + q, k, out);
         }
     }
     if (E <= kEG && renorm) return;
 #pragma unroll
     for (int q = 0; q < kMT; ++q)
-        if (t0 + q < N) select_and_write(mine[q], lane, t0 + q, E, k, renorm, idx_out, w_out);
+        if (t0 + q < N) select_and_write(mine[q], lane, t0 + q, E, k, renorm, out);
 }
 
+
+// The same arithmetic for more than kEG experts: a workgroup of kWW wavefronts serves MT tokens and its
+// wavefronts share the experts, kEG at a time, so that a gate vector is loaded once per MT tokens and
+// no wavefront walks all experts (shapes as for router_multi_kernel).  The logits meet in LDS and
+// wavefront q selects for token q.  Bound by the gate's re-reads from L2 and by latency: 512 tokens,
+// 64 experts, width 2048 took 24-36 us with one token per workgroup (134 MB of gate rows).
+constexpr int kWW = 8;
+template <typename T, int MT>
+__global__ __launch_bounds__(kWW * 64) void router_wide_kernel(
+    const T* __restrict__ X, const T* __restrict__ Wg, int N, int d, int E, int k, int renorm,
+    RouterOut out) {
+    constexpr int V = Chunk<T>::V;
+    static_assert(MT <= kWW, "a wavefront per token selects");
+    __shared__ float slog[MT][kMaxExperts];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int t0 = blockIdx.x * MT;
+    const int cpl = d / (V * 64);  // vectors per lane, a multiple of kMCB
+    const T* xrow[MT];
+#pragma unroll
+    for (int q = 0; q < MT; ++q) xrow[q] = X + (size_t)min(t0 + q, N - 1) * d + (size_t)lane * V;
+    for (int e0 = wave * kEG; e0 < E; e0 += kWW * kEG) {
+        float acc[MT][kEG];
+#pragma unroll
+        for (int q = 0; q < MT; ++q)
+#pragma unroll
+            for (int j = 0; j < kEG; ++j) acc[q][j] = 0.f;
+        const T* wrow = Wg + (size_t)e0 * d + (size_t)lane * V;
+        for (int c0 = 0; c0 < cpl; c0 += kMCB) {
+            typename Chunk<T>::Raw xr[MT][kMCB], wr[kEG][kMCB];
+#pragma unroll
+            for (int q = 0; q < MT; ++q)
+#pragma unroll
+                for (int b = 0; b < kMCB; ++b) xr[q][b] = Chunk<T>::raw(xrow[q] + (size_t)(c0 + b) * 64 * V);
+#pragma unroll
+            for (int j = 0; j < kEG; ++j)
+#pragma unroll
+                for (int b = 0; b < kMCB; ++b)
+                    wr[j][b] = Chunk<T>::raw(wrow + (size_t)j * d + (size_t)(c0 + b) * 64 * V);
+#pragma unroll
+            for (int b = 0; b < kMCB; ++b) {
+                float xv[MT][V];
+#pragma unroll
+                for (int q = 0; q < MT; ++q) Chunk<T>::widen(xr[q][b], xv[q]);
+#pragma unroll
+                for (int j = 0; j < kEG; ++j) {
+                    float wv[V];
+                    Chunk<T>::widen(wr[j][b], wv);
+#pragma unroll
+                    for (int q = 0; q < MT; ++q)
+#pragma unroll
+                        for (int i = 0; i < V; ++i) acc[q][j] = __builtin_fmaf(xv[q][i], wv[i], acc[q][j]);
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+            float tot[kEG];
+            butterfly8(acc[q], lane, tot);
+#pragma unroll
+            for (int j = 0; j < kEG; ++j)  // lane j of the group keeps the logit of expert e0 + j
+                if (lane == j) {
+                    slog[q][e0 + j] = tot[j];
+                    if (out.logits != nullptr && t0 + q < N) out.logits[(size_t)(t0 + q) * E + e0 + j] = tot[j];
+                }
+        }
+    }
+    __syncthreads();
+    if (wave >= MT || t0 + wave >= N) return;
+    if (E <= 64 && renorm) {
+        rank_and_write(lane < E ? slog[wave][lane] : 0.f, lane, t0 + wave, E, k, out);
+        return;
+    }
+    float mine[4];
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) mine[s4] = lane + 64 * s4 < E ? slog[wave][lane + 64 * s4] : 0.f;
+    select_and_write(mine, lane, t0 + wave, E, k, renorm, out);
+}
 
 // The same arithmetic with one workgroup per token: wavefront w scores experts w*kSG, w*kSG+1,
 // then (w+kSW)*kSG, ...; the token's row stays in registers (at most kSC vectors per lane) and
@@ -375,7 +484,7 @@ constexpr int kSC = 16;  // vectors of the row per lane, at most (template param
 template <typename T, int SC>
 __global__ __launch_bounds__(kSW * 64) void router_split_kernel(
     const T* __restrict__ X, const T* __restrict__ Wg, int N, int d, int E, int k, int renorm,
-    float* __restrict__ logits_out, int32_t* __restrict__ idx_out, float* __restrict__ w_out) {
+    RouterOut out) {
     constexpr int V = Chunk<T>::V;
     __shared__ float slog[kMaxExperts];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -419,7 +528,7 @@ __global__ __launch_bounds__(kSW * 64) void router_split_kernel(
             const int e = e0 + j;
             if (e < E && lane == 0) {
                 slog[e] = acc[j];
-                if (logits_out != nullptr) logits_out[(size_t)t * E + e] = acc[j];
+                if (out.logits != nullptr) out.logits[(size_t)t * E + e] = acc[j];
             }
         }
     }
@@ -429,27 +538,39 @@ __global__ __launch_bounds__(kSW * 64) void router_split_kernel(
         float lg[kEG];
 #pragma unroll
         for (int e = 0; e < kEG; ++e) lg[e] = e < E ? slog[e] : 0.f;
-        select_uniform_and_write(lg, E, lane, t, k, idx_out, w_out);
+        select_uniform_and_write(lg, E, lane, t, k, out);
         return;
     }
     float mine[4];
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) mine[s4] = lane + 64 * s4 < E ? slog[lane + 64 * s4] : 0.f;
-    select_and_write(mine, lane, t, E, k, renorm, idx_out, w_out);
+    select_and_write(mine, lane, t, E, k, renorm, out);
 }
 
 }  // namespace
 
 void launch_router(hipStream_t st, int dtype, const void* x, const void* wg, const Shape& s,
-                   float* logits_out, int32_t* idx_out, float* w_out) {
+                   const RouterOut& out) {
     if (s.N <= 0) return;
     const int V = dtype == 0 ? 4 : 8;
     const int cpl = (s.d / V + 63) / 64;
+    // more experts than one group: the tokens of a workgroup share the gate rows.  Few tokens spread over
+    // more workgroups instead (one token each below 256, two below 1024)
+    if (dtype != 0 && s.d % (8 * 64 * kMCB) == 0 && s.E % kEG == 0 && s.E > kEG) {
+        const int mt = s.N < 256 ? 1 : s.N < 1024 ? 2 : 4;
+        const dim3 grid((s.N + mt - 1) / mt), block(kWW * 64);
+#define KMOE_WIDE(MT)                                                                                     \
+    hipLaunchKernelGGL((router_wide_kernel<bf16raw, MT>), grid, block, 0, st, (const bf16raw*)x,            \
+                       (const bf16raw*)wg, s.N, s.d, s.E, s.k, s.renorm, out)
+        if (mt == 1) KMOE_WIDE(1); else if (mt == 2) KMOE_WIDE(2); else KMOE_WIDE(4);
+#undef KMOE_WIDE
+        return;
+    }
     if (s.N <= 2048 && cpl <= kSC) {  // small batch group: one workgroup per token
         dim3 grid(s.N), block(kSW * 64);
 #define KMOE_SPLIT(T, SC)                                                                              \
     hipLaunchKernelGGL((router_split_kernel<T, SC>), grid, block, 0, st, (const T*)x, (const T*)wg, s.N, \
-                       s.d, s.E, s.k, s.renorm, logits_out, idx_out, w_out)
+                       s.d, s.E, s.k, s.renorm, out)
         if (dtype == 0) {
             if (cpl <= 2) KMOE_SPLIT(float, 2); else if (cpl <= 8) KMOE_SPLIT(float, 8); else KMOE_SPLIT(float, 16);
         } else {
@@ -463,19 +584,16 @@ void launch_router(hipStream_t st, int dtype, const void* x, const void* wg, con
         const int per_block = kRouterWaves * kMT;
         dim3 grid((s.N + per_block - 1) / per_block), block(kRouterWaves * 64);
         hipLaunchKernelGGL(router_multi_kernel<bf16raw>, grid, block, 0, st, (const bf16raw*)x,
-                           (const bf16raw*)wg, s.N, s.d, s.E, s.k, s.renorm, logits_out, idx_out,
-                           w_out);
+                           (const bf16raw*)wg, s.N, s.d, s.E, s.k, s.renorm, out);
         return;
     }
     dim3 grid((s.N + kRouterWaves - 1) / kRouterWaves), block(kRouterWaves * 64);
     if (dtype == 0) {
         hipLaunchKernelGGL(router_kernel<float>, grid, block, 0, st, (const float*)x,
-                           (const float*)wg, s.N, s.d, s.E, s.k, s.renorm, logits_out, idx_out,
-                           w_out);
+                           (const float*)wg, s.N, s.d, s.E, s.k, s.renorm, out);
     } else {
         hipLaunchKernelGGL(router_kernel<bf16raw>, grid, block, 0, st, (const bf16raw*)x,
-                           (const bf16raw*)wg, s.N, s.d, s.E, s.k, s.renorm, logits_out, idx_out,
-                           w_out);
+                           (const bf16raw*)wg, s.N, s.d, s.E, s.k, s.renorm, out);
     }
 }
 

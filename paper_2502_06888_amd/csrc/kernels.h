@@ -46,6 +46,18 @@ struct PlanPtrs {
     int32_t* exp_ntiles;  // [E+S]
     int32_t* blk_expert;  // [max_rowblks] routed expert owning a row block
     int32_t* mail;        // [2E+1] counts, exec_order, n_active: the host's mailbox (pinned, written by the plan)
+    // the caller's own copies of counts, offsets, perm, inv_perm and exec_order (null: not wanted),
+    // written by the same kernels: a copy launch per array cost 4-5 us each
+    int32_t *out_counts, *out_offsets, *out_perm, *out_inv_perm, *out_exec_order;
+};
+
+// Where the router writes a token's winners and weights: the plan's arrays and the caller's (may be null).
+struct RouterOut {
+    float* logits;    // null: not wanted
+    int32_t* idx;
+    float* w;
+    int32_t* idx2;
+    float* w2;
 };
 
 struct Shape {
@@ -56,7 +68,7 @@ struct Shape {
 
 // ---- router -------------------------------------------------------------------------------
 void launch_router(hipStream_t st, int dtype, const void* x, const void* wg, const Shape& s,
-                   float* logits_out, int32_t* idx_out, float* w_out);
+                   const RouterOut& out);
 
 // ---- dispatch plan ------------------------------------------------------------------------
 void launch_plan(hipStream_t st, const Shape& s, const BatchOffsets& bo, const PlanPtrs& p,

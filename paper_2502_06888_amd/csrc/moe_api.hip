@@ -276,6 +276,18 @@ bool is_pinned_host(const void* p) {
     return at.type == hipMemoryTypeHost;
 }
 
+// Memory of the current device: an output there is written by the kernels themselves; any other is
+// filled by a copy.
+bool on_this_device(const void* p) {
+    hipPointerAttribute_t at;
+    int dev = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
 Shape make_shape(const moe_ctx* c, int n_tokens) {
     Shape s;
     s.N = n_tokens;
@@ -810,25 +822,39 @@ moe_status moe_route(moe_ctx* ctx, int32_t layer, const void* x_dev,
     const bool prof = ctx->profiling;
     const int span = span_open(ctx, st, 1);
     if (prof) (void)hipEventRecord(ctx->pev[0], st);
-    launch_router(st, ctx->cfg.dtype, x_dev, ls.wg, s, logits_dev, ctx->plan.topk_idx, ctx->plan.topk_w);
+    // outputs the caller asks for: dst is written by the kernel (direct) or copied afterwards
+    struct Wanted {
+        void* dst;
+        const void* src;
+        size_t bytes;
+        bool direct;
+    };
+    const size_t A = (size_t)N * k;
+    PlanPtrs plan = ctx->plan;
+    Wanted wanted[] = {{topk_idx_dev, plan.topk_idx, A * 4, false},
+                       {topk_w_dev, plan.topk_w, A * 4, false},
+                       {counts_dev, plan.counts, (size_t)E * 4, false},
+                       {offsets_dev, plan.offsets, (size_t)(E + 1) * 4, false},
+                       {perm_dev, plan.perm, A * 4, false},
+                       {inv_perm_dev, plan.inv_perm, A * 4, false},
+                       {exec_order_dev, plan.exec_order, (size_t)E * 4, false}};
+    for (Wanted& o : wanted) o.direct = o.dst && o.bytes > 0 && on_this_device(o.dst);
+    auto direct = [&](int i) { return wanted[i].direct ? (int32_t*)wanted[i].dst : nullptr; };
+    launch_router(st, ctx->cfg.dtype, x_dev, ls.wg, s,
+                  RouterOut{logits_dev, plan.topk_idx, plan.topk_w, direct(0), (float*)direct(1)});
     if (prof) (void)hipEventRecord(ctx->pev[1], st);
-    launch_plan(st, s, bo, ctx->plan, ctx->L.max_tiles);
+    plan.out_counts = direct(2);
+    plan.out_offsets = direct(3);
+    plan.out_perm = direct(4);
+    plan.out_inv_perm = direct(5);
+    plan.out_exec_order = direct(6);
+    launch_plan(st, s, bo, plan, ctx->L.max_tiles);
     if (prof) (void)hipEventRecord(ctx->pev[2], st);
     span_close(ctx, st, span);
     ctx->prof_route = prof;
     HIP_TRY(ctx, hipGetLastError());
-    const size_t A = (size_t)N * k;
-    auto out = [&](void* dst, const void* src, size_t bytes) -> hipError_t {
-        if (!dst || bytes == 0) return hipSuccess;
-        return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, st);
-    };
-    HIP_TRY(ctx, out(topk_idx_dev, ctx->plan.topk_idx, A * 4));
-    HIP_TRY(ctx, out(topk_w_dev, ctx->plan.topk_w, A * 4));
-    HIP_TRY(ctx, out(counts_dev, ctx->plan.counts, (size_t)E * 4));
-    HIP_TRY(ctx, out(offsets_dev, ctx->plan.offsets, (size_t)(E + 1) * 4));
-    HIP_TRY(ctx, out(perm_dev, ctx->plan.perm, A * 4));
-    HIP_TRY(ctx, out(inv_perm_dev, ctx->plan.inv_perm, A * 4));
-    HIP_TRY(ctx, out(exec_order_dev, ctx->plan.exec_order, (size_t)E * 4));
+    for (const Wanted& o : wanted)
+        if (o.dst && o.bytes > 0 && !o.direct) HIP_TRY(ctx, hipMemcpyAsync(o.dst, o.src, o.bytes, hipMemcpyDeviceToDevice, st));
     if (ctx->corr_learn) {
         int32_t* prev = (int32_t*)(ctx->ws + ctx->L.prev_idx);
         if (layer > 0 && ctx->prev_idx_layer == layer - 1 && ctx->prev_idx_tokens == N && N > 0) {
@@ -1550,7 +1576,7 @@ moe_status moe_route_static(void* stream, int32_t dtype, const void* x_dev, cons
     s.renorm = renormalize ? 1 : 0;
     s.max_rowblks = (int32_t)max_rowblks;
     hipStream_t st = (hipStream_t)stream;
-    launch_router(st, dtype, x_dev, wg_dev, s, logits_dev, p.topk_idx, p.topk_w);
+    launch_router(st, dtype, x_dev, wg_dev, s, RouterOut{logits_dev, p.topk_idx, p.topk_w, nullptr, nullptr});
     launch_plan(st, s, bo, p, max_tiles);
     HIP_TRY(nullptr, hipGetLastError());
     return MOE_OK;
