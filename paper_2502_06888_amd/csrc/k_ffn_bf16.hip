@@ -135,12 +135,16 @@ struct XMap {
 };
 
 // When PASSES * T fits one LDS buffer the stores need no guard.
+// Units of one LDS buffer: what the passes of a stage write, at most a whole tile's stage.
+template <int PASSES, int T>
+constexpr int buf_units() { return PASSES * T < kBufUnits ? PASSES * T : kBufUnits; }
+
 template <int PASSES, int T>
 __device__ __forceinline__ void store_x(const TileCtx& c, const u32x4 (&xr)[PASSES], int buf) {
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
         const int u = (int)threadIdx.x + p * T;
-        if (PASSES * T <= kBufUnits || u < kBufUnits) c.lds[buf * kBufUnits + u] = xr[p];
+        if (PASSES * T <= kBufUnits || u < kBufUnits) c.lds[buf * buf_units<PASSES, T>() + u] = xr[p];
     }
 }
 // HT = 0: bf16 operands; HT = 1: fp16 operands (down projection with H carried as fp16).
@@ -253,9 +257,10 @@ __device__ __forceinline__ void stage_mfma(const u32x4* L, u32x4 (&w)[SX][U], gp
 
 // Register budget of one shape: the weight ring is RING steps deep (U KiB per step in flight
 // per wavefront), the activation look-ahead DX stages.
-template <int NB, int WAVES, int U>
+template <int NB, int WAVES, int U, int TB>
 struct Shape2 {
-    static constexpr int RING = (U == 1) ? (NB <= 5 ? 16 : 8) : 8;
+    // (short tiles: twice the wavefronts, half the registers of each)
+    static constexpr int RING = (U == 1 && TB == kTileBlks) ? (NB <= 5 ? 16 : 8) : 8;
     // two stages ahead wherever the registers allow: small tiles, and the two-unit shape (one
     // wavefront per SIMD, accumulators in AGPRs), whose full tiles miss L2 most often
     static constexpr int DX = (NB <= 5 || U == 2) ? 2 : 1;
@@ -263,18 +268,18 @@ struct Shape2 {
 
 // Registers of the software pipeline of one tile pass: the weight ring (RS stages of SX steps,
 // U units) and the activations in flight to LDS (DX stages ahead).
-template <int NB, int WAVES, int U, int SX>
+template <int NB, int WAVES, int U, int SX, int TB>
 struct Pipe {
     static constexpr int T = WAVES * 64;
     static constexpr int PASSES = (NB * kBlkStageUnits + T - 1) / T;
-    static constexpr int RS = Shape2<NB, WAVES, U>::RING / SX;
+    static constexpr int RS = Shape2<NB, WAVES, U, TB>::RING / SX;
     // Activation look-ahead in stages.  The memory counter retires loads in issue order, so the
     // wait for a stage's activations (before they are stored to LDS) also waits for every
     // weight load issued before them.  With a look-ahead of one stage that cuts the useful
     // depth of the weight ring to one stage whatever its size; with DX stages between the issue
     // of the activation loads and their wait, all older weight loads have been consumed by
     // then and the ring keeps its full depth.
-    static constexpr int DX = Shape2<NB, WAVES, U>::DX;
+    static constexpr int DX = Shape2<NB, WAVES, U, TB>::DX;
     static constexpr int G = RS > DX ? RS : DX;  // stages per unrolled group (RS, DX in {1,2,4})
     static_assert(RS >= 1 && G % RS == 0 && G % DX == 0, "group must cycle ring and look-ahead");
     u32x4 wr[RS][SX][U];
@@ -294,9 +299,9 @@ struct Pipe {
 // loop head are the same on entry and on the back edge.  Nothing is waited for here: a
 // workgroup calls this for its next pass before the epilogue of the current one, so the
 // memory latency of the ring fill hides behind the epilogue.
-template <int NB, int WAVES, int U, int SX, int PL>
-__device__ __forceinline__ void open_pass(const TileCtx& c, Pipe<NB, WAVES, U, SX>& pp) {
-    using P = Pipe<NB, WAVES, U, SX>;
+template <int NB, int WAVES, int U, int SX, int PL, int TB>
+__device__ __forceinline__ void open_pass(const TileCtx& c, Pipe<NB, WAVES, U, SX, TB>& pp) {
+    using P = Pipe<NB, WAVES, U, SX, TB>;
 #pragma unroll
     for (int i = 0; i < P::G; ++i) {
         if (i < P::DX) pp.template load<PL>(c, i, c.k0 + i * SX);
@@ -313,11 +318,11 @@ __device__ __forceinline__ void open_pass(const TileCtx& c, Pipe<NB, WAVES, U, S
 
 // One pass over the reduction range of the tile for the U units of every wavefront; the pass
 // must have been opened.  On return all LDS reads of the pass are behind a barrier.
-template <int MODE, int NB, int WAVES, int U, int SX, int PL, int HT = 0>
-__device__ __forceinline__ void run_pass(const TileCtx& c, Pipe<NB, WAVES, U, SX>& pp,
+template <int MODE, int NB, int WAVES, int U, int SX, int PL, int TB, int HT = 0>
+__device__ __forceinline__ void run_pass(const TileCtx& c, Pipe<NB, WAVES, U, SX, TB>& pp,
                                          f32x16 (&acc)[U][NB]) {
     static_assert(SX * PL == kFragsPerBlk, "stage geometry");
-    using P = Pipe<NB, WAVES, U, SX>;
+    using P = Pipe<NB, WAVES, U, SX, TB>;
     constexpr int T = P::T, PASSES = P::PASSES, RS = P::RS, DX = P::DX, G = P::G;
     constexpr int D = 3;
     const int lane = threadIdx.x & 63;
@@ -342,10 +347,10 @@ __device__ __forceinline__ void run_pass(const TileCtx& c, Pipe<NB, WAVES, U, SX
         for (int g = 0; g < G; ++g) {
             const int kk = k + g * SX;
             __builtin_amdgcn_sched_barrier(0);
-            const u32x4* L = c.lds + buf * kBufUnits + lane;
+            const u32x4* L = c.lds + buf * buf_units<PASSES, T>() + lane;
             stage_mfma<MODE, NB, U, SX, PL, D, HT, PASSES, T, DX>(
                 L, pp.wr[g % RS], c.wbase + (size_t)(kk + RS * SX) * 64, c.ustride, acc,
-                c.lds + (buf ^ 1) * kBufUnits, pp.xr[(g + 1) % DX], c, pp.xm, kk + DX * SX, pp.xr[g % DX]);
+                c.lds + (buf ^ 1) * buf_units<PASSES, T>(), pp.xr[(g + 1) % DX], c, pp.xm, kk + DX * SX, pp.xr[g % DX]);
             __builtin_amdgcn_sched_barrier(0);
             __syncthreads();
             buf ^= 1;
@@ -360,7 +365,7 @@ __device__ __forceinline__ void run_pass(const TileCtx& c, Pipe<NB, WAVES, U, SX
                 const bool more = kk + SX < c.k1;
                 if (kk + DX * SX < c.k1)
                     pp.template load<PL>(c, g % DX, kk + DX * SX);
-                const u32x4* L = c.lds + buf * kBufUnits + lane;
+                const u32x4* L = c.lds + buf * buf_units<PASSES, T>() + lane;
 #pragma unroll
                 for (int j = 0; j < SX; ++j) {
                     if (kk + j < c.k1) {
@@ -408,8 +413,12 @@ __device__ __forceinline__ const uint8_t* blob_of(const FfnArgs& a, int e) {
 // weight reads are L2 hits behind the first workgroup of a column.  (Dealing the panels round
 // robin instead, so that all XCDs work on the same expert at the same time and share its weights
 // through the memory-side cache, was measured 10-20 % slower: every XCD then asks the same
-// memory channels for the same lines at once.)
+// memory channels for the same lines at once.)  Short tiles: the tiles of an expert are adjacent
+// in the tile table, and for each item all of them come before the next item, so that the tiles of a
+// busy (or shared) expert read a weight stream together (64 + 2 experts of 2048 x 1408, 512 tokens: up
+// projection 205 -> 188 us, 4.5 TB/s from HBM by the counters; tall tiles 209 us).
 constexpr int kPanelTiles = 4, kPanelCols = 8;
+template <int TB>
 __device__ __forceinline__ Wg locate(const FfnArgs& a, int n_groups, int split) {
     Wg w;
     const int ntile = a.tile_count ? *a.tile_count : a.tile_count_v;
@@ -434,6 +443,14 @@ __device__ __forceinline__ Wg locate(const FfnArgs& a, int n_groups, int split) 
         r = L % per_tile;
     }
     w.tile = (a.tile_first ? *a.tile_first : a.tile_first_v) + tile;
+    if (TB == kShortBlks && w.live) {
+        const int e = a.tile_expert[w.tile], n = a.exp_ntiles[e];
+        if (n > 1) {
+            const int first = a.exp_tile0[e], l = (w.tile - first) * per_tile + r;
+            w.tile = first + l % n;
+            r = l / n;
+        }
+    }
     w.sp = r / n_groups;
     w.grp = r % n_groups;
     return w;
@@ -555,37 +572,52 @@ __device__ __forceinline__ void store_down(const FfnArgs& a, const f32x16 (&acc)
 // run's loads issued before the epilogue, were measured to gain nothing, and the loop around
 // the reduction loop made the compiler wait in every stage for reloads it had placed on the
 // outer back edge.)
-template <int MODE, int NB, int WAVES, int U, int PL, int HT = 0>
+template <int MODE, int NB, int WAVES, int U, int PL, int TB, int HT = 0>
 __device__ __forceinline__ void run_tile(const FfnArgs& a, TileCtx c, gptr wsection, int n_units,
                                          int grp, int hblk0, int sp, int expert, float scale) {
     constexpr int SX = 8 / PL;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    Pipe<NB, WAVES, U, SX> pp;
+    Pipe<NB, WAVES, U, SX, TB> pp;
     f32x16 acc[U][NB];
     const int unit0 = (grp * WAVES + wave) * U;
     const int wunit = min(unit0, n_units - U);
     c.wbase = wsection + (size_t)wunit * c.ustride + lane;
     pp.init(c);
-    open_pass<NB, WAVES, U, SX, PL>(c, pp);
-    run_pass<MODE, NB, WAVES, U, SX, PL, HT>(c, pp, acc);
+    open_pass<NB, WAVES, U, SX, PL, TB>(c, pp);
+    run_pass<MODE, NB, WAVES, U, SX, PL, TB, HT>(c, pp, acc);
     if (MODE == 0)
         store_up<NB, WAVES, U>(a, acc, c.nblk, wunit, unit0, hblk0, expert, c.lds);
     else
         store_down<NB, U>(a, acc, c.nblk, wunit, unit0, hblk0, sp, scale);
 }
 
+// Row-block classes of a tile of up to TB blocks.
 #define NB_SWITCH(CALL)                       \
-    if (nblk <= 2) { CALL(2); }               \
+    if constexpr (TB == kShortBlks) {         \
+        if (nblk <= 1) { CALL(1); }           \
+        else { CALL(2); }                     \
+    }                                         \
+    else if (nblk <= 2) { CALL(2); }          \
     else if (nblk <= 4) { CALL(4); }          \
     else if (nblk <= 5) { CALL(5); }          \
     else if (nblk <= 6) { CALL(6); }          \
     else { CALL(8); }
-static_assert(kTileBlks == 8, "row-block classes above cover tiles of up to 8 blocks");
+static_assert(kTileBlks == 8 && kShortBlks == 2, "row-block classes above cover tiles of up to 8 and 2 blocks");
 
-template <int WAVES, int U>
-__global__ __launch_bounds__(WAVES * 64) void ffn_up_kernel(FfnArgs a, int n_groups) {
+// Wavefronts per SIMD the register budget of a kernel leaves room for, and its LDS: short tiles run
+// two workgroups of eight wavefronts per compute unit, tall ones one workgroup.
+constexpr int waves_per_simd(int TB) { return TB == kShortBlks ? 4 : 1; }
+template <int WAVES, int TB>
+constexpr int lds_bytes() {
+    constexpr int T = WAVES * 64, PASSES = (TB * kBlkStageUnits + T - 1) / T;
+    return 2 * buf_units<PASSES, T>() * 16;
+}
+static_assert(lds_bytes<4, kTileBlks>() == kLdsBytes && 2 * lds_bytes<8, kShortBlks>() <= 160 * 1024, "LDS of a compute unit");
+
+template <int WAVES, int U, int TB>
+__global__ __launch_bounds__(WAVES * 64, waves_per_simd(TB)) void ffn_up_kernel(FfnArgs a, int n_groups) {
     extern __shared__ u32x4 lds[];
-    const Wg w = locate(a, n_groups, 1);
+    const Wg w = locate<TB>(a, n_groups, 1);
     if (!w.live) return;
     const int e = a.tile_expert[w.tile];
     const int nblk = a.tile_nblk[w.tile];
@@ -601,7 +633,7 @@ __global__ __launch_bounds__(WAVES * 64) void ffn_up_kernel(FfnArgs a, int n_gro
     c.k1 = c.nks;
     c.nblk = nblk;
     bind_activations(c);
-#define CALL(NB) run_tile<0, NB, WAVES, U, 1>(a, c, as_global(blob), a.f / 16, w.grp, hblk0, 0, e, 1.f)
+#define CALL(NB) run_tile<0, NB, WAVES, U, 1, TB>(a, c, as_global(blob), a.f / 16, w.grp, hblk0, 0, e, 1.f)
     NB_SWITCH(CALL)
 #undef CALL
 }
@@ -624,10 +656,10 @@ __device__ __forceinline__ int wants_remainder(const FfnArgs& a, int nblk, int h
 // is multiplied as well (two planes per stage, twice the MFMAs) when the launch asks for it
 // (h_mode 1) or when, for some token row of the tile, the energy of the remainders recorded by
 // the up kernel exceeds the expert's threshold (h_mode 0); the test is uniform over the workgroup.
-template <int WAVES, int U>
-__global__ __launch_bounds__(WAVES * 64) void ffn_down_kernel(FfnArgs a, int n_groups) {
+template <int WAVES, int U, int TB>
+__global__ __launch_bounds__(WAVES * 64, waves_per_simd(TB)) void ffn_down_kernel(FfnArgs a, int n_groups) {
     extern __shared__ u32x4 lds[];
-    const Wg w = locate(a, n_groups, a.split_k);
+    const Wg w = locate<TB>(a, n_groups, a.split_k);
     if (!w.live) return;
     const int e = a.tile_expert[w.tile];
     const int nblk = a.tile_nblk[w.tile];
@@ -650,7 +682,7 @@ __global__ __launch_bounds__(WAVES * 64) void ffn_down_kernel(FfnArgs a, int n_g
         const int nstage = (c.nks + SX - 1) / SX;
         c.k0 = (int)((long long)w.sp * nstage / a.split_k) * SX;
         c.k1 = min((int)((long long)(w.sp + 1) * nstage / a.split_k) * SX, c.nks);
-#define CALL(NB) run_tile<1, NB, WAVES, U, 2, 1>(a, c, wsec, a.d / 32, w.grp, hblk0, w.sp, e, scale)
+#define CALL(NB) run_tile<1, NB, WAVES, U, 2, TB, 1>(a, c, wsec, a.d / 32, w.grp, hblk0, w.sp, e, scale)
         NB_SWITCH(CALL)
 #undef CALL
     } else {
@@ -658,7 +690,7 @@ __global__ __launch_bounds__(WAVES * 64) void ffn_down_kernel(FfnArgs a, int n_g
         const int nstage = (c.nks + SX - 1) / SX;
         c.k0 = (int)((long long)w.sp * nstage / a.split_k) * SX;
         c.k1 = min((int)((long long)(w.sp + 1) * nstage / a.split_k) * SX, c.nks);
-#define CALL(NB) run_tile<1, NB, WAVES, U, 1, 1>(a, c, wsec, a.d / 32, w.grp, hblk0, w.sp, e, scale)
+#define CALL(NB) run_tile<1, NB, WAVES, U, 1, TB, 1>(a, c, wsec, a.d / 32, w.grp, hblk0, w.sp, e, scale)
         NB_SWITCH(CALL)
 #undef CALL
     }
@@ -765,7 +797,7 @@ __device__ __forceinline__ void run_pass_q4(const TileCtx& c, const QCtx& q, Pip
             const int kk = k + g * SX;
             pp.load(c, g % DX, kk + DX * SX);
             __builtin_amdgcn_sched_barrier(0);
-            const u32x4* L = c.lds + buf * kBufUnits + lane;
+            const u32x4* L = c.lds + buf * buf_units<PASSES, T>() + lane;
             u32x4 win[DD];
 #pragma unroll
             for (int t = 0; t < DD; ++t) win[t] = KMOE_FRAG_AT(t);
@@ -798,7 +830,7 @@ __device__ __forceinline__ void run_pass_q4(const TileCtx& c, const QCtx& q, Pip
                 const bool more = kk + SX < c.k1;
                 if (kk + DX * SX < c.k1)
                     pp.load(c, g % DX, kk + DX * SX);
-                const u32x4* L = c.lds + buf * kBufUnits + lane;
+                const u32x4* L = c.lds + buf * buf_units<PASSES, T>() + lane;
 #pragma unroll
                 for (int j = 0; j < SX; ++j) {
                     if (kk + j < c.k1) {
@@ -847,10 +879,10 @@ __device__ __forceinline__ void run_tile_q4(const FfnArgs& a, TileCtx c, const u
 }
 
 // Blob of a 4-bit expert: [up codes d*f | up (s,z) d*f/8 | down codes d*f/2 | down (s,z) d*f/16] bytes.
-template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void ffn_up_q4_kernel(FfnArgs a, int n_groups) {
+template <int WAVES, int TB>
+__global__ __launch_bounds__(WAVES * 64, waves_per_simd(TB)) void ffn_up_q4_kernel(FfnArgs a, int n_groups) {
     extern __shared__ u32x4 lds[];
-    const Wg w = locate(a, n_groups, 1);
+    const Wg w = locate<TB>(a, n_groups, 1);
     if (!w.live) return;
     const int e = a.tile_expert[w.tile];
     const int nblk = a.tile_nblk[w.tile];
@@ -873,11 +905,11 @@ __global__ __launch_bounds__(WAVES * 64) void ffn_up_q4_kernel(FfnArgs a, int n_
 #undef CALL
 }
 
-template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void ffn_down_q4_kernel(FfnArgs a, int n_groups) {
+template <int WAVES, int TB>
+__global__ __launch_bounds__(WAVES * 64, waves_per_simd(TB)) void ffn_down_q4_kernel(FfnArgs a, int n_groups) {
     static_assert(WAVES * 64 >= kTileBlks * kRowBlk, "one thread per token row of the tile");
     extern __shared__ u32x4 lds[];
-    const Wg w = locate(a, n_groups, a.split_k);
+    const Wg w = locate<TB>(a, n_groups, a.split_k);
     if (!w.live) return;
     const int e = a.tile_expert[w.tile];
     const int nblk = a.tile_nblk[w.tile];
@@ -915,50 +947,68 @@ __global__ __launch_bounds__(WAVES * 64) void ffn_down_q4_kernel(FfnArgs a, int 
     }
 }
 
-template <int WAVES, int U>
+template <int WAVES, int U, int TB>
 void launch_up(hipStream_t st, const FfnArgs& a) {
     const int n_groups = (a.f / 16 + WAVES * U - 1) / (WAVES * U);
     const int grid = (a.max_tiles * n_groups + kXcd - 1) / kXcd * kXcd;
-    hipLaunchKernelGGL((ffn_up_kernel<WAVES, U>), dim3(grid), dim3(WAVES * 64), kLdsBytes, st, a,
+    hipLaunchKernelGGL((ffn_up_kernel<WAVES, U, TB>), dim3(grid), dim3(WAVES * 64), (lds_bytes<WAVES, TB>()), st, a,
                        n_groups);
 }
 
-template <int WAVES, int U>
+template <int WAVES, int U, int TB>
 void launch_down(hipStream_t st, const FfnArgs& a) {
     const int n_groups = (a.d / 32 + WAVES * U - 1) / (WAVES * U);
     const int grid = (a.max_tiles * n_groups * a.split_k + kXcd - 1) / kXcd * kXcd;
-    hipLaunchKernelGGL((ffn_down_kernel<WAVES, U>), dim3(grid), dim3(WAVES * 64), kLdsBytes, st, a,
+    hipLaunchKernelGGL((ffn_down_kernel<WAVES, U, TB>), dim3(grid), dim3(WAVES * 64), (lds_bytes<WAVES, TB>()), st, a,
                        n_groups);
 }
 
+template <int WAVES, int TB>
+void launch_up_q4(hipStream_t st, const FfnArgs& a) {
+    const int n_groups = (a.f / 16 + WAVES - 1) / WAVES;
+    const int grid = (a.max_tiles * n_groups + kXcd - 1) / kXcd * kXcd;
+    hipLaunchKernelGGL((ffn_up_q4_kernel<WAVES, TB>), dim3(grid), dim3(WAVES * 64), (lds_bytes<WAVES, TB>()), st, a, n_groups);
+}
+
+template <int WAVES, int TB>
+void launch_down_q4(hipStream_t st, const FfnArgs& a) {
+    const int n_groups = (a.d / 32 + WAVES - 1) / WAVES;
+    const int grid = (a.max_tiles * n_groups * a.split_k + kXcd - 1) / kXcd * kXcd;
+    hipLaunchKernelGGL((ffn_down_q4_kernel<WAVES, TB>), dim3(grid), dim3(WAVES * 64), (lds_bytes<WAVES, TB>()), st, a, n_groups);
+}
+
 template <typename K>
-hipError_t allow_lds(K kernel) {
+hipError_t allow_lds(K kernel, int bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 }  // namespace
 
 int ffn_configure() {
-    hipError_t e = allow_lds(&ffn_up_kernel<8, 1>);
-    if (e == hipSuccess) e = allow_lds(&ffn_up_q4_kernel<8>);
-    if (e == hipSuccess) e = allow_lds(&ffn_down_q4_kernel<8>);
-    if (e == hipSuccess) e = allow_lds(&ffn_up_kernel<7, 1>);
-    if (e == hipSuccess) e = allow_lds(&ffn_up_kernel<4, 2>);
-    if (e == hipSuccess) e = allow_lds(&ffn_down_kernel<8, 1>);
-    if (e == hipSuccess) e = allow_lds(&ffn_down_kernel<4, 2>);
-    return (int)e;
+    hipError_t e = hipSuccess;
+#define KMOE_ALLOW(...) \
+    if (e == hipSuccess) e = allow_lds(&__VA_ARGS__, kLdsBytes)
+    KMOE_ALLOW(ffn_up_kernel<8, 1, kTileBlks>);
+    KMOE_ALLOW(ffn_up_kernel<7, 1, kTileBlks>);
+    KMOE_ALLOW(ffn_up_kernel<4, 2, kTileBlks>);
+    KMOE_ALLOW(ffn_down_kernel<8, 1, kTileBlks>);
+    KMOE_ALLOW(ffn_down_kernel<4, 2, kTileBlks>);
+    KMOE_ALLOW(ffn_up_q4_kernel<8, kTileBlks>);
+    KMOE_ALLOW(ffn_down_q4_kernel<8, kTileBlks>);
+#undef KMOE_ALLOW
+    return (int)e;  // the short-tile kernels stay below the default limit of 64 KiB
 }
+static_assert(lds_bytes<8, kShortBlks>() <= 65536 && lds_bytes<7, kShortBlks>() <= 65536, "default LDS limit");
 
 // Launch shapes.  variant 1 / 2: eight / seven wavefronts per workgroup, one output unit each;
 // variant 3: four wavefronts with two units each (every activation fragment read from LDS feeds
 // two MFMAs).  Default: tiles expected to be full (many rows per expert, MFMA-bound) take the
-// two-unit shape, small tiles (weight streaming dominates) eight single-unit wavefronts.
+// two-unit shape, small tiles (weight streaming dominates) eight single-unit wavefronts, short tiles
+// the kernels with two workgroups per compute unit.
 void launch_ffn_up_bf16(hipStream_t st, const FfnArgs& a) {
     if (a.weight_bits == 4) {
-        const int n_groups = (a.f / 16 + 7) / 8;
-        const int grid = (a.max_tiles * n_groups + kXcd - 1) / kXcd * kXcd;
-        hipLaunchKernelGGL((ffn_up_q4_kernel<8>), dim3(grid), dim3(512), kLdsBytes, st, a, n_groups);
+        if (a.short_tiles) launch_up_q4<8, kShortBlks>(st, a); else launch_up_q4<8, kTileBlks>(st, a);
         return;
     }
     const int units = a.f / 16;
@@ -967,34 +1017,35 @@ void launch_ffn_up_bf16(hipStream_t st, const FfnArgs& a) {
         v = a.full_tiles ? 3 : 1;
         if (!a.full_tiles) {
             // small tiles: the chip works through the workgroups in rounds of one per compute unit
-            // (LDS); seven wavefronts per workgroup instead of eight when that fills the last
-            // round better (rounds x units per workgroup is what the launch costs)
-            const long tiles = a.est_tiles > 0 ? a.est_tiles : 1;
-            auto cost = [&](int w) { return ((tiles * ((units + w - 1) / w) + 255) / 256) * w; };
+            // (LDS; two with short tiles); seven wavefronts per workgroup instead of eight when that
+            // fills the last round better (rounds x units per workgroup is what the launch costs)
+            const long tiles = a.est_tiles > 0 ? a.est_tiles : 1, slots = a.short_tiles ? 512 : 256;
+            auto cost = [&](int w) { return ((tiles * ((units + w - 1) / w) + slots - 1) / slots) * w; };
             if (cost(7) < cost(8)) v = 2;
         }
     }
     if (v == 3 && units >= 2)
-        launch_up<4, 2>(st, a);
+        launch_up<4, 2, kTileBlks>(st, a);
     else if (v == 2)
-        launch_up<7, 1>(st, a);
+        a.short_tiles ? launch_up<7, 1, kShortBlks>(st, a) : launch_up<7, 1, kTileBlks>(st, a);
     else
-        launch_up<8, 1>(st, a);
+        a.short_tiles ? launch_up<8, 1, kShortBlks>(st, a) : launch_up<8, 1, kTileBlks>(st, a);
 }
 
 void launch_ffn_down_bf16(hipStream_t st, const FfnArgs& a) {
     if (a.weight_bits == 4) {  // 4-bit experts: weights dequantised in registers, same H format
-        const int n_groups = (a.d / 32 + 7) / 8;
-        const int grid = (a.max_tiles * n_groups * a.split_k + kXcd - 1) / kXcd * kXcd;
-        hipLaunchKernelGGL((ffn_down_q4_kernel<8>), dim3(grid), dim3(512), kLdsBytes, st, a, n_groups);
+        if (a.short_tiles) launch_down_q4<8, kShortBlks>(st, a); else launch_down_q4<8, kTileBlks>(st, a);
         return;
     }
     // Two units per wavefront halve the LDS reads per MFMA: faster on full tiles (prefill layer)
     // and whenever the remainder plane is multiplied too (twice the MFMAs per weight byte); with
     // one plane on small tiles (decode layer) eight single-unit wavefronts are 2-3 % faster.
     const int units = a.d / 32;
-    const bool two = (a.variant == 3 || (a.variant == 0 && (a.full_tiles || a.h_mode == 1))) && units >= 2;
-    if (two) launch_down<4, 2>(st, a); else launch_down<8, 1>(st, a);
+    const bool two = (a.variant == 3 || (a.variant == 0 && !a.short_tiles && (a.full_tiles || a.h_mode == 1))) && units >= 2;
+    if (two)
+        launch_down<4, 2, kTileBlks>(st, a);
+    else
+        a.short_tiles ? launch_down<8, 1, kShortBlks>(st, a) : launch_down<8, 1, kTileBlks>(st, a);
 }
 
 }  // namespace kmoe

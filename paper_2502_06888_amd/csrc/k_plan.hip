@@ -169,10 +169,11 @@ __device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int
     __syncthreads();
     // tiles: shared experts first (they serve every batch), then routed in execution order
     const int routed_blks = ptotal / kRowBlk, nblk_tok = (s.N + kRowBlk - 1) / kRowBlk;
-    const int per_shared = (nblk_tok + kTileBlks - 1) / kTileBlks, shared_tiles = s.S * per_shared;
+    const int lg = s.tile_lg, last = (1 << lg) - 1;  // a tile is up to 2^lg row blocks
+    const int per_shared = (nblk_tok + last) >> lg, shared_tiles = s.S * per_shared;
     const int mine = tid < E ? L.ord[tid] : -1;  // expert at place tid of the order
     const int nb = mine >= 0 ? (L.cnt[mine] + kRowBlk - 1) / kRowBlk : 0;
-    int t0 = (nb + kTileBlks - 1) / kTileBlks, place = mine >= 0 ? 1 : 0, routed_tiles, nact;
+    int t0 = (nb + last) >> lg, place = mine >= 0 ? 1 : 0, routed_tiles, nact;
     scan2(t0, place, routed_tiles, nact, L.wsum);
     t0 += shared_tiles;
     const int nt = min(shared_tiles + routed_tiles, max_tiles);
@@ -189,7 +190,7 @@ __device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int
         if (p.out_exec_order) p.out_exec_order[tid] = mine;
         if (mine >= 0) {
             p.exp_tile0[mine] = t0;
-            p.exp_ntiles[mine] = max(0, min((nb + kTileBlks - 1) / kTileBlks, max_tiles - t0));
+            p.exp_ntiles[mine] = max(0, min((nb + last) >> lg, max_tiles - t0));
         }
         if (c == 0) {
             p.exp_tile0[tid] = 0;
@@ -221,20 +222,20 @@ __device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int
         const int e = L.ord[owner];
         if (e >= 0) {
             const int x0 = L.pof[e] / kRowBlk, n = (L.cnt[e] + kRowBlk - 1) / kRowBlk, first = (int)L.key[owner];
-            for (int i = part; i * kTileBlks < n && first + i < max_tiles; i += 1 << lt) {
+            for (int i = part; i << lg < n && first + i < max_tiles; i += 1 << lt) {
                 p.tile_expert[first + i] = e;
-                p.tile_xblk[first + i] = x0 + i * kTileBlks;
-                p.tile_hblk[first + i] = x0 + i * kTileBlks;
-                p.tile_nblk[first + i] = min(kTileBlks, n - i * kTileBlks);
+                p.tile_xblk[first + i] = x0 + (i << lg);
+                p.tile_hblk[first + i] = x0 + (i << lg);
+                p.tile_nblk[first + i] = min(1 << lg, n - (i << lg));
             }
         }
     }
     for (int i = tid; i < shared_tiles && i < max_tiles; i += T) {
-        const int sh = i / per_shared, b = (i - sh * per_shared) * kTileBlks;
+        const int sh = i / per_shared, b = (i - sh * per_shared) << lg;
         p.tile_expert[i] = E + sh;
         p.tile_xblk[i] = routed_blks + b;
         p.tile_hblk[i] = routed_blks + sh * nblk_tok + b;
-        p.tile_nblk[i] = min(kTileBlks, nblk_tok - b);
+        p.tile_nblk[i] = min(1 << lg, nblk_tok - b);
     }
 }
 

@@ -7,15 +7,34 @@ namespace kmoe {
 
 constexpr int kLanes = 64;
 constexpr int kRowBlk = 32;        // rows (tokens) per MFMA block
-constexpr int kTileBlks = 8;       // row blocks per tile (256 rows)
+constexpr int kTileLg = 3, kTileBlks = 1 << kTileLg;     // row blocks per tile (256 rows), at most
+constexpr int kShortLg = 1, kShortBlks = 1 << kShortLg;  // the same for small batch groups (see short_tiles)
 constexpr int kPlanChunk = 1024;   // assignments per block of the dispatch kernels
 constexpr int kMaxExperts = 256;
 constexpr int kMaxTopK = 8;
 constexpr int kMaxBatches = 64;
 
-// Capacity of the tile tables for a context.
+// Tiles of two row blocks instead of eight: such a tile's accumulators and activation stages leave
+// room for two workgroups per compute unit, so that one streams weights while the other starts or
+// stores, and the last round of workgroups costs half as much.  For groups in which an expert rarely
+// has more than 64 rows (48 on average; a busier expert is several tiles that share its weights
+// through L2).  Shared experts have a row per token: beyond 512 they would be streamed too often.  With
+// few experts the tall tiles' deeper weight rings already stream at 6.4 TB/s.
+// (8 experts of 4096 x 14336, 4 tokens: tall 355 us a layer, short 366-379; 64 + 2 experts of
+// 2048 x 1408, 512 tokens: tall 370, short 330.)
+inline bool short_tiles(int64_t n_tokens, int k, int E, int S) {
+    return E >= 16 && n_tokens * k <= 48ll * E && (S == 0 || n_tokens <= 512);
+}
+
+// Capacity of the tile tables for a context (either tile height).
 inline int max_tiles_for(int max_rowblks, int E, int S, int max_tokens) {
-    return max_rowblks / kTileBlks + E + S * ((max_tokens + kTileBlks * kRowBlk - 1) / (kTileBlks * kRowBlk) + 1) + 1;
+    auto tiles = [&](int rowblks, int tokens, int blks) {
+        return rowblks / blks + E + S * ((tokens + blks * kRowBlk - 1) / (blks * kRowBlk) + 1) + 1;
+    };
+    const int short_rowblks = 48 * E / kRowBlk + 1 + E;
+    const int tall = tiles(max_rowblks, max_tokens, kTileBlks);
+    const int low = tiles(max_rowblks < short_rowblks ? max_rowblks : short_rowblks, max_tokens < 512 ? max_tokens : 512, kShortBlks);
+    return tall > low ? tall : low;
 }
 
 struct BatchOffsets {
@@ -41,7 +60,7 @@ struct PlanPtrs {
     int32_t* tile_expert; // [max_tiles]   expert id (E+s for shared)
     int32_t* tile_xblk;   // [max_tiles]   first row block in the packed activations
     int32_t* tile_hblk;   // [max_tiles]   first row block in H / O
-    int32_t* tile_nblk;   // [max_tiles]   row blocks in this tile (1..8)
+    int32_t* tile_nblk;   // [max_tiles]   row blocks in this tile (1..8, 1..2 for short tiles)
     int32_t* exp_tile0;   // [E+S] first tile of an expert
     int32_t* exp_ntiles;  // [E+S]
     int32_t* blk_expert;  // [max_rowblks] routed expert owning a row block
@@ -64,6 +83,7 @@ struct Shape {
     int32_t N, d, f, E, k, S;
     int32_t renorm;
     int32_t max_rowblks;   // capacity of the routed padded-row space, in row blocks
+    int32_t tile_lg;       // log2 of the row blocks per tile (kTileBlks or kShortBlks)
 };
 
 // ---- router -------------------------------------------------------------------------------
@@ -111,6 +131,8 @@ struct FfnArgs {
     const int32_t* tile_xblk;
     const int32_t* tile_hblk;
     const int32_t* tile_nblk;
+    const int32_t* exp_tile0;    // first tile and tiles of an expert (short tiles only)
+    const int32_t* exp_ntiles;
     const int32_t* tile_first;   // device: index of the first tile of this launch (null = tile_first_v)
     const int32_t* tile_count;   // device: number of tiles of this launch (null = tile_count_v)
     int32_t tile_first_v, tile_count_v;  // the same by value, from the host's mirror of the tile tables
@@ -127,6 +149,7 @@ struct FfnArgs {
                                  // workgroups that multiplied the remainder plane on their own finding (h_mode 0)
     int32_t variant;             // kernel shape (waves per workgroup x units per wave); 0 = default
     int32_t panel;               // full tiles: 1 + log2 of the tiles per panel of the workgroup order (0 = default)
+    int32_t short_tiles;         // the plan's tiles have at most kShortBlks row blocks
     int32_t full_tiles;          // host estimate: most tiles are full (more than 160 rows per expert)
     int32_t weight_bits;         // 0/16: bf16 weights; 4: 4-bit codes in groups of 64 with (s, z)
     int32_t split_k;             // down projection only

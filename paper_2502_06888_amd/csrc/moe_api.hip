@@ -25,7 +25,6 @@
 using namespace kmoe;
 
 namespace {
-constexpr int kTileRows = kRowBlk * kTileBlks;
 // experts smaller than this (bytes) are copied over two alternating streams (four were measured slower)
 constexpr int64_t kSecondCopyStreamBelow = 64ll << 20;
 // consecutive small experts share a pair of launches while their blobs stay below this
@@ -298,6 +297,8 @@ Shape make_shape(const moe_ctx* c, int n_tokens) {
     s.S = c->cfg.n_shared;
     s.renorm = c->cfg.renormalize;
     s.max_rowblks = (int32_t)c->L.max_rowblks;
+    const bool low = c->cfg.dtype == MOE_BF16 && short_tiles(n_tokens, s.k, s.E, s.S);
+    s.tile_lg = low ? kShortLg : kTileLg;
     return s;
 }
 
@@ -307,38 +308,51 @@ bool all_resident_layer(const moe_ctx* c, int layer) {
     return true;
 }
 
+// Tiles a group of A assignments is expected to have: one per expert, more where the rows ask for it.
+int64_t expected_tiles(const Shape& s) {
+    const int64_t A = (int64_t)s.N * s.k, rows = (int64_t)kRowBlk << s.tile_lg;
+    return std::max<int64_t>(std::min<int64_t>(s.E, A), (A + rows - 1) / rows) + (int64_t)s.S * ((s.N + rows - 1) / rows);
+}
+
+// Tiles it has at most.
+int most_tiles(const moe_ctx* c, const Shape& s) {
+    const int64_t A = (int64_t)s.N * s.k, rows = (int64_t)kRowBlk << s.tile_lg;
+    return (int)std::min<int64_t>(c->L.max_tiles, ((A / kRowBlk + s.E) >> s.tile_lg) + std::min<int64_t>(s.E, A) +
+                                                      (int64_t)s.S * ((s.N + rows - 1) / rows) + 1);
+}
+
 int auto_split_k(const moe_ctx* c, int n_tokens) {
     if (c->cfg.dtype != MOE_BF16) return 1;
     int cap = c->L.split_cap;
     const int nstage = c->cfg.d_ff / 64;
     cap = std::min(cap, nstage);
     if (c->split_k_user > 0) return std::min(c->split_k_user, cap);
-    const int64_t A = (int64_t)n_tokens * c->cfg.top_k;
-    const int64_t tiles = std::max<int64_t>(std::min<int64_t>(c->cfg.n_experts, A), (A + kTileRows - 1) / kTileRows) +
-                          (int64_t)c->cfg.n_shared * ((n_tokens + kTileRows - 1) / kTileRows);
+    const Shape s = make_shape(c, n_tokens);
+    const int64_t tiles = expected_tiles(s), per_cu = s.tile_lg == kShortLg ? 2 : 1;
     const int64_t groups = (c->cfg.d_model / 32 + 7) / 8;
     const int64_t wgs = std::max<int64_t>(1, tiles * groups);
-    int64_t want = (256 + wgs - 1) / wgs;  // one workgroup per compute unit; partial sums cost the combine
+    int64_t want = (256 * per_cu + wgs - 1) / wgs;  // as many workgroups as run at a time; partial sums cost the combine
     return (int)std::max<int64_t>(1, std::min<int64_t>(want, cap));
 }
 
 // Host mirror of the device tile enumeration (plan_scan_kernel): shared experts first, then the
-// routed experts in execution order, 16 row blocks per tile.
+// routed experts in execution order, up to 2^tile_lg row blocks per tile.
 void build_host_tiles(moe_ctx* c) {
     const int E = c->cfg.n_experts, S = c->cfg.n_shared;
     c->h_tiles.assign(E + S, HostTile{});
     int nt = 0;
     const int nblk_tok = (c->routed_tokens + kRowBlk - 1) / kRowBlk;
+    const int lg = make_shape(c, c->routed_tokens).tile_lg, last = (1 << lg) - 1;
     for (int sh = 0; sh < S; ++sh) {
         c->h_tiles[E + sh].first = nt;
-        nt += (nblk_tok + kTileBlks - 1) / kTileBlks;
+        nt += (nblk_tok + last) >> lg;
         c->h_tiles[E + sh].count = nt - c->h_tiles[E + sh].first;
     }
     for (int i = 0; i < c->h_nactive; ++i) {
         const int e = c->h_order[i];
         const int nb = (c->h_counts[e] + kRowBlk - 1) / kRowBlk;
         c->h_tiles[e].first = nt;
-        nt += (nb + kTileBlks - 1) / kTileBlks;
+        nt += (nb + last) >> lg;
         c->h_tiles[e].count = nt - c->h_tiles[e].first;
     }
 }
@@ -949,11 +963,14 @@ moe_status moe_layer_forward(moe_ctx* ctx, int32_t layer, const void* x_dev, voi
     a.tile_xblk = p.tile_xblk;
     a.tile_hblk = p.tile_hblk;
     a.tile_nblk = p.tile_nblk;
+    a.exp_tile0 = p.exp_tile0;
+    a.exp_ntiles = p.exp_ntiles;
     a.d = s.d;
     a.f = s.f;
     a.o_split_stride = ctx->L.o_split_stride;
     a.variant = ctx->variant % 10;
     a.panel = ctx->variant / 10;
+    a.short_tiles = s.tile_lg == kShortLg;
     a.full_tiles = ((int64_t)N * s.k / std::max(1, E) > 160) ? 1 : 0;
     a.h_mode = ctx->h_mode;
     a.h_plane_units = ctx->L.h_plane_units;
@@ -970,16 +987,12 @@ moe_status moe_layer_forward(moe_ctx* ctx, int32_t layer, const void* x_dev, voi
     if (prof) (void)hipEventRecord(ctx->pev[4], st);
 
     if (all_resident) {
-        const int64_t A = (int64_t)N * s.k;
-        a.max_tiles = (int)std::min<int64_t>(ctx->L.max_tiles,
-                                             (A / kRowBlk + E) / kTileBlks + std::min<int64_t>(E, A) +
-                                                 (int64_t)S * ((N + kTileRows - 1) / kTileRows) + 1);
+        a.max_tiles = most_tiles(ctx, s);
         if (bf16) {
             a.w_single = nullptr;
             a.tile_first = nullptr;
             a.tile_count = p.meta + 1;
-            a.est_tiles = (int)(std::max<int64_t>(std::min<int64_t>(E, A), (A + kTileRows - 1) / kTileRows) +
-                                (int64_t)S * ((N + kTileRows - 1) / kTileRows));
+            a.est_tiles = (int)expected_tiles(s);
             a.act = w + ctx->L.xp;
             a.out = w + ctx->L.h;
             a.split_k = 1;
@@ -1318,11 +1331,14 @@ moe_status moe_measure(moe_ctx* ctx, int32_t layer, const void* x_dev,
         a.tile_xblk = p.tile_xblk;
         a.tile_hblk = p.tile_hblk;
         a.tile_nblk = p.tile_nblk;
+        a.exp_tile0 = p.exp_tile0;
+        a.exp_ntiles = p.exp_ntiles;
         a.d = s.d;
         a.f = s.f;
         a.o_split_stride = ctx->L.o_split_stride;
         a.variant = ctx->variant % 10;
         a.panel = ctx->variant / 10;
+        a.short_tiles = s.tile_lg == kShortLg;
         a.full_tiles = ((int64_t)N * s.k / std::max(1, E) > 160) ? 1 : 0;
         a.h_mode = ctx->h_mode;
         a.h_plane_units = ctx->L.h_plane_units;
@@ -1574,6 +1590,7 @@ moe_status moe_route_static(void* stream, int32_t dtype, const void* x_dev, cons
     s.k = top_k;
     s.S = 0;
     s.renorm = renormalize ? 1 : 0;
+    s.tile_lg = kTileLg;
     s.max_rowblks = (int32_t)max_rowblks;
     hipStream_t st = (hipStream_t)stream;
     launch_router(st, dtype, x_dev, wg_dev, s, RouterOut{logits_dev, p.topk_idx, p.topk_w, nullptr, nullptr});

@@ -541,3 +541,15 @@ def test_plan_at_the_edges_of_its_kernels(E, k, batches):
     assert counts == list(want.disp.counts) and order == list(want.disp.exec_order)
     assert n_active == int((want.disp.counts > 0).sum())
     ctx.close()
+
+
+@pytest.mark.parametrize("E,k,S,batches", [
+    (16, 8, 1, (33,)),    # 16 or 17 rows on average, 33 of the shared expert: a second block with one row
+    (16, 1, 2, (700, 68)),     # 48 rows on average, but more than 512 with shared experts: tall tiles
+    (16, 1, 0, (700, 68)),      # the most assignments of 16 experts that take short tiles
+    (16, 1, 0, (769,)),         # one more: tall tiles
+    (15, 2, 1, (120,)),         # too few experts: tall tiles
+    (40, 8, 1, (240,)),         # 48 rows on average, some experts beyond 64: two short tiles
+    (24, 2, 1, (512,)), (24, 2, 1, (513,))])   # with shared experts short tiles end at 512 tokens
+def test_short_tiles_of_two_row_blocks(E, k, S, batches):
+    run_case(I.Workload(f"short{E}x{k}", "bf16", 128, 192, E, k, n_shared=S, batch_tokens=batches, seed=31, w_std=0.1))
