@@ -32,6 +32,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // one 16-byte unit as a first-class value
 typedef const __attribute__((address_space(1))) u32x4* gptr;  // global (HBM) address space
@@ -722,19 +724,24 @@ __device__ __forceinline__ bf16x8 dequant8(uint32_t codes, uint32_t sz) {
     const float s = __uint_as_float(sz << 16);
     const float z = __uint_as_float(sz & 0xffff0000u);
     const float zs = -z * s;
+    // the codes of even and of odd columns, one byte each: a byte converts to float in one instruction
+    // (the empty statements keep the compiler from going back to a shift and a mask per code)
+    uint32_t even = codes & 0x0f0f0f0fu, odd = (codes >> 4) & 0x0f0f0f0fu;
+    asm("" : "+v"(even));
+    asm("" : "+v"(odd));
     float v[8];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) v[p] = __builtin_fmaf((float)((codes >> (4 * p)) & 15u), s, zs);
-    bf16x8 r;
+    for (int p = 0; p < 8; ++p)
+        v[p] = __builtin_fmaf((float)(((p & 1 ? odd : even) >> (8 * (p / 2))) & 0xffu), s, zs);
+    uint32_t r[4];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) r[p] = (__bf16)v[p];
-    if (HT == 1) {
-        f16x8 h;
+    for (int p = 0; p < 4; ++p)  // two at once, round to nearest even
+        r[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v[2 * p], v[2 * p + 1]}), bf16x2));
+    if (HT == 1)
 #pragma unroll
-        for (int p = 0; p < 8; ++p) h[p] = (_Float16)(float)r[p];
-        return __builtin_bit_cast(bf16x8, h);
-    }
-    return r;
+        for (int p = 0; p < 4; ++p)
+            r[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{__uint_as_float(r[p] << 16), __uint_as_float(r[p] & 0xffff0000u)}), f16x2));
+    return __builtin_bit_cast(bf16x8, u32x4{r[0], r[1], r[2], r[3]});
 }
 
 template <int NB, int WAVES, int SX>
@@ -774,13 +781,83 @@ __device__ __forceinline__ void open_pass_q4(const TileCtx& c, const QCtx& q, Pi
     }
 }
 
+// MFMAs of a whole stage, as stage_mfma, with the dequantisation of the next step's fragment (the
+// first step of the next stage after the last one) between the MFMAs of the current step: wf holds the
+// stage's first fragment on entry and the next stage's on return.  A vector instruction takes four
+// cycles, an MFMA 32: with NS MFMAs per step the 24 (up) or 36 (down) instructions of a fragment hide
+// behind them from NS = 4 or 5 on; in one block ahead of the step they added up with the MFMAs.
+// The quad of a step is reloaded once its last fragment has been taken, one step before its MFMAs.
+template <int MODE, int NB, int SX, int PL, int D, int HT, int PASSES, int T, int DX, int QS, int RS, int RQ>
+__device__ __forceinline__ void stage_mfma_q4(const u32x4* L, u32x4 (&wq)[RQ], uint32_t (&sz)[RQ], int g, const QCtx& q,
+                                              bf16x8& wf, f32x16 (&acc)[1][NB], u32x4* next_buf,
+                                              const u32x4 (&xs)[PASSES], const TileCtx& c,
+                                              const XMap<PASSES, T, SX, PL>& xm, int kk, u32x4 (&xl)[PASSES]) {
+    constexpr int NS = NB * PL, NF = NS * SX, DD = D < NF ? D : NF;
+    constexpr int L1 = DX == 1 ? (NF / 4 > PASSES ? NF / 4 : PASSES) : NF;
+    constexpr int S0 = DX == 1 ? NF / 2 : 0;
+    constexpr int kValu = ((HT == 1 ? 36 : 24) + NS - 1) / NS;  // vector instructions between two MFMAs
+    static_assert(PASSES <= NF, "one pass per fragment at most");
+    u32x4 win[DD];
+#define KMOE_FRAG_AT(t) L[(((t) % NS) * SX + (t) / NS) * 64]
+#define KMOE_LOAD_AT(p) (((p) * L1) / PASSES)
+#define KMOE_STORE_AT(p) (S0 + ((p) * (NF - S0)) / PASSES)
+#pragma unroll
+    for (int t = 0; t < DD; ++t) win[t] = KMOE_FRAG_AT(t);
+    bf16x8 wn = wf;
+#pragma unroll
+    for (int t = 0; t < NF; ++t) {
+        const int j = t / NS, b = (t % NS) / PL;
+        acc[0][b] = mfma<MODE, HT>(wf, as_bf16x8(win[t % DD]), acc[0][b]);
+        if (t % NS == 0) {
+            const int slot = j + 1 < SX ? (g % RS) * QS + (j + 1) / 4 : ((g + 1) % RS) * QS;
+            wn = dequant8<HT>(wq[slot][(j + 1) % 4], sz[slot]);
+        }
+        if (t + DD < NF) win[t % DD] = KMOE_FRAG_AT(t + DD);
+        {
+            const int p = t < S0 ? PASSES : ((t - S0) * PASSES + (NF - S0) - 1) / (NF - S0);
+            if (p < PASSES && KMOE_STORE_AT(p) == t) {
+                const int u = (int)threadIdx.x + p * T;
+                if (PASSES * T <= kBufUnits || u < kBufUnits) next_buf[u] = xs[p];
+            }
+        }
+        {
+            const int p = (t * PASSES + L1 - 1) / L1;
+            if (p < PASSES && KMOE_LOAD_AT(p) == t) xl[p] = xm.template load<false>(c, p, kk + DX * SX);
+        }
+        if (t % NS == NS - 1) {
+            wf = wn;
+            if (j % 4 == 2) {  // step j + 1, the quad's last, has been taken: next ring turn
+                const int slot = (g % RS) * QS + j / 4;
+                const size_t quad = (size_t)((kk + RS * SX) / 4 + j / 4);
+                wq[slot] = load_stream(q.nib + quad * 64);
+                sz[slot] = q.sz[quad * 32];
+            }
+        }
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, DD, 0);
+#pragma unroll
+    for (int t = 0; t < NF; ++t) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+        if (t + DD < NF) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        const int ps = t < S0 ? PASSES : ((t - S0) * PASSES + (NF - S0) - 1) / (NF - S0);
+        if (ps < PASSES && KMOE_STORE_AT(ps) == t) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        const int pl = (t * PASSES + L1 - 1) / L1;
+        if (pl < PASSES && KMOE_LOAD_AT(pl) == t) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        if (t % NS == NS - 1 && t / NS % 4 == 2) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+    }
+#undef KMOE_FRAG_AT
+#undef KMOE_LOAD_AT
+#undef KMOE_STORE_AT
+}
+
 template <int MODE, int NB, int WAVES, int SX, int PL, int HT>
 __device__ __forceinline__ void run_pass_q4(const TileCtx& c, const QCtx& q, PipeQ<NB, WAVES, SX>& pp,
                                             f32x16 (&acc)[1][NB]) {
     static_assert(SX * PL == kFragsPerBlk, "stage geometry");
     using P = PipeQ<NB, WAVES, SX>;
     constexpr int T = P::T, PASSES = P::PASSES, RS = P::RS, DX = P::DX, G = P::G, QS = P::QS;
-    constexpr int NS = NB * PL, NF = NS * SX, D = 3, DD = D < NF ? D : NF;
+    constexpr int NS = NB * PL, D = 3;
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -790,33 +867,17 @@ __device__ __forceinline__ void run_pass_q4(const TileCtx& c, const QCtx& q, Pip
     __syncthreads();
 
     int k = c.k0, buf = 0;
-#define KMOE_FRAG_AT(t) L[(((t) % NS) * SX + (t) / NS) * 64]
-    for (; k + (G + RS) * SX <= c.k1; k += G * SX) {
+    // steady state, branch-free: the ring reloads reach RS stages ahead, the unclamped activation loads DX
+    bf16x8 wf = dequant8<HT>(pp.wq[0][0], pp.sz[0]);
+    for (; k + (G + (RS > DX ? RS : DX)) * SX <= c.k1; k += G * SX) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int kk = k + g * SX;
-            pp.load(c, g % DX, kk + DX * SX);
             __builtin_amdgcn_sched_barrier(0);
-            const u32x4* L = c.lds + buf * buf_units<PASSES, T>() + lane;
-            u32x4 win[DD];
-#pragma unroll
-            for (int t = 0; t < DD; ++t) win[t] = KMOE_FRAG_AT(t);
-            bf16x8 wf;
-#pragma unroll
-            for (int t = 0; t < NF; ++t) {
-                const int j = t / NS, b = (t % NS) / PL;
-                const int slot = (g % RS) * QS + j / 4;
-                if (t % NS == 0) wf = dequant8<HT>(pp.wq[slot][j % 4], pp.sz[slot]);
-                acc[0][b] = mfma<MODE, HT>(wf, as_bf16x8(win[t % DD]), acc[0][b]);
-                if (t + DD < NF) win[t % DD] = KMOE_FRAG_AT(t + DD);
-                if (t % NS == NS - 1 && j % 4 == 3) {  // the quad is consumed: next ring turn
-                    const size_t quad = (size_t)((kk + RS * SX) / 4 + j / 4);
-                    pp.wq[slot] = load_stream(q.nib + quad * 64);
-                    pp.sz[slot] = q.sz[quad * 32];
-                }
-            }
+            stage_mfma_q4<MODE, NB, SX, PL, D, HT, PASSES, T, DX, QS, RS, P::RQ>(
+                c.lds + buf * buf_units<PASSES, T>() + lane, pp.wq, pp.sz, g, q, wf, acc,
+                c.lds + (buf ^ 1) * buf_units<PASSES, T>(), pp.xr[(g + 1) % DX], c, pp.xm, kk, pp.xr[g % DX]);
             __builtin_amdgcn_sched_barrier(0);
-            store_x<PASSES, T>(c, pp.xr[(g + 1) % DX], buf ^ 1);
             __syncthreads();
             buf ^= 1;
         }
@@ -852,7 +913,6 @@ __device__ __forceinline__ void run_pass_q4(const TileCtx& c, const QCtx& q, Pip
             }
         }
     }
-#undef KMOE_FRAG_AT
 }
 
 template <int MODE, int NB, int WAVES, int PL>
@@ -995,6 +1055,7 @@ int ffn_configure() {
     KMOE_ALLOW(ffn_down_kernel<8, 1, kTileBlks>);
     KMOE_ALLOW(ffn_down_kernel<4, 2, kTileBlks>);
     KMOE_ALLOW(ffn_up_q4_kernel<8, kTileBlks>);
+    KMOE_ALLOW(ffn_up_q4_kernel<7, kTileBlks>);
     KMOE_ALLOW(ffn_down_q4_kernel<8, kTileBlks>);
 #undef KMOE_ALLOW
     return (int)e;  // the short-tile kernels stay below the default limit of 64 KiB
@@ -1007,23 +1068,21 @@ static_assert(lds_bytes<8, kShortBlks>() <= 65536 && lds_bytes<7, kShortBlks>() 
 // two-unit shape, small tiles (weight streaming dominates) eight single-unit wavefronts, short tiles
 // the kernels with two workgroups per compute unit.
 void launch_ffn_up_bf16(hipStream_t st, const FfnArgs& a) {
-    if (a.weight_bits == 4) {
-        if (a.short_tiles) launch_up_q4<8, kShortBlks>(st, a); else launch_up_q4<8, kTileBlks>(st, a);
+    // Tiles that are not full: the chip works through the workgroups in rounds of one per compute unit
+    // (LDS; two with short tiles); seven wavefronts per workgroup instead of eight when that fills the
+    // last round better (rounds x units per workgroup is what the launch costs)
+    const int units = a.f / 16;
+    const long tiles = a.est_tiles > 0 ? a.est_tiles : 1, slots = a.short_tiles ? 512 : 256;
+    auto cost = [&](int w) { return ((tiles * ((units + w - 1) / w) + slots - 1) / slots) * w; };
+    const int by_rounds = cost(7) < cost(8) ? 2 : 1;
+    if (a.weight_bits == 4) {  // one unit per wavefront always
+        if (by_rounds == 2)
+            a.short_tiles ? launch_up_q4<7, kShortBlks>(st, a) : launch_up_q4<7, kTileBlks>(st, a);
+        else
+            a.short_tiles ? launch_up_q4<8, kShortBlks>(st, a) : launch_up_q4<8, kTileBlks>(st, a);
         return;
     }
-    const int units = a.f / 16;
-    int v = a.variant;
-    if (v == 0) {
-        v = a.full_tiles ? 3 : 1;
-        if (!a.full_tiles) {
-            // small tiles: the chip works through the workgroups in rounds of one per compute unit
-            // (LDS; two with short tiles); seven wavefronts per workgroup instead of eight when that
-            // fills the last round better (rounds x units per workgroup is what the launch costs)
-            const long tiles = a.est_tiles > 0 ? a.est_tiles : 1, slots = a.short_tiles ? 512 : 256;
-            auto cost = [&](int w) { return ((tiles * ((units + w - 1) / w) + slots - 1) / slots) * w; };
-            if (cost(7) < cost(8)) v = 2;
-        }
-    }
+    const int v = a.variant != 0 ? a.variant : a.full_tiles ? 3 : by_rounds;
     if (v == 3 && units >= 2)
         launch_up<4, 2, kTileBlks>(st, a);
     else if (v == 2)
