@@ -600,9 +600,11 @@ __device__ __forceinline__ void run_tile(const FfnArgs& a, TileCtx c, gptr wsect
         else { CALL(2); }                     \
     }                                         \
     else if (nblk <= 2) { CALL(2); }          \
+    else if (nblk <= 3) { CALL(3); }          \
     else if (nblk <= 4) { CALL(4); }          \
     else if (nblk <= 5) { CALL(5); }          \
     else if (nblk <= 6) { CALL(6); }          \
+    else if (nblk <= 7) { CALL(7); }          \
     else { CALL(8); }
 static_assert(kTileBlks == 8 && kShortBlks == 2, "row-block classes above cover tiles of up to 8 and 2 blocks");
 
@@ -1062,6 +1064,12 @@ int ffn_configure() {
 }
 static_assert(lds_bytes<8, kShortBlks>() <= 65536 && lds_bytes<7, kShortBlks>() <= 65536, "default LDS limit");
 
+// Full tiles take the two-unit shape only for reductions at least this long: one wavefront per SIMD
+// has nothing to run while it fills its pipeline and stores its results, which two wavefronts share.
+// Reductions of 2048 and 1408 (4099 tokens over 64 + 2 experts): two units 407 + 278 us, one unit
+// 392 + 262; of 4096 and 14336 (1601 tokens over 8): two units 767 + 365, one unit 807 + 390.
+constexpr int kLongReduction = 3072;
+
 // Launch shapes.  variant 1 / 2: eight / seven wavefronts per workgroup, one output unit each;
 // variant 3: four wavefronts with two units each (every activation fragment read from LDS feeds
 // two MFMAs).  Default: tiles expected to be full (many rows per expert, MFMA-bound) take the
@@ -1082,7 +1090,7 @@ void launch_ffn_up_bf16(hipStream_t st, const FfnArgs& a) {
             a.short_tiles ? launch_up_q4<8, kShortBlks>(st, a) : launch_up_q4<8, kTileBlks>(st, a);
         return;
     }
-    const int v = a.variant != 0 ? a.variant : a.full_tiles ? 3 : by_rounds;
+    const int v = a.variant != 0 ? a.variant : !a.full_tiles ? by_rounds : a.d >= kLongReduction ? 3 : 1;
     if (v == 3 && units >= 2)
         launch_up<4, 2, kTileBlks>(st, a);
     else if (v == 2)
@@ -1100,7 +1108,7 @@ void launch_ffn_down_bf16(hipStream_t st, const FfnArgs& a) {
     // and whenever the remainder plane is multiplied too (twice the MFMAs per weight byte); with
     // one plane on small tiles (decode layer) eight single-unit wavefronts are 2-3 % faster.
     const int units = a.d / 32;
-    const bool two = (a.variant == 3 || (a.variant == 0 && !a.short_tiles && (a.full_tiles || a.h_mode == 1))) && units >= 2;
+    const bool two = (a.variant == 3 || (a.variant == 0 && !a.short_tiles && ((a.full_tiles && a.f >= kLongReduction) || a.h_mode == 1))) && units >= 2;
     if (two)
         launch_down<4, 2, kTileBlks>(st, a);
     else

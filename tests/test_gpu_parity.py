@@ -553,3 +553,10 @@ def test_plan_at_the_edges_of_its_kernels(E, k, batches):
     (24, 2, 1, (512,)), (24, 2, 1, (513,))])   # with shared experts short tiles end at 512 tokens
 def test_short_tiles_of_two_row_blocks(E, k, S, batches):
     run_case(I.Workload(f"short{E}x{k}", "bf16", 128, 192, E, k, n_shared=S, batch_tokens=batches, seed=31, w_std=0.1))
+
+
+@pytest.mark.parametrize("batches,S", [((288,), 0), ((417, 1), 1), ((257,), 2), ((545,), 0)])
+def test_experts_of_several_tiles_are_cut_evenly(batches, S):
+    """Every token goes to every expert (top-2 of 2): 9 blocks as 5 + 4, 14 as 7 + 7, 9 with one row in
+    the last, 18 as 6 + 6 + 6; routed and shared experts alike."""
+    run_case(I.Workload("even_tiles", "bf16", 128, 192, 2, 2, n_shared=S, batch_tokens=batches, seed=37, w_std=0.1))
