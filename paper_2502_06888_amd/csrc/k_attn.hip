@@ -579,7 +579,8 @@ int pick_attn_splits(const Dims& dm, const GroupTab& tab, int max_splits) {
     const int step = kAttnWaves * rpw * kChunk;
     long best = 0;
     int splits = 1;
-    for (int n = 1; n <= max_splits && (n - 1) * step < len; ++n) {
+    // more than two rounds of workgroups never pay
+    for (int n = 1; n <= max_splits && (n - 1) * step < len && (n == 1 || pairs * n <= 2 * slots); ++n) {
         const long passes = ((len + n - 1) / n + step - 1) / step;
         const long cost = (pairs * n + slots - 1) / slots * (passes + kRangeCost) + (n > 1 ? kMergeCost : 0);
         if (n == 1 || cost < best) {

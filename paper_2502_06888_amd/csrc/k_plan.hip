@@ -146,7 +146,8 @@ __device__ __forceinline__ int tile_cut(int j, int tiles, int n, int lg) {
 // Totals -> scans, execution order, tile tables, host mail.  L.cnt[] and L.nbt[] hold the tokens and
 // the batches of every expert on entry (behind a barrier).  Latency-bound (one workgroup): one
 // thread per expert, prefix sums over the threads, and the tables written by 2^lt threads per
-// expert.  (Thread 0 walking experts and tiles one by one made the scan of 64 experts take 27 us; this 7.)
+// expert.  (Thread 0 walking experts and tiles one by one made the scan of 64 experts take 27 us of a
+// 52 us plan; the whole plan of 3072 assignments to 64 experts now takes 11 us in one launch.)
 template <int T>
 __device__ __forceinline__ void scan_body(const Shape& s, const PlanPtrs& p, int max_tiles, ScanLds& L) {
     static_assert(T >= kMaxExperts && T % 64 == 0, "one thread per expert");

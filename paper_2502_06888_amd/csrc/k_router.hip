@@ -308,14 +308,54 @@ __global__ __launch_bounds__(kRouterWaves * 64) void router_kernel(
 }
 
 
-// The same arithmetic for large batch groups: one wavefront serves kMT tokens at a time, so that
-// every vector of the gate matrix it loads (and widens) feeds kMT tokens, and the loop body has no
-// branch: it serves shapes in which every lane holds a whole number of kMCB-vector groups and the
-// experts come in whole groups of kEG (anything else takes router_kernel), so all loads of a
-// group are in flight together.  Per (token, expert, lane) the order of the fused multiply-adds
-// is the one stated at the top.  Tokens past the end re-read the last row and write nothing.
+// The same arithmetic for large batch groups of exactly kEG experts: one wavefront serves kMT tokens at a
+// time, so that every vector of the gate matrix it loads (and widens) feeds kMT tokens, and the loop
+// body has no branch: it serves shapes in which every lane holds a whole number of kMCB-vector groups
+// (anything else takes router_kernel), so all loads of a group are in flight together.  Per (token,
+// expert, lane) the order of the fused multiply-adds is the one stated at the top.  Tokens past the
+// end re-read the last row and write nothing.
 constexpr int kMT = 4;   // tokens per wavefront
 constexpr int kMCB = 2;  // vectors per lane loaded together
+
+// Adds to acc[q][j] the products of the MT token rows and kEG gate rows whose lane parts start at
+// xrow[q] and wrow, cpl vectors per lane (a multiple of kMCB).
+template <typename T, int MT>
+__device__ __forceinline__ void score_group(const T* const (&xrow)[MT], const T* wrow, int d, int cpl,
+                                            float (&acc)[MT][kEG]) {
+    constexpr int V = Chunk<T>::V;
+#pragma unroll
+    for (int q = 0; q < MT; ++q)
+#pragma unroll
+        for (int j = 0; j < kEG; ++j) acc[q][j] = 0.f;
+    for (int c0 = 0; c0 < cpl; c0 += kMCB) {
+        typename Chunk<T>::Raw xr[MT][kMCB], wr[kEG][kMCB];
+#pragma unroll
+        for (int q = 0; q < MT; ++q)
+#pragma unroll
+            for (int b = 0; b < kMCB; ++b) xr[q][b] = Chunk<T>::raw(xrow[q] + (size_t)(c0 + b) * 64 * V);
+#pragma unroll
+        for (int j = 0; j < kEG; ++j)
+#pragma unroll
+            for (int b = 0; b < kMCB; ++b)
+                wr[j][b] = Chunk<T>::raw(wrow + (size_t)j * d + (size_t)(c0 + b) * 64 * V);
+#pragma unroll
+        for (int b = 0; b < kMCB; ++b) {
+            float xv[MT][V];
+#pragma unroll
+            for (int q = 0; q < MT; ++q) Chunk<T>::widen(xr[q][b], xv[q]);
+#pragma unroll
+            for (int j = 0; j < kEG; ++j) {
+                float wv[V];
+                Chunk<T>::widen(wr[j][b], wv);
+#pragma unroll
+                for (int q = 0; q < MT; ++q)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) acc[q][j] = __builtin_fmaf(xv[q][i], wv[i], acc[q][j]);
+            }
+        }
+    }
+}
+
 template <typename T>
 __global__ __launch_bounds__(kRouterWaves * 64) void router_multi_kernel(
     const T* __restrict__ X, const T* __restrict__ Wg, int N, int d, int E, int k, int renorm,
@@ -324,77 +364,30 @@ __global__ __launch_bounds__(kRouterWaves * 64) void router_multi_kernel(
     const int lane = threadIdx.x & 63;
     const int t0 = (blockIdx.x * kRouterWaves + (threadIdx.x >> 6)) * kMT;
     if (t0 >= N) return;  // whole wavefront leaves; no block-wide synchronisation below
-    const int cpl = d / (V * 64);  // vectors per lane, a multiple of kMCB
     const T* xrow[kMT];
 #pragma unroll
     for (int q = 0; q < kMT; ++q) xrow[q] = X + (size_t)min(t0 + q, N - 1) * d + (size_t)lane * V;
-
-    float mine[kMT][4];  // per token: logits of experts lane, lane+64, lane+128, lane+192
+    float acc[kMT][kEG];
+    score_group<T, kMT>(xrow, Wg + (size_t)lane * V, d, d / (V * 64), acc);
 #pragma unroll
-    for (int q = 0; q < kMT; ++q)
+    for (int q = 0; q < kMT; ++q) {
+        float tot[kEG];
+        butterfly8(acc[q], lane, tot);
+        if (t0 + q >= N) continue;
+        if (out.logits != nullptr && lane == 0)
 #pragma unroll
-        for (int s = 0; s < 4; ++s) mine[q][s] = 0.f;
-
-    for (int e0 = 0; e0 < E; e0 += kEG) {
-        float acc[kMT][kEG];
-#pragma unroll
-        for (int q = 0; q < kMT; ++q)
-#pragma unroll
-            for (int j = 0; j < kEG; ++j) acc[q][j] = 0.f;
-        const T* wrow = Wg + (size_t)e0 * d + (size_t)lane * V;
-        for (int c0 = 0; c0 < cpl; c0 += kMCB) {
-            typename Chunk<T>::Raw xr[kMT][kMCB], wr[kEG][kMCB];
-#pragma unroll
-            for (int q = 0; q < kMT; ++q)
-#pragma unroll
-                for (int b = 0; b < kMCB; ++b) xr[q][b] = Chunk<T>::raw(xrow[q] + (size_t)(c0 + b) * 64 * V);
+            for (int j = 0; j < kEG; ++j) out.logits[(size_t)(t0 + q) * E + j] = tot[j];
+        if (renorm) {
+            select_uniform_and_write(tot, E, lane, t0 + q, k, out);
+        } else {
+            float mine[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < kEG; ++j)
-#pragma unroll
-                for (int b = 0; b < kMCB; ++b)
-                    wr[j][b] = Chunk<T>::raw(wrow + (size_t)j * d + (size_t)(c0 + b) * 64 * V);
-            float xv[kMT][kMCB][V];
-#pragma unroll
-            for (int q = 0; q < kMT; ++q)
-#pragma unroll
-                for (int b = 0; b < kMCB; ++b) Chunk<T>::widen(xr[q][b], xv[q][b]);
-#pragma unroll
-            for (int j = 0; j < kEG; ++j) {
-#pragma unroll
-                for (int b = 0; b < kMCB; ++b) {
-                    float wv[V];
-                    Chunk<T>::widen(wr[j][b], wv);
-#pragma unroll
-                    for (int q = 0; q < kMT; ++q)
-#pragma unroll
-                        for (int i = 0; i < V; ++i) acc[q][j] = __builtin_fmaf(xv[q][b][i], wv[i], acc[q][j]);
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kMT; ++q) {
-            float tot[kEG];
-            butterfly8(acc[q], lane, tot);
-#pragma unroll
-            for (int j = 0; j < kEG; ++j) {
-                const int e = e0 + j;
-                if (out.logits != nullptr && lane == 0 && t0 + q < N) out.logits[(size_t)(t0 + q) * E + e] = tot[j];
-                if ((e & 63) == lane) {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        if ((e >> 6) == s) mine[q][s] = tot[j];
-                }
-            }
-            if (E <= kEG && renorm && t0 + q < N)  // one group holds every expert: select in registers
-                select_uniform_and_write(tot, E, lane, t0 + q, k, out);
+                if (lane == j) mine[0] = tot[j];
+            select_and_write(mine, lane, t0 + q, E, k, renorm, out);
         }
     }
-    if (E <= kEG && renorm) return;
-#pragma unroll
-    for (int q = 0; q < kMT; ++q)
-        if (t0 + q < N) select_and_write(mine[q], lane, t0 + q, E, k, renorm, out);
 }
-
 
 // The same arithmetic for more than kEG experts: a workgroup of kWW wavefronts serves MT tokens and its
 // wavefronts share the experts, kEG at a time, so that a gate vector is loaded once per MT tokens and
@@ -417,38 +410,7 @@ __global__ __launch_bounds__(kWW * 64) void router_wide_kernel(
     for (int q = 0; q < MT; ++q) xrow[q] = X + (size_t)min(t0 + q, N - 1) * d + (size_t)lane * V;
     for (int e0 = wave * kEG; e0 < E; e0 += kWW * kEG) {
         float acc[MT][kEG];
-#pragma unroll
-        for (int q = 0; q < MT; ++q)
-#pragma unroll
-            for (int j = 0; j < kEG; ++j) acc[q][j] = 0.f;
-        const T* wrow = Wg + (size_t)e0 * d + (size_t)lane * V;
-        for (int c0 = 0; c0 < cpl; c0 += kMCB) {
-            typename Chunk<T>::Raw xr[MT][kMCB], wr[kEG][kMCB];
-#pragma unroll
-            for (int q = 0; q < MT; ++q)
-#pragma unroll
-                for (int b = 0; b < kMCB; ++b) xr[q][b] = Chunk<T>::raw(xrow[q] + (size_t)(c0 + b) * 64 * V);
-#pragma unroll
-            for (int j = 0; j < kEG; ++j)
-#pragma unroll
-                for (int b = 0; b < kMCB; ++b)
-                    wr[j][b] = Chunk<T>::raw(wrow + (size_t)j * d + (size_t)(c0 + b) * 64 * V);
-#pragma unroll
-            for (int b = 0; b < kMCB; ++b) {
-                float xv[MT][V];
-#pragma unroll
-                for (int q = 0; q < MT; ++q) Chunk<T>::widen(xr[q][b], xv[q]);
-#pragma unroll
-                for (int j = 0; j < kEG; ++j) {
-                    float wv[V];
-                    Chunk<T>::widen(wr[j][b], wv);
-#pragma unroll
-                    for (int q = 0; q < MT; ++q)
-#pragma unroll
-                        for (int i = 0; i < V; ++i) acc[q][j] = __builtin_fmaf(xv[q][i], wv[i], acc[q][j]);
-                }
-            }
-        }
+        score_group<T, MT>(xrow, Wg + (size_t)e0 * d + (size_t)lane * V, d, cpl, acc);
 #pragma unroll
         for (int q = 0; q < MT; ++q) {
             float tot[kEG];
@@ -580,7 +542,7 @@ void launch_router(hipStream_t st, int dtype, const void* x, const void* wg, con
         return;
     }
     // large bf16 batch groups of a shape the branch-free kernel serves: kMT tokens share every gate vector
-    if (dtype != 0 && s.N >= 8192 && s.d % (8 * 64 * kMCB) == 0 && s.E % kEG == 0) {
+    if (dtype != 0 && s.N >= 8192 && s.d % (8 * 64 * kMCB) == 0 && s.E == kEG) {
         const int per_block = kRouterWaves * kMT;
         dim3 grid((s.N + per_block - 1) / per_block), block(kRouterWaves * 64);
         hipLaunchKernelGGL(router_multi_kernel<bf16raw>, grid, block, 0, st, (const bf16raw*)x,

@@ -560,3 +560,27 @@ def test_experts_of_several_tiles_are_cut_evenly(batches, S):
     """Every token goes to every expert (top-2 of 2): 9 blocks as 5 + 4, 14 as 7 + 7, 9 with one row in
     the last, 18 as 6 + 6 + 6; routed and shared experts alike."""
     run_case(I.Workload("even_tiles", "bf16", 128, 192, 2, 2, n_shared=S, batch_tokens=batches, seed=37, w_std=0.1))
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 1023, 1024, 1027])
+@pytest.mark.parametrize("E,k,renorm", [(16, 4, True), (64, 6, True), (64, 8, False), (72, 3, True)])
+def test_router_sharing_gate_rows_between_tokens(n, E, k, renorm):
+    """Token counts around the lines between one, two and four tokens per workgroup; tokens of zeros and
+    repeated gate rows make ties (lower index first), a negated row makes zeros of both signs."""
+    w = I.Workload("shared_gate", "bf16", 1024, 64, E, k, batch_tokens=(n,), seed=41, w_std=0.1)
+    data, _ = I.gen_layer(w, with_experts=False)
+    data.wg[5], data.wg[E - 1] = data.wg[2], data.wg[2]
+    data.wg[3] = -data.wg[2]
+    data.x[::7] = 0
+    ctx = H.make_ctx(w, renorm=renorm)
+    ctx.set_gate(0, data.wg.to(ctx.device))
+    x, out = data.x.to(ctx.device), H.alloc_route_outputs(w, n, ctx.device)
+    torch.cuda.synchronize()
+    ctx.route(0, x, w.batch_offsets, out)
+    torch.cuda.synchronize()
+    want = H.oracle_layer(w, data, w.batch_offsets, with_output=False, renorm=renorm)
+    got = {f: getattr(out, f).cpu().numpy() for f in ("logits", "counts", "offsets", "perm", "inv_perm", "exec_order")}
+    got["idx"] = out.topk_idx.cpu().numpy().reshape(n, k)
+    got["w"] = out.topk_w.cpu().numpy().reshape(n, k)
+    H.check_routing(got, want, E)
+    ctx.close()
