@@ -149,3 +149,24 @@ def test_seeded_sweep_of_q4_configurations(seed):
     w = I.Workload(f"q4sweep{seed}", "bf16", d, f, E, k, n_shared=int(g.integers(0, 3)), batch_tokens=tuple(sizes),
                    zipf_s=1.1 if seed % 2 else 0.0, seed=seed, w_std=float(1.1 / (d * f) ** 0.25))
     run_case(w)
+
+
+@pytest.mark.parametrize("d,f,E,k,S,batches", [
+    (64, 64, 16, 2, 0, (5,)),          # short tiles, the reduction is one quad: drain only
+    (448, 192, 20, 4, 1, (100, 0, 9)),  # 28 and 12 steps: inside and just past the ring's look-ahead
+    (1024, 1088, 16, 1, 1, (500,)),    # long enough for the steady state, both row-block classes
+    (576, 1024, 3, 2, 0, (417,)),      # tall tiles of 4 to 7 blocks
+])
+@pytest.mark.parametrize("h_planes", [1, 2])
+def test_q4_steady_state_and_drain(d, f, E, k, S, batches, h_planes):
+    w = I.Workload("q4_steps", "bf16", d, f, E, k, n_shared=S, batch_tokens=batches, seed=43, w_std=0.08)
+    data, _ = I.gen_layer(w, 0, with_experts=False)
+    experts = [I.gen_expert_q4(w, 0, e) for e in range(E + S)]
+    ctx = make_ctx_q4(w)
+    ctx.set_tuning(0, h_planes, 0)
+    place_q4(ctx, w, 0, data.wg, experts)
+    got = H.gpu_layer(ctx, w, 0, data.x, w.batch_offsets)
+    want = oracle_q4(w, data, experts)
+    H.check_routing(got, want, E)
+    H.check_output(got["y"], want.y, w.dtype)
+    ctx.close()
