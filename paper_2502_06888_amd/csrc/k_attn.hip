@@ -175,7 +175,9 @@ __global__ __launch_bounds__(256, 2) void proj_kernel(const u32x4* __restrict__ 
     }
 }
 
-// One thread per rotated pair of q or k, or per element of v, of one sequence.
+// One thread per rotated pair of kFinHeads consecutive heads of q and k (they share the angle, whose
+// reduction, sine and cosine cost more than the sums), or per element of v, of one sequence.
+constexpr int kFinHeads = 4;
 __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict__ part, int splits,
                                                          int64_t split_stride, Dims dm, GroupTab tab,
                                                          const double* __restrict__ inv_freq,
@@ -187,45 +189,59 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict
     uint16_t* vc = (uint16_t*)tab.vc[bt];
     uint16_t* new_rows = (uint16_t*)tab.new_rows[bt];
     const int dq = dm.Hq * hd, dkv = dm.Hkv * hd, n_out = dq + 2 * dkv;
-    const int n_pairs = (dm.Hq + dm.Hkv) * half;
+    const int heads = dm.Hq + dm.Hkv;  // heads 0..Hq-1 are q, then k
+    const int n_pairs = (heads + kFinHeads - 1) / kFinHeads * half;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n_pairs + dkv) return;
     const float* row = part + (size_t)row_g * n_out;
-    auto total = [&](int col) {
-        float a = 0.f;
-        for (int sp = 0; sp < splits; ++sp) a += row[(size_t)sp * split_stride + col];
-        return a;
-    };
     if (i < n_pairs) {
-        const int h = i / half, j = i % half;  // heads 0..Hq-1 are q, then k
-        const float a = total(h * hd + j), b = total(h * hd + j + half);
+        const int h0 = i / half * kFinHeads, j = i % half;
+        float a[kFinHeads], b[kFinHeads];
+#pragma unroll
+        for (int u = 0; u < kFinHeads; ++u) a[u] = b[u] = 0.f;
+        for (int sp = 0; sp < splits; ++sp) {  // partial sums in order, all heads of a split side by side
+            const float* p = row + (size_t)sp * split_stride + j;
+#pragma unroll
+            for (int u = 0; u < kFinHeads; ++u) {
+                const int h = min(h0 + u, heads - 1);  // past the last head: the last one again, unused
+                a[u] += p[h * hd];
+                b[u] += p[h * hd + half];
+            }
+        }
         // angle reduced to [-pi, pi] in double, sine and cosine of the remainder in single
         const double ang = (double)pos * inv_freq[j];
         const double turns = rint(ang * 0.15915494309189535);
         const float red = (float)(ang - turns * 6.283185307179586);
         float sf, c;
         sincosf(red, &sf, &c);
-        const float r0 = a * c - b * sf, r1 = b * c + a * sf;
-        if (h < dm.Hq) {
-            // 1/sqrt(hd) and log2(e) folded in: the attention kernel works with base-2 exponentials
-            const float qscale = 1.4426950408889634f / sqrtf((float)hd);
-            q[((size_t)row_g * dm.Hq + h) * hd + j] = r0 * qscale;
-            q[((size_t)row_g * dm.Hq + h) * hd + j + half] = r1 * qscale;
-        } else {
-            const int hk = h - dm.Hq;
-            const uint16_t b0 = (uint16_t)bf_bits(r0), b1 = (uint16_t)bf_bits(r1);
-            uint16_t* dst = kc + (((size_t)s * dm.Hkv + hk) * dm.max_len + pos) * hd;
-            dst[j] = b0;
-            dst[j + half] = b1;
-            if (new_rows != nullptr) {
-                uint16_t* nr = new_rows + ((size_t)s * dm.Hkv + hk) * hd;
-                nr[j] = b0;
-                nr[j + half] = b1;
+#pragma unroll
+        for (int u = 0; u < kFinHeads; ++u) {
+            const int h = h0 + u;
+            if (h >= heads) break;
+            const float r0 = a[u] * c - b[u] * sf, r1 = b[u] * c + a[u] * sf;
+            if (h < dm.Hq) {
+                // 1/sqrt(hd) and log2(e) folded in: the attention kernel works with base-2 exponentials
+                const float qscale = 1.4426950408889634f / sqrtf((float)hd);
+                q[((size_t)row_g * dm.Hq + h) * hd + j] = r0 * qscale;
+                q[((size_t)row_g * dm.Hq + h) * hd + j + half] = r1 * qscale;
+            } else {
+                const int hk = h - dm.Hq;
+                const uint16_t b0 = (uint16_t)bf_bits(r0), b1 = (uint16_t)bf_bits(r1);
+                uint16_t* dst = kc + (((size_t)s * dm.Hkv + hk) * dm.max_len + pos) * hd;
+                dst[j] = b0;
+                dst[j + half] = b1;
+                if (new_rows != nullptr) {
+                    uint16_t* nr = new_rows + ((size_t)s * dm.Hkv + hk) * hd;
+                    nr[j] = b0;
+                    nr[j + half] = b1;
+                }
             }
         }
     } else {
         const int e = i - n_pairs, hk = e / hd, j = e % hd;
-        const uint16_t b = (uint16_t)bf_bits(total(dq + dkv + e));
+        float v = 0.f;
+        for (int sp = 0; sp < splits; ++sp) v += row[(size_t)sp * split_stride + dq + dkv + e];
+        const uint16_t b = (uint16_t)bf_bits(v);
         vc[(((size_t)s * dm.Hkv + hk) * dm.max_len + pos) * hd + j] = b;
         if (new_rows != nullptr) new_rows[((size_t)(n_seq + s) * dm.Hkv + hk) * hd + j] = b;
     }
@@ -561,7 +577,7 @@ void launch_proj(hipStream_t st, const void* a_frag, const void* w_frag, int row
 
 void launch_qkv_finish(hipStream_t st, const float* part, int splits, int64_t split_stride,
                        const Dims& dm, const GroupTab& tab, const double* inv_freq, float* q) {
-    const int items = (dm.Hq + dm.Hkv) * (dm.hd / 2) + dm.Hkv * dm.hd;
+    const int items = (dm.Hq + dm.Hkv + kFinHeads - 1) / kFinHeads * (dm.hd / 2) + dm.Hkv * dm.hd;
     hipLaunchKernelGGL(qkv_finish_kernel, dim3((items + 255) / 256, tab.row0[tab.n]), dim3(256), 0, st, part,
                        splits, split_stride, dm, tab, inv_freq, q);
 }
