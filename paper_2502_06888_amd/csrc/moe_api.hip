@@ -275,16 +275,21 @@ bool is_pinned_host(const void* p) {
     return at.type == hipMemoryTypeHost;
 }
 
-// Memory of the current device: an output there is written by the kernels themselves; any other is
-// filled by a copy.
-bool on_this_device(const void* p) {
+// An output of moe_route that the kernels may write themselves: `bytes` inside one allocation of the
+// current device, aligned for whole words.  Any other (pinned, managed or another device's memory, odd
+// addresses, allocations that end too early) is filled by a copy, which serves it or refuses it.
+bool kernels_may_write(const void* p, size_t bytes) {
     hipPointerAttribute_t at;
     int dev = 0;
-    if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if ((uintptr_t)p % sizeof(int32_t) != 0) return false;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == dev;
+    return at.type == hipMemoryTypeDevice && at.device == dev && (uintptr_t)p + bytes <= (uintptr_t)base + size;
 }
 
 Shape make_shape(const moe_ctx* c, int n_tokens) {
@@ -836,7 +841,8 @@ moe_status moe_route(moe_ctx* ctx, int32_t layer, const void* x_dev,
     const bool prof = ctx->profiling;
     const int span = span_open(ctx, st, 1);
     if (prof) (void)hipEventRecord(ctx->pev[0], st);
-    // outputs the caller asks for: dst is written by the kernel (direct) or copied afterwards
+    // outputs the caller asks for: dst is written by the kernels (direct) or copied afterwards, in the order
+    // below.  Direct only if it shares no byte with what the kernels read or with another output.
     struct Wanted {
         void* dst;
         const void* src;
@@ -852,7 +858,16 @@ moe_status moe_route(moe_ctx* ctx, int32_t layer, const void* x_dev,
                        {perm_dev, plan.perm, A * 4, false},
                        {inv_perm_dev, plan.inv_perm, A * 4, false},
                        {exec_order_dev, plan.exec_order, (size_t)E * 4, false}};
-    for (Wanted& o : wanted) o.direct = o.dst && o.bytes > 0 && on_this_device(o.dst);
+    const size_t elt = ctx->cfg.dtype == MOE_BF16 ? 2 : 4, d = (size_t)ctx->cfg.d_model;
+    auto apart = [](const void* p, size_t n, const void* q, size_t m) {
+        return !p || !q || n == 0 || m == 0 || (uintptr_t)p + n <= (uintptr_t)q || (uintptr_t)q + m <= (uintptr_t)p;
+    };
+    for (Wanted& o : wanted) {
+        o.direct = o.dst && o.bytes > 0 && apart(o.dst, o.bytes, x_dev, (size_t)N * d * elt) &&
+                   apart(o.dst, o.bytes, ls.wg, E * d * elt) && apart(o.dst, o.bytes, logits_dev, (size_t)N * E * 4);
+        for (const Wanted& u : wanted) o.direct = o.direct && (&u == &o || apart(o.dst, o.bytes, u.dst, u.bytes));
+        o.direct = o.direct && kernels_may_write(o.dst, o.bytes);
+    }
     auto direct = [&](int i) { return wanted[i].direct ? (int32_t*)wanted[i].dst : nullptr; };
     launch_router(st, ctx->cfg.dtype, x_dev, ls.wg, s,
                   RouterOut{logits_dev, plan.topk_idx, plan.topk_w, direct(0), (float*)direct(1)});
@@ -868,7 +883,7 @@ moe_status moe_route(moe_ctx* ctx, int32_t layer, const void* x_dev,
     ctx->prof_route = prof;
     HIP_TRY(ctx, hipGetLastError());
     for (const Wanted& o : wanted)
-        if (o.dst && o.bytes > 0 && !o.direct) HIP_TRY(ctx, hipMemcpyAsync(o.dst, o.src, o.bytes, hipMemcpyDeviceToDevice, st));
+        if (o.dst && o.bytes > 0 && !o.direct) HIP_TRY(ctx, hipMemcpyAsync(o.dst, o.src, o.bytes, hipMemcpyDefault, st));
     if (ctx->corr_learn) {
         int32_t* prev = (int32_t*)(ctx->ws + ctx->L.prev_idx);
         if (layer > 0 && ctx->prev_idx_layer == layer - 1 && ctx->prev_idx_tokens == N && N > 0) {

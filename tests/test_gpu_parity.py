@@ -1,6 +1,8 @@
 """GPU parity: the HIP path, called through the C-ABI, against the CPU oracle on the same
 seeded inputs.  Integer results must match bit for bit (and so must the fp32 gate logits,
 which decide them); outputs within the stated tolerance."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -584,3 +586,104 @@ def test_router_sharing_gate_rows_between_tokens(n, E, k, renorm):
     got["w"] = out.topk_w.cpu().numpy().reshape(n, k)
     H.check_routing(got, want, E)
     ctx.close()
+
+
+ROUTE_ARRAYS = ("topk_idx", "topk_w", "counts", "offsets", "perm", "inv_perm", "exec_order")
+
+
+def routed(w, change=lambda out, x: None):
+    """moe_route of one layer with its outputs as `change` has replaced them; (want, outputs)."""
+    data, _ = I.gen_layer(w, with_experts=False)
+    ctx = H.make_ctx(w)
+    ctx.set_gate(0, data.wg.to(ctx.device))
+    x, out = data.x.to(ctx.device), H.alloc_route_outputs(w, w.n_tokens, ctx.device)
+    change(out, x)
+    torch.cuda.synchronize()
+    try:
+        ctx.route(0, x, w.batch_offsets, out)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    want = H.oracle_layer(w, data, w.batch_offsets, with_output=False)
+    return want, out
+
+
+def check_arrays(want, out, names):
+    whole = dict(topk_idx=want.idx.reshape(-1), counts=want.disp.counts, offsets=want.disp.offsets, perm=want.disp.perm,
+                 inv_perm=want.disp.inv_perm, exec_order=want.disp.exec_order)
+    for n in names:
+        got = getattr(out, n).cpu().numpy()
+        if n == "topk_w":
+            assert np.allclose(got, want.w.reshape(-1), rtol=1e-5, atol=1e-6)
+        else:
+            assert np.array_equal(got, whole[n]), n
+
+
+ROUTED = [I.Workload("route_out_wide", "bf16", 1024, 64, 16, 3, batch_tokens=(70, 31), seed=47, w_std=0.1),
+          I.Workload("route_out_chunked", "bf16", 128, 64, 5, 4, batch_tokens=(1100,), seed=47, w_std=0.1)]
+
+
+@pytest.mark.parametrize("w", ROUTED, ids=lambda w: w.name)
+@pytest.mark.parametrize("pinned", [ROUTE_ARRAYS, ROUTE_ARRAYS[::2], ROUTE_ARRAYS[1::2]], ids=["all", "even", "odd"])
+def test_route_outputs_in_pinned_memory_beside_outputs_on_the_device(w, pinned):
+    def change(out, x):
+        for n in pinned:
+            t = getattr(out, n)
+            setattr(out, n, torch.empty(t.shape, dtype=t.dtype, pin_memory=True))
+    want, out = routed(w, change)
+    check_arrays(want, out, ROUTE_ARRAYS)
+
+
+@pytest.mark.parametrize("w", ROUTED, ids=lambda w: w.name)
+def test_route_outputs_that_share_memory_or_are_not_aligned(w):
+    """Outputs over the tokens, over one another (the later one stays) and at odd addresses hold what a
+    copy after the kernels would leave there."""
+    def over_x(out, x):
+        out.topk_idx = x.view(torch.int32).reshape(-1)[:w.n_tokens * w.top_k]
+    want, out = routed(w, over_x)
+    check_arrays(want, out, ROUTE_ARRAYS)
+
+    def same(out, x):
+        out.inv_perm = out.perm
+        out.offsets = torch.cat((out.offsets, out.exec_order))[:w.n_experts + 1]
+        out.exec_order = out.offsets[1:]
+    want, out = routed(w, same)
+    check_arrays(want, out, ("topk_idx", "topk_w", "counts", "inv_perm", "exec_order"))
+    assert int(out.offsets[0]) == 0
+
+    def odd(out, x):
+        for n in ROUTE_ARRAYS:
+            t = getattr(out, n)
+            setattr(out, n, torch.zeros(4 * t.numel() + 8, dtype=torch.uint8, device=x.device)[1:4 * t.numel() + 1])
+    want, out = routed(w, odd)
+    for n in ROUTE_ARRAYS:
+        t = getattr(out, n).clone()
+        setattr(out, n, t.view(torch.float32 if n == "topk_w" else torch.int32))
+    check_arrays(want, out, ROUTE_ARRAYS)
+
+
+@pytest.mark.parametrize("name", ROUTE_ARRAYS)
+def test_route_refuses_outputs_beyond_their_allocation(name):
+    """An allocation that ends 16 bytes before the output does (and inside its last page)."""
+    w = ROUTED[0]
+    lib = B.load_library()
+    hip = [getattr(lib, f) for f in ("hipMalloc", "hipFree", "hipGetLastError")]  # of the runtime the library is linked to
+    A = w.n_tokens * w.top_k
+    need = 4 * {"counts": w.n_experts, "exec_order": w.n_experts, "offsets": w.n_experts + 1}.get(name, A)
+    assert (need - 16) % 4096 + 16 <= 4096
+    p = C.c_void_p()
+    assert hip[0](C.byref(p), C.c_size_t(need - 16)) == 0
+
+    class Short:
+        def data_ptr(self):
+            return p.value
+
+    def change(out, x):
+        setattr(out, name, Short())
+    try:
+        with pytest.raises(B.MoeError) as ei:
+            routed(w, change)
+        assert ei.value.status == B.MOE_ERR_HIP
+    finally:
+        hip[2]()                                                  # or torch's next call would report it
+        assert hip[1](p) == 0
