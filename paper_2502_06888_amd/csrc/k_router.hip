@@ -129,7 +129,7 @@ __device__ __forceinline__ void select_and_write(const float (&mine)[4], int lan
 // of every expert is counted instead of selecting k times with a wavefront arg-max (12 dependent
 // cross-lane moves through LDS per winner: at k = 6 half of the time of a 64-expert router).  Ranks
 // come from a total order on (logit, index): the logit's bits mapped to an unsigned integer that
-// grows with it, zeros of both signs alike.
+// grows with it, zeros of both signs alike.  No logit is NaN.
 __device__ __forceinline__ void rank_and_write(float v, int lane, int t, int E, int k, const RouterOut& out) {
     const uint32_t u = __float_as_uint(v + 0.f);  // -0 -> +0
     // lanes without an expert: below every key, and behind every expert on a tie
@@ -426,8 +426,11 @@ __global__ __launch_bounds__(kWW * 64) void router_wide_kernel(
     __syncthreads();
     if (wave >= MT || t0 + wave >= N) return;
     if (E <= 64 && renorm) {
-        rank_and_write(lane < E ? slog[wave][lane] : 0.f, lane, t0 + wave, E, k, out);
-        return;
+        const float v = lane < E ? slog[wave][lane] : 0.f;
+        if (__ballot(v != v) == 0ull) {  // NaN has no place in the order of ranks: selected as everywhere else
+            rank_and_write(v, lane, t0 + wave, E, k, out);
+            return;
+        }
     }
     float mine[4];
 #pragma unroll

@@ -588,6 +588,43 @@ def test_router_sharing_gate_rows_between_tokens(n, E, k, renorm):
     ctx.close()
 
 
+@pytest.mark.parametrize("E,k", [(16, 3), (64, 8)])
+def test_router_with_infinite_and_nan_logits(E, k):
+    """Tokens whose logits are infinite of both signs or NaN, all of them or some, beside sound tokens.
+    The selection with renormalised weights (by ranks, up to 64 experts) picks what the selection without
+    them picks (k times the best); ids of a token are distinct; sound tokens are those of the oracle."""
+    w = I.Workload("odd_logits", "bf16", 1024, 64, E, k, batch_tokens=(301,), seed=53, w_std=0.1)
+    data, _ = I.gen_layer(w, with_experts=False)
+    inf, nan = float("inf"), float("nan")
+    data.wg[1, 0], data.wg[1, 1:] = 1.0, 0.0          # expert 1: sum of one product, the others of many
+    x = data.x
+    x[0], x[1, 5], x[2, 0], x[3, 0] = nan, nan, inf, -inf
+    x[4] = 0
+    x[4, 0] = inf                                     # 0 * inf: NaN where the gate weight is zero
+    x[6, 0], x[6, 1] = inf, -inf
+    x[7] = 3.0e38
+    picked = []
+    for renorm in (True, False):
+        ctx = H.make_ctx(w, renorm=renorm)
+        ctx.set_gate(0, data.wg.to(ctx.device))
+        out, xd = H.alloc_route_outputs(w, w.n_tokens, ctx.device), x.to(ctx.device)
+        torch.cuda.synchronize()
+        ctx.route(0, xd, w.batch_offsets, out)
+        torch.cuda.synchronize()
+        picked.append({n: getattr(out, n).cpu().numpy() for n in ("logits", "topk_idx", "topk_w", "counts")})
+        ctx.close()
+    a, b = picked
+    assert not np.isfinite(a["logits"][:8]).all(axis=1)[[0, 1, 2, 3, 4, 6]].any()
+    assert np.array_equal(a["logits"].view(np.uint32), b["logits"].view(np.uint32))
+    assert np.array_equal(a["topk_idx"], b["topk_idx"]) and np.array_equal(a["counts"], b["counts"])
+    idx = a["topk_idx"].reshape(-1, k)
+    assert all(len(set(row)) == k and 0 <= row.min() and row.max() < E for row in idx)
+    want = H.oracle_layer(w, data, w.batch_offsets, with_output=False)
+    sound = np.isfinite(a["logits"]).all(axis=1)
+    assert np.array_equal(idx[sound], want.idx[sound])
+    assert np.allclose(a["topk_w"].reshape(-1, k)[sound], want.w[sound], rtol=1e-5, atol=1e-6)
+
+
 ROUTE_ARRAYS = ("topk_idx", "topk_w", "counts", "offsets", "perm", "inv_perm", "exec_order")
 
 
