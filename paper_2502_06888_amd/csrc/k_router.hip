@@ -389,10 +389,10 @@ __global__ __launch_bounds__(kRouterWaves * 64) void router_multi_kernel(
     }
 }
 
-// The same arithmetic for more than kEG experts: a workgroup of kWW wavefronts serves MT tokens and its
-// wavefronts share the experts, kEG at a time, so that a gate vector is loaded once per MT tokens and
-// no wavefront walks all experts (shapes as for router_multi_kernel).  The logits meet in LDS and
-// wavefront q selects for token q.  Bound by the gate's re-reads from L2 and by latency: 512 tokens,
+// The same arithmetic for more than kEG experts: a workgroup of up to kWW wavefronts serves MT tokens and
+// its wavefronts share the experts, kEG at a time, so that a gate vector is loaded once per MT tokens and
+// no wavefront walks all experts (shapes as for router_multi_kernel).  The logits meet in LDS and the
+// wavefronts select for the tokens.  Bound by the gate's re-reads from L2 and by latency: 512 tokens,
 // 64 experts, width 2048 took 24-36 us with one token per workgroup (134 MB of gate rows).
 constexpr int kWW = 8;
 template <typename T, int MT>
@@ -400,15 +400,15 @@ __global__ __launch_bounds__(kWW * 64) void router_wide_kernel(
     const T* __restrict__ X, const T* __restrict__ Wg, int N, int d, int E, int k, int renorm,
     RouterOut out) {
     constexpr int V = Chunk<T>::V;
-    static_assert(MT <= kWW, "a wavefront per token selects");
     __shared__ float slog[MT][kMaxExperts];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int waves = blockDim.x / 64;
     const int t0 = blockIdx.x * MT;
     const int cpl = d / (V * 64);  // vectors per lane, a multiple of kMCB
     const T* xrow[MT];
 #pragma unroll
     for (int q = 0; q < MT; ++q) xrow[q] = X + (size_t)min(t0 + q, N - 1) * d + (size_t)lane * V;
-    for (int e0 = wave * kEG; e0 < E; e0 += kWW * kEG) {
+    for (int e0 = wave * kEG; e0 < E; e0 += waves * kEG) {
         float acc[MT][kEG];
         score_group<T, MT>(xrow, Wg + (size_t)e0 * d + (size_t)lane * V, d, cpl, acc);
 #pragma unroll
@@ -424,18 +424,19 @@ __global__ __launch_bounds__(kWW * 64) void router_wide_kernel(
         }
     }
     __syncthreads();
-    if (wave >= MT || t0 + wave >= N) return;
-    if (E <= 64 && renorm) {
-        const float v = lane < E ? slog[wave][lane] : 0.f;
-        if (__ballot(v != v) == 0ull) {  // NaN has no place in the order of ranks: selected as everywhere else
-            rank_and_write(v, lane, t0 + wave, E, k, out);
-            return;
+    for (int q = wave; q < MT && t0 + q < N; q += waves) {
+        if (E <= 64 && renorm) {
+            const float v = lane < E ? slog[q][lane] : 0.f;
+            if (__ballot(v != v) == 0ull) {  // NaN has no place in the order of ranks: selected as everywhere else
+                rank_and_write(v, lane, t0 + q, E, k, out);
+                continue;
+            }
         }
-    }
-    float mine[4];
+        float mine[4];
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) mine[s4] = lane + 64 * s4 < E ? slog[wave][lane + 64 * s4] : 0.f;
-    select_and_write(mine, lane, t0 + wave, E, k, renorm, out);
+        for (int s4 = 0; s4 < 4; ++s4) mine[s4] = lane + 64 * s4 < E ? slog[q][lane + 64 * s4] : 0.f;
+        select_and_write(mine, lane, t0 + q, E, k, renorm, out);
+    }
 }
 
 // The same arithmetic with one workgroup per token: wavefront w scores experts w*kSG, w*kSG+1,
@@ -523,7 +524,14 @@ void launch_router(hipStream_t st, int dtype, const void* x, const void* wg, con
     // more workgroups instead (one token each below 256, two below 1024)
     if (dtype != 0 && s.d % (8 * 64 * kMCB) == 0 && s.E % kEG == 0 && s.E > kEG) {
         const int mt = s.N < 256 ? 1 : s.N < 1024 ? 2 : 4;
-        const dim3 grid((s.N + mt - 1) / mt), block(kWW * 64);
+        // Wavefronts per workgroup: no more than there are groups of experts (idle ones would only hold
+        // registers: 16 experts, width 4096, 8192 tokens 79 us with eight, 35 with two).  From 2048 tokens
+        // on the workgroups no longer run all at once, and up to four wavefronts that walk the groups in
+        // even passes use the chip better (64 experts, width 2048, eight against four: 1024 tokens 15 and
+        // 20 us, 2048 24 and 23, 8192 73 and 61).
+        const int groups = s.E / kEG, most = s.N < 2048 ? kWW : kWW / 2, passes = (groups + most - 1) / most;
+        const int waves = s.N < 2048 ? (groups < most ? groups : most) : (groups + passes - 1) / passes;
+        const dim3 grid((s.N + mt - 1) / mt), block(waves * 64);
 #define KMOE_WIDE(MT)                                                                                     \
     hipLaunchKernelGGL((router_wide_kernel<bf16raw, MT>), grid, block, 0, st, (const bf16raw*)x,            \
                        (const bf16raw*)wg, s.N, s.d, s.E, s.k, s.renorm, out)

@@ -588,6 +588,15 @@ def test_router_sharing_gate_rows_between_tokens(n, E, k, renorm):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,E,k,renorm", [
+    (2047, 16, 2, True), (2048, 16, 2, True),        # two wavefronts for four tokens
+    (2051, 24, 3, False), (2049, 40, 4, True),        # three; five groups of experts in two uneven passes
+    (2050, 56, 4, True), (2048, 72, 2, False),        # four and three; three passes of three
+    (2047, 72, 2, True), (2051, 136, 8, False)])      # eight in two passes, the second of one; five passes
+def test_router_wavefronts_share_the_experts(n, E, k, renorm):
+    test_router_sharing_gate_rows_between_tokens(n, E, k, renorm)
+
+
 @pytest.mark.parametrize("E,k", [(16, 3), (64, 8)])
 def test_router_with_infinite_and_nan_logits(E, k):
     """Tokens whose logits are infinite of both signs or NaN, all of them or some, beside sound tokens.
