@@ -353,27 +353,29 @@ __global__ __launch_bounds__(kThreads) void plan_rank_kernel(const int32_t* __re
     }
 }
 
-// All three phases in one block of 16 wavefronts, for batch groups of up to kFusedMax assignments.
+// All three phases in one block of T threads, for batch groups of up to kFusedRounds * T assignments.
 // The counts are the sums of the wavefront segments that the ranks need anyway, so nothing but the
-// batch masks goes through LDS atomics.
+// batch masks goes through LDS atomics.  Up to 512 assignments take 256 threads: starting and joining
+// twelve more wavefronts costs more than they save (gate and plan of 8 experts, 16 to 256 assignments 13.6
+// us with 1024 threads, 12.3 with 256; 512 13.7 and 13.5; 1024 14.1 and 14.7).
 constexpr int kFusedThreads = 1024, kFusedRounds = 4, kFusedMax = kFusedThreads * kFusedRounds;
-constexpr int kFusedWaves = kFusedThreads / 64;
-__global__ __launch_bounds__(kFusedThreads) void plan_fused_kernel(const int32_t* __restrict__ idx,
-                                                                   Shape s, BatchOffsets bo, PlanPtrs p,
-                                                                   int max_tiles, int rounds) {
+template <int T>
+__global__ __launch_bounds__(T) void plan_fused_kernel(const int32_t* __restrict__ idx, Shape s, BatchOffsets bo,
+                                                       PlanPtrs p, int max_tiles, int rounds) {
+    constexpr int kWaves = T / 64;
     __shared__ ScanLds L;
     __shared__ unsigned long long msk[kMaxExperts];
-    __shared__ uint16_t seg[kFusedRounds * kFusedWaves][kMaxExperts];  // tokens of expert e in (round, wave) segment
+    __shared__ uint16_t seg[kFusedRounds * kWaves][kMaxExperts];  // tokens of expert e in (round, wave) segment
     __shared__ int32_t sbo[kMaxBatches + 1];
-    const int A = s.N * s.k, E = s.E, wave = threadIdx.x >> 6, segs = rounds * kFusedWaves;
+    const int A = s.N * s.k, E = s.E, wave = threadIdx.x >> 6, segs = rounds * kWaves;
     int my_e[kFusedRounds], my_rank[kFusedRounds];
 #pragma unroll
     for (int r = 0; r < kFusedRounds; ++r) {
-        const int a = r * kFusedThreads + threadIdx.x;
+        const int a = r * T + threadIdx.x;
         my_e[r] = a < A ? idx[a] : -1;
     }
     if (threadIdx.x <= kMaxBatches) sbo[threadIdx.x] = bo.v[threadIdx.x];
-    for (int i = threadIdx.x; i < segs * E; i += kFusedThreads) seg[i / E][i % E] = 0;
+    for (int i = threadIdx.x; i < segs * E; i += T) seg[i / E][i % E] = 0;
     if (threadIdx.x < E) msk[threadIdx.x] = 0ull;
     __syncthreads();
     const int ebits = bits_for(E);
@@ -381,10 +383,10 @@ __global__ __launch_bounds__(kFusedThreads) void plan_fused_kernel(const int32_t
     for (int r = 0; r < kFusedRounds; ++r) {
         my_rank[r] = 0;
         if (r < rounds) {  // uniform
-            const int a = r * kFusedThreads + threadIdx.x, e = my_e[r];
+            const int a = r * T + threadIdx.x, e = my_e[r];
             const unsigned long long same = same_expert(e, ebits);
             my_rank[r] = __popcll(same & lanes_below());
-            if (e >= 0 && my_rank[r] == 0) seg[r * kFusedWaves + wave][e] = (uint16_t)__popcll(same);
+            if (e >= 0 && my_rank[r] == 0) seg[r * kWaves + wave][e] = (uint16_t)__popcll(same);
             add_batch(msk, e, a < A ? batch_of(sbo, bo.n, a / s.k) : 0, same);
         }
     }
@@ -401,12 +403,12 @@ __global__ __launch_bounds__(kFusedThreads) void plan_fused_kernel(const int32_t
         L.nbt[threadIdx.x] = __popcll(msk[threadIdx.x]);
     }
     __syncthreads();
-    scan_body<kFusedThreads>(s, p, max_tiles, L);
+    scan_body<T>(s, p, max_tiles, L);
 #pragma unroll
     for (int r = 0; r < kFusedRounds; ++r) {
         if (my_e[r] >= 0) {
-            const int a = r * kFusedThreads + threadIdx.x;
-            const int pos = L.off[my_e[r]] + seg[r * kFusedWaves + wave][my_e[r]] + my_rank[r];
+            const int a = r * T + threadIdx.x;
+            const int pos = L.off[my_e[r]] + seg[r * kWaves + wave][my_e[r]] + my_rank[r];
             put_rank(p, a, pos);
         }
     }
@@ -439,8 +441,13 @@ void launch_corr_update(hipStream_t st, const int32_t* idx_prev, const int32_t* 
 void launch_plan(hipStream_t st, const Shape& s, const BatchOffsets& bo, const PlanPtrs& p,
                  int max_tiles) {
     const int A = s.N * s.k;
+    if (A <= 2 * kThreads) {
+        hipLaunchKernelGGL(plan_fused_kernel<kThreads>, dim3(1), dim3(kThreads), 0, st, p.topk_idx, s, bo, p,
+                           max_tiles, (A + kThreads - 1) / kThreads);
+        return;
+    }
     if (A <= kFusedMax) {
-        hipLaunchKernelGGL(plan_fused_kernel, dim3(1), dim3(kFusedThreads), 0, st, p.topk_idx, s, bo, p,
+        hipLaunchKernelGGL(plan_fused_kernel<kFusedThreads>, dim3(1), dim3(kFusedThreads), 0, st, p.topk_idx, s, bo, p,
                            max_tiles, (A + kFusedThreads - 1) / kFusedThreads);
         return;
     }

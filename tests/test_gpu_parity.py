@@ -521,6 +521,7 @@ def test_seeded_sweep_of_small_configurations(seed):
 @pytest.mark.parametrize("E,k,batches", [
     (1, 1, (1,)), (2, 2, (511, 1)),                # one expert; 1024 assignments: one round of the fused plan
     (256, 8, (1, 0, 127)),                         # as many experts as threads per scan, 1024 assignments
+    (8, 2, (128, 0, 1)), (256, 8, (3,) * 21 + (1,)), (2, 1, (513,)),  # 258 and 512: two rounds of 256; 513: one of 1024
     (64, 6, (31,) * 22 + (0,)),                    # 4092: four rounds, the last one short
     (7, 4, (1024,)), (7, 4, (1, 1024)),            # 4096 and 4100 assignments: fused and chunked
     (256, 8, (40,) * 64), (3, 1, (5000, 3))])      # 20 chunks over all experts, 64 batches; few experts
