@@ -51,13 +51,19 @@ int pick_splits(int row_blocks, int K, int n_out); // split-K factor the launche
 void launch_qkv_finish(hipStream_t st, const float* part, int splits, int64_t split_stride,
                        const Dims& dm, const GroupTab& tab, const double* inv_freq, float* q);
 
+// Ranges the cached positions are cut into: n[b] for every sequence of batch b; first[b] = the (sequence,
+// range) items of the batches before it.
+struct RangeTab {
+    int32_t n[kMaxGroup];
+    int32_t first[kMaxGroup + 1];
+};
+
 // Softmax attention of the new token of every sequence over its batch's cache positions 0..pos;
 // output as bf16 in fragment order ([rows, Hq*hd] as the A operand of the output projection).  The
-// positions may be cut into up to max_splits ranges (pick_attn_splits says how many); `scratch`
-// then holds splits * rows * Hq * (hd + 2) floats: sums, then (maximum, weight) pairs.
-int pick_attn_splits(const Dims& dm, const GroupTab& tab, int max_splits);
+// positions may be cut into up to max_ranges ranges per sequence (attn_ranges says how many); `scratch`
+// holds max_ranges * rows * Hq * (hd + 2) floats: sums, then (maximum, weight) pairs.
 int launch_attention(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab, float* scratch,
-                     int max_splits, void* o_frag);
+                     int max_ranges, void* o_frag);
 
 // y = x + sum of the split-K partials of the output projection, one rounding to bf16.
 void launch_out_finish(hipStream_t st, const float* part, int splits, int64_t split_stride,

@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "attn_kernels.h"
+#include "attn_ranges.h"
 
 namespace kattn {
 namespace {
@@ -296,31 +297,32 @@ __device__ __forceinline__ void write_head(u32x4* __restrict__ o_frag, int row, 
 // Bound by the cache bytes as long as the chip has loads in flight.  A few sequences with long
 // caches do not fill it with one workgroup per (sequence, head): 4 sequences x 8 heads x 8000
 // positions (6 query heads each) ran 32 workgroups for 920 us (0.14 TB/s; 284 bytes of scratch per
-// lane came on top), so the positions are cut into `splits` equal ranges (pick_attn_splits): 23
-// ranges take 36 us (3.6 TB/s) and 5 us for the merge.  With one range the workgroup writes the
-// attention output itself; with several each writes its unnormalised sums and attn_merge_kernel adds
-// them up.  512 sequences x 8 heads x 513 positions keep one range: 173 us, 6.3 TB/s.
-constexpr int kAttnWaves = 4, kChunk = 2;
-
-// Wavefronts per SIMD: query and output slices of a lane take 16 * G registers.  Up to four heads
-// fit the 128 registers that four wavefronts leave; more would spill, so those run with fewer
-// wavefronts and keep their loads in flight by requesting the next chunk before using this one.
-constexpr int attn_waves_per_simd(int G) { return G <= 4 ? 4 : G <= 6 ? 3 : 2; }
-
+// lane came on top), so the positions of a batch's sequences are cut into equal ranges (attn_ranges):
+// 23 ranges take 36 us (3.6 TB/s) and 5 us for the merge.  A sequence of one range is written by its
+// workgroup; with several each writes its unnormalised sums and attn_merge_kernel adds them up.  512
+// sequences x 8 heads x 513 positions keep one range: 173 us, 6.3 TB/s.
 template <int HD, int G>
 __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_decode_kernel(
-    const float* __restrict__ q, Dims dm, GroupTab tab, int splits, float* __restrict__ part_acc,
+    const float* __restrict__ q, Dims dm, GroupTab tab, int all, RangeTab rt, float* __restrict__ part_acc,
     float2* __restrict__ part_ml, u32x4* __restrict__ o_frag) {
     constexpr int LPR = HD / 8, RPW = 64 / LPR;
     constexpr bool AHEAD = G > 4;
     __shared__ float sm[kAttnWaves][G * LPR][10];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int sp = blockIdx.x % splits, pair = blockIdx.x / splits;
-    const int row_g = pair / dm.Hkv, hk = pair % dm.Hkv;
-    const int bt = find_batch(tab, row_g);
-    const int s = row_g - tab.row0[bt], len = tab.pos[bt] + 1;  // positions 0..pos
-    const int per = (len + splits - 1) / splits;
-    const int first = sp * per, end = min(first + per, len);  // empty for the last ranges of a short cache
+    int bt = 0, ranges = all, in_batch = (int)blockIdx.x, row0 = 0;
+    if (all == 0) {
+        while (bt + 1 < tab.n && (int)blockIdx.x >= rt.first[bt + 1] * dm.Hkv) ++bt;
+        ranges = rt.n[bt];
+        in_batch -= rt.first[bt] * dm.Hkv;
+        row0 = tab.row0[bt];
+    }
+    const int sp = in_batch % ranges, pair = in_batch / ranges;
+    const int hk = pair % dm.Hkv, row_g = row0 + pair / dm.Hkv;
+    if (all != 0) bt = find_batch(tab, row_g);
+    const int s = row_g - tab.row0[bt];
+    const int len = tab.pos[bt] + 1;  // positions 0..pos
+    const int per = (len + ranges - 1) / ranges;
+    const int first = sp * per, end = min(first + per, len);  // the last range may be empty
     const int sub = lane % LPR, slot = lane / LPR;
     float qr[G][8];
 #pragma unroll
@@ -445,8 +447,8 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
             for (int j = 0; j < 8; ++j) a2[j] = e[2 + j];
             merge(t, e[0], e[1], a2);
         }
-        if (splits > 1) {
-            const size_t at = ((size_t)sp * tab.row0[tab.n] + row_g) * dm.Hq + hk * G + g;
+        if (ranges > 1) {
+            const size_t at = (size_t)((all != 0 ? row_g * all : rt.first[bt] + s * ranges) + sp) * dm.Hq + hk * G + g;
             float4* pa = reinterpret_cast<float4*>(part_acc + at * HD + sb * 8);
             pa[0] = make_float4(t.acc[0], t.acc[1], t.acc[2], t.acc[3]);
             pa[1] = make_float4(t.acc[4], t.acc[5], t.acc[6], t.acc[7]);
@@ -464,24 +466,31 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
 constexpr int kMergeAhead = 4;
 template <int HD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_acc,
-                                                         const float2* __restrict__ part_ml, int splits,
-                                                         int rows, int Hq, u32x4* __restrict__ o_frag) {
+                                                         const float2* __restrict__ part_ml, int rows, int Hq,
+                                                         int all, u32x4* __restrict__ o_frag, GroupTab tab, RangeTab rt) {
     constexpr int LPR = HD / 8, SIDE = 64 / LPR;
     const int lane = threadIdx.x & 63, sub = lane % LPR;
-    const int rh = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (rh >= rows * Hq) return;  // uniform over the wavefront
-    const size_t stride = (size_t)rows * Hq;
+    const int rh = blockIdx.x * 4 + (threadIdx.x >> 6), row = rh / Hq, head = rh % Hq;
+    if (row >= rows) return;  // uniform over the wavefront
+    int ranges = all;
+    size_t first = (size_t)row * all;
+    if (all == 0) {
+        const int bt = find_batch(tab, row);
+        ranges = rt.n[bt];
+        first = (size_t)rt.first[bt] + (size_t)(row - tab.row0[bt]) * ranges;
+        if (ranges == 1) return;
+    }
     Soft t;
     t.m = kEmpty;
     t.l = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) t.acc[j] = 0.f;
-    for (int s0 = lane / LPR; s0 < splits; s0 += SIDE * kMergeAhead) {
+    for (int s0 = lane / LPR; s0 < ranges; s0 += SIDE * kMergeAhead) {
         float2 ml[kMergeAhead];
         float4 lo[kMergeAhead], hi[kMergeAhead];
 #pragma unroll
         for (int u = 0; u < kMergeAhead; ++u) {  // past the end: the last range again, unused
-            const size_t at = (size_t)min(s0 + u * SIDE, splits - 1) * stride + rh;
+            const size_t at = (first + min(s0 + u * SIDE, ranges - 1)) * Hq + head;
             const float4* pa = reinterpret_cast<const float4*>(part_acc + at * HD + sub * 8);
             ml[u] = part_ml[at];
             lo[u] = pa[0];
@@ -489,7 +498,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
         }
 #pragma unroll
         for (int u = 0; u < kMergeAhead; ++u) {
-            if (s0 + u * SIDE >= splits) break;
+            if (s0 + u * SIDE >= ranges) break;
             const float a2[8] = {lo[u].x, lo[u].y, lo[u].z, lo[u].w, hi[u].x, hi[u].y, hi[u].z, hi[u].w};
             merge(t, ml[u].x, ml[u].y, a2);
         }
@@ -502,7 +511,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
         for (int j = 0; j < 8; ++j) a2[j] = __shfl_xor(t.acc[j], off, 64);
         merge(t, m2, l2, a2);
     }
-    if (lane < LPR) write_head<HD>(o_frag, rh / Hq, (rh % Hq) * LPR + sub, Hq, t);
+    if (lane < LPR) write_head<HD>(o_frag, row, head * LPR + sub, Hq, t);
 }
 
 __global__ __launch_bounds__(256) void out_finish_kernel(const float* __restrict__ part, int splits,
@@ -582,57 +591,46 @@ void launch_qkv_finish(hipStream_t st, const float* part, int splits, int64_t sp
                        splits, split_stride, dm, tab, inv_freq, q);
 }
 
-// Ranges the cached positions of every (sequence, key-value head) are cut into.  A range costs its
-// loop passes plus a fixed part (query load, slot merge, partial sums written and read: about
-// four passes, kRangeCost); the chip holds `slots` workgroups at a time, so the launch costs
-// ceil(pairs * n / slots) rounds of that.  The merge launch counts as kMergeCost passes.
-int pick_attn_splits(const Dims& dm, const GroupTab& tab, int max_splits) {
-    constexpr int kRangeCost = 4, kMergeCost = 8;
-    const int G = dm.Hq / dm.Hkv, rpw = 512 / dm.hd;
-    const long pairs = (long)tab.row0[tab.n] * dm.Hkv, slots = 256L * attn_waves_per_simd(G);
-    int len = 0;
-    for (int b = 0; b < tab.n; ++b) len = tab.pos[b] + 1 > len ? tab.pos[b] + 1 : len;
-    const int step = kAttnWaves * rpw * kChunk;
-    long best = 0;
-    int splits = 1;
-    // more than two rounds of workgroups never pay
-    for (int n = 1; n <= max_splits && (n - 1) * step < len && (n == 1 || pairs * n <= 2 * slots); ++n) {
-        const long passes = ((len + n - 1) / n + step - 1) / step;
-        const long cost = (pairs * n + slots - 1) / slots * (passes + kRangeCost) + (n > 1 ? kMergeCost : 0);
-        if (n == 1 || cost < best) {
-            best = cost;
-            splits = n;
-        }
-    }
-    return splits;
-}
-
 template <int HD>
 static int launch_attention_hd(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab,
-                               float* scratch, int max_splits, void* o_frag) {
-    const int splits = pick_attn_splits(dm, tab, max_splits), rows = tab.row0[tab.n];
-    const dim3 grid(rows * dm.Hkv * splits), block(kAttnWaves * 64);
+                               float* scratch, int max_ranges, void* o_frag) {
+    const int rows = tab.row0[tab.n], G = dm.Hq / dm.Hkv;
+    RangeTab rt;
+    rt.first[0] = 0;
+    bool cut = false, same = true;
+    for (int b = 0; b < tab.n; ++b) {
+        rt.n[b] = b > 0 && tab.pos[b] == tab.pos[b - 1] ? rt.n[b - 1]
+                                                        : attn_ranges(tab.pos[b] + 1, (long)rows * dm.Hkv, G, HD, max_ranges);
+        rt.first[b + 1] = rt.first[b] + (tab.row0[b + 1] - tab.row0[b]) * rt.n[b];
+        cut = cut || rt.n[b] > 1;
+        same = same && rt.n[b] == rt.n[0];
+    }
+    // the number of ranges if it is the same everywhere: the kernels then need not look it up first (each
+    // look-up is a wait on the arguments, about 0.5 us in kernels of 5)
+    const int all = same ? rt.n[0] : 0;
+    const int items = rt.first[tab.n];
+    const dim3 grid(items * dm.Hkv), block(kAttnWaves * 64);
     u32x4* O = (u32x4*)o_frag;
-    float2* ml = (float2*)(scratch + (size_t)splits * rows * dm.Hq * HD);
-    switch (dm.Hq / dm.Hkv) {
+    float2* ml = (float2*)(scratch + (size_t)items * dm.Hq * HD);
+    switch (G) {
 #define KATTN_CASE(G) \
-    case G: hipLaunchKernelGGL((attn_decode_kernel<HD, G>), grid, block, 0, st, q, dm, tab, splits, scratch, ml, O); break;
+    case G: hipLaunchKernelGGL((attn_decode_kernel<HD, G>), grid, block, 0, st, q, dm, tab, all, rt, scratch, ml, O); break;
         KATTN_CASE(1) KATTN_CASE(2) KATTN_CASE(3) KATTN_CASE(4) KATTN_CASE(5) KATTN_CASE(6) KATTN_CASE(7) KATTN_CASE(8)
 #undef KATTN_CASE
         default: return -1;
     }
-    if (splits > 1)
+    if (cut)
         hipLaunchKernelGGL(attn_merge_kernel<HD>, dim3((rows * dm.Hq + 3) / 4), dim3(256), 0, st,
-                           scratch, ml, splits, rows, dm.Hq, O);
+                           scratch, ml, rows, dm.Hq, all, O, tab, rt);
     return 0;
 }
 
 int launch_attention(hipStream_t st, const float* q, const Dims& dm, const GroupTab& tab, float* scratch,
-                     int max_splits, void* o_frag) {
+                     int max_ranges, void* o_frag) {
     switch (dm.hd) {
-        case 32: return launch_attention_hd<32>(st, q, dm, tab, scratch, max_splits, o_frag);
-        case 64: return launch_attention_hd<64>(st, q, dm, tab, scratch, max_splits, o_frag);
-        case 128: return launch_attention_hd<128>(st, q, dm, tab, scratch, max_splits, o_frag);
+        case 32: return launch_attention_hd<32>(st, q, dm, tab, scratch, max_ranges, o_frag);
+        case 64: return launch_attention_hd<64>(st, q, dm, tab, scratch, max_ranges, o_frag);
+        case 128: return launch_attention_hd<128>(st, q, dm, tab, scratch, max_ranges, o_frag);
     }
     return -1;
 }

@@ -13,6 +13,8 @@ from oracle import attn_ref as R
 from paper_2502_06888_amd import attn_binding as A
 from paper_2502_06888_amd import inputs as I
 
+from test_attn_ranges import CUT
+
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
@@ -113,12 +115,77 @@ def test_head_shapes(hd, hq, hkv):
     (128, 8, 1, (2, 1), (1023, 30), False),      # a short cache next to a long one: its last ranges are empty
     (64, 20, 4, (3,), (2047,), True),            # whole loop passes, caches streamed
     (32, 4, 4, (1, 2, 1), (1500, 0, 255), False),
-    (128, 5, 1, (1,), (64, ), False),            # a range of one row at the end
+    (128, 5, 1, (1,), (64, ), False),            # just too short to be cut
     (128, 14, 2, (7,), (321,), False)])
 def test_long_caches_of_few_sequences_are_cut_into_ranges(hd, hq, hkv, seqs, pos, on_host):
     w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=hd, n_q_heads=hq, n_kv_heads=hkv,
                  d_model=256, batch_seqs=seqs, batch_pos=pos, max_len=max(pos) + 2, seed=17)
     run_group(w, on_host=on_host)
+
+
+def quiet(w):
+    """Weights, hidden states and caches of a group whose output is the attention's alone: the residual is
+    2^-13 of its usual size (normalised all the same, rms_eps is smaller still) and the value rows of the
+    new positions are eight times theirs, so that a position lost shows."""
+    ws = I.gen_attn_weights(w, 0)
+    ws["wv"] = ws["wv"] * 8
+    hs = [I.gen_attn_hidden(w, 0, b) * 2.0 ** -13 for b in range(w.n_batches)]
+    caches = [I.gen_kv_cache(w, 0, b) for b in range(w.n_batches)]
+    return ws, hs, caches
+
+
+def run_quiet(w, ws, hs, caches, on_host=False):
+    ctx = A.AttnContext(A.config_for(w), DEV)
+    ctx.set_weights(*[ws[n].to(DEV) for n in ("norm", "wq", "wk", "wv", "wo")])
+    put = (lambda t: t.clone().pin_memory()) if on_host else (lambda t: t.to(DEV))
+    batches = [A.AttnBatch(put(k), put(v), put(h), put(torch.zeros_like(h)), p)
+               for (k, v), h, p in zip(caches, hs, w.batch_pos)]
+    torch.cuda.synchronize()
+    ctx.forward_group(batches)
+    ctx.synchronize()
+    torch.cuda.synchronize()
+    ctx.close()
+    return [b.h_out.cpu() for b in batches]
+
+
+@pytest.mark.parametrize("hd,hq,hkv,seqs,pos,on_host,n", CUT)
+def test_every_range_of_a_cut_cache_counts(hd, hq, hkv, seqs, pos, on_host, n):
+    """Relative error of the output of each batch without the residual.  Operands rounded to bf16 (relative
+    2^-9 at most, 2^-9 / sqrt(3) on average) enter four times: normalised row, new cache row, attention
+    output, result; 2^-9 * 2 = 4e-3 bounds their sum in the 2-norm.  In the oracle the loss of any one
+    range is planted: it must move the output by at least three times that."""
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=hd, n_q_heads=hq, n_kv_heads=hkv, d_model=256,
+                 batch_seqs=seqs, batch_pos=pos, max_len=max(pos) + 2, seed=59, rms_eps=1e-14)
+    ws, hs, caches = quiet(w)
+    want = oracle_group(w, ws, hs, caches)
+    got = run_quiet(w, ws, hs, caches, on_host)
+    limit = 2.0 ** -8
+    for b, (y, (ref, _, _)) in enumerate(zip(got, want)):
+        err = np.linalg.norm(y.double().numpy() - ref) / np.linalg.norm(ref)
+        assert err <= limit, f"batch {b}: {err:.2e} of the result"
+        if n[b] == 1:
+            continue
+        per = -(-(pos[b] + 1) // n[b])
+        for r in sorted({0, 1, n[b] // 2, n[b] - 1}):
+            lost, ws2 = [list(c) for c in caches], dict(ws)
+            lost[b][1] = lost[b][1].clone()
+            lost[b][1][:, :, r * per:(r + 1) * per] = 0
+            if r == n[b] - 1:
+                ws2["wv"] = torch.zeros_like(ws["wv"])      # the new position is in the last range
+            planted = oracle_group(w, ws2, hs, lost)[b][0]
+            moved = np.linalg.norm(planted - ref) / np.linalg.norm(ref)
+            assert moved >= 3 * limit, f"range {r} of batch {b} moves the result by {moved:.2e} only"
+
+
+def test_a_sequence_does_not_depend_on_the_lengths_of_the_others():
+    """The same first batch beside short and beside long caches, same number of rows: same bits."""
+    outs = []
+    for other in (3, 700, 3000):
+        w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=128, n_q_heads=8, n_kv_heads=1, d_model=256,
+                     batch_seqs=(24, 2), batch_pos=(900, other), max_len=3008, seed=61, rms_eps=1e-14)
+        ws, hs, caches = quiet(w)
+        outs.append(run_quiet(w, ws, hs, caches)[0])
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
 def test_ragged_rows_and_several_row_tiles():
