@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
 #pragma unroll
         for (int j = 0; j < 8; ++j) st[g].acc[j] = 0.f;
     }
-    // rows past the end re-read the range's last row (in bounds, weight 0)
+    // rows past the end re-read the range's last row (in bounds and at hand) and count as zeros
     auto load = [&](u32x4(&kr)[kChunk], u32x4(&vr)[kChunk], int p0) {
 #pragma unroll
         for (int c = 0; c < kChunk; ++c) {
@@ -367,6 +367,10 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
         bool valid[kChunk];
 #pragma unroll
         for (int c = 0; c < kChunk; ++c) valid[c] = p0 + c * RPW + slot < end;
+        if (p0 + kChunk * RPW > end)  // weight 0 alone would make NaN of an infinite value
+#pragma unroll
+            for (int c = 0; c < kChunk; ++c)
+                if (!valid[c]) vraw[c] = u32x4{0u, 0u, 0u, 0u};
         float sc[G][kChunk];
 #pragma unroll
         for (int c = 0; c < kChunk; ++c) {

@@ -188,6 +188,28 @@ def test_a_sequence_does_not_depend_on_the_lengths_of_the_others():
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
+@pytest.mark.parametrize("pos", [321, 30])
+def test_infinite_values_in_a_cache_row_stay_infinite(pos):
+    """One infinite element of a value row (first and last rows of the ranges of 30 positions that the
+    longer cache is cut into): the heads that read it are infinite there, not NaN, whatever rows the kernel
+    reads beside it with weight zero.  Output weights all alike: such a sequence's outputs are infinite,
+    the others' are untouched."""
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=128, n_q_heads=4, n_kv_heads=2, d_model=256,
+                 batch_seqs=(7,), batch_pos=(pos,), max_len=324, seed=67, rms_eps=1e-14)
+    ws, hs, caches = quiet(w)
+    ws["wo"] = torch.full_like(ws["wo"], 0.0625)
+    clean = run_quiet(w, ws, hs, caches)[0]
+    for row in (0, 29, 30, 59, 300, pos - 1):
+        if row >= pos:
+            continue
+        k, v = caches[0][0], caches[0][1].clone()
+        v[3, 1, row, 5] = float("inf")
+        y = run_quiet(w, ws, hs, [(k, v)])[0]
+        assert (y[3] == float("inf")).all(), f"row {row}: {y[3, :4]}"
+        y[3] = clean[3]
+        assert torch.equal(y, clean)
+
+
 def test_ragged_rows_and_several_row_tiles():
     # 130 sequences: five row blocks -> two row tiles of four blocks, the last one ragged
     w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=64,
