@@ -176,9 +176,9 @@ __global__ __launch_bounds__(256, 2) void proj_kernel(const u32x4* __restrict__ 
     }
 }
 
-// One thread per rotated pair of kFinHeads consecutive heads of q and k (they share the angle, whose
-// reduction, sine and cosine cost more than the sums), or per element of v, of one sequence.
-constexpr int kFinHeads = 4;
+// One thread per rotated pair of FH consecutive heads of q and k (they share the angle, whose reduction,
+// sine and cosine cost more than the sums), or per element of v, of one sequence.
+template <int FH>
 __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict__ part, int splits,
                                                          int64_t split_stride, Dims dm, GroupTab tab,
                                                          const double* __restrict__ inv_freq,
@@ -191,19 +191,19 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict
     uint16_t* new_rows = (uint16_t*)tab.new_rows[bt];
     const int dq = dm.Hq * hd, dkv = dm.Hkv * hd, n_out = dq + 2 * dkv;
     const int heads = dm.Hq + dm.Hkv;  // heads 0..Hq-1 are q, then k
-    const int n_pairs = (heads + kFinHeads - 1) / kFinHeads * half;
+    const int n_pairs = (heads + FH - 1) / FH * half;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n_pairs + dkv) return;
     const float* row = part + (size_t)row_g * n_out;
     if (i < n_pairs) {
-        const int h0 = i / half * kFinHeads, j = i % half;
-        float a[kFinHeads], b[kFinHeads];
+        const int h0 = i / half * FH, j = i % half;
+        float a[FH], b[FH];
 #pragma unroll
-        for (int u = 0; u < kFinHeads; ++u) a[u] = b[u] = 0.f;
+        for (int u = 0; u < FH; ++u) a[u] = b[u] = 0.f;
         for (int sp = 0; sp < splits; ++sp) {  // partial sums in order, all heads of a split side by side
             const float* p = row + (size_t)sp * split_stride + j;
 #pragma unroll
-            for (int u = 0; u < kFinHeads; ++u) {
+            for (int u = 0; u < FH; ++u) {
                 const int h = min(h0 + u, heads - 1);  // past the last head: the last one again, unused
                 a[u] += p[h * hd];
                 b[u] += p[h * hd + half];
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict
         float sf, c;
         sincosf(red, &sf, &c);
 #pragma unroll
-        for (int u = 0; u < kFinHeads; ++u) {
+        for (int u = 0; u < FH; ++u) {
             const int h = h0 + u;
             if (h >= heads) break;
             const float r0 = a[u] * c - b[u] * sf, r1 = b[u] * c + a[u] * sf;
@@ -588,11 +588,19 @@ void launch_proj(hipStream_t st, const void* a_frag, const void* w_frag, int row
         hipLaunchKernelGGL((proj_kernel<1, 1>), grid, block, 0, st, A, W, out, S, CB, splits, n_rt, n_out, split_stride);
 }
 
+// Heads per thread: few rows leave threads to spare, and one head each is done soonest; from 256 rows on
+// the chip is full and two share the angle.  (32/8 heads of 128: 16 rows 3.3 us with one head, 3.5 with
+// two, 4.0 with four; 512 rows 9.1, 7.7 and 7.2; 48/8 heads, 512 rows 11.9, 10.1 and 14.6; 32/8 heads of
+// 32, 64 rows 3.4, 3.6 and 5.1.)
 void launch_qkv_finish(hipStream_t st, const float* part, int splits, int64_t split_stride,
                        const Dims& dm, const GroupTab& tab, const double* inv_freq, float* q) {
-    const int items = (dm.Hq + dm.Hkv + kFinHeads - 1) / kFinHeads * (dm.hd / 2) + dm.Hkv * dm.hd;
-    hipLaunchKernelGGL(qkv_finish_kernel, dim3((items + 255) / 256, tab.row0[tab.n]), dim3(256), 0, st, part,
-                       splits, split_stride, dm, tab, inv_freq, q);
+    const int rows = tab.row0[tab.n], FH = rows < 256 ? 1 : 2;
+    const int items = (dm.Hq + dm.Hkv + FH - 1) / FH * (dm.hd / 2) + dm.Hkv * dm.hd;
+    const dim3 grid((items + 255) / 256, rows), block(256);
+    if (FH == 1)
+        hipLaunchKernelGGL(qkv_finish_kernel<1>, grid, block, 0, st, part, splits, split_stride, dm, tab, inv_freq, q);
+    else
+        hipLaunchKernelGGL(qkv_finish_kernel<2>, grid, block, 0, st, part, splits, split_stride, dm, tab, inv_freq, q);
 }
 
 template <int HD>

@@ -218,6 +218,14 @@ def test_ragged_rows_and_several_row_tiles():
     run_group(w, on_host=True)
 
 
+@pytest.mark.parametrize("rows,hq,hkv", [(255, 8, 1), (256, 8, 1), (257, 8, 2), (300, 4, 4)])
+def test_rotation_of_one_or_two_heads_per_thread(rows, hq, hkv):
+    """Around the line between one and two heads per thread; an odd number of heads leaves one alone."""
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], d_model=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=32,
+                 batch_seqs=(rows - 2, 2), batch_pos=(5, 11), max_len=16, seed=71)
+    run_group(w, on_host=False)
+
+
 def test_group_mixing_host_and_device_batches():
     """Batches whose caches live on the host next to batches that live on the device, in both
     alternations and with a run of device batches between two host batches."""
