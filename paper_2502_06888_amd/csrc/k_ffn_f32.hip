@@ -5,16 +5,21 @@
 // to 64 rows of one expert (two row blocks of a tile) and UN units of 32 weight rows; a unit of the
 // up projection stacks 16 rows of W1 on the same 16 of W3, so that the gate and the up value of a
 // feature meet in one lane.  The four wavefronts are NB row blocks x UN units x KS parts of the
-// reduction.  fp32 operands and accumulation throughout (32x32x2 MFMA, one fused multiply-add per
-// product, summed in three levels, which keeps the error of a wavefront's dot product over 64 lanes: one
-// chain per accumulator gave 6e-7 of the result at 1024 x 2048, this 2e-7), accurate expf.
+// reduction.  fp32 operands and products (32x32x2 MFMA, one fused multiply-add per product), accurate
+// expf; chains of eight products, pairs of chains added in fp32, the rest of the sum in fp64.  That
+// rounds a dot product of any length less than 64 lanes that stride it and meet in a tree do: relative
+// error of the layer against 64 bits, in 1e-7, 64 x 64 1.32 (64 lanes: 1.42), 256 x 512 1.34 (1.58),
+// 1024 x 256 1.33 (1.78), 1024 x 2048 1.40 (2.06), 2048 x 4096 1.48 (2.56).  (Chains of 16 and fp32 sums
+// above them: 1.59, 1.78, 1.91, 2.04, 2.31, and 4 % faster; fp32 sums above chains of 8: as fast as
+// those, 1.41, 1.70, 1.82, 1.96, 2.23.)
 //
 // What bounds it: the matrix instruction, and with few rows per expert the expert weights.  A
 // workgroup per row with a dot product per wavefront read every weight once per row: the layer of
-// 256 tokens, top-2 of 8 experts, 1024 x 2048 took 844 (up) + 774 us (down); in tiles it takes 71 + 51 us
-// (60 and 42 TFLOP/s, padding rows not counted).  Both operands pass through LDS (straight from the
-// row-major matrices, 32 bytes of 32 rows per load, they took twice as long): whole 128-byte lines from memory, double buffered, the 16-byte pieces
-// of a row permuted by the row's number so that the reads of 16 rows spread over the 64 banks.
+// 256 tokens, top-2 of 8 experts, 1024 x 2048 took 844 (up) + 774 us (down); in tiles it takes 75 + 54 us
+// (57 and 40 TFLOP/s, padding rows not counted).  Both operands pass through LDS (straight from the
+// row-major matrices, 32 bytes of 32 rows per load, they took twice as long): whole 128-byte lines from
+// memory, double buffered, the 16-byte pieces of a row permuted by the row's number so that the reads
+// of 16 rows spread over the 64 banks.
 #include <type_traits>
 
 #include "kernels.h"
@@ -82,11 +87,9 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
                 lds[buf * G::STAGE + slot(sl, r0 + 32 * i, piece)] = in ? x[sl * RL + i] : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     };
-    // three levels of sums: 16 products in an accumulator, four stages in `part`, the parts in `total`
-    f32x16 total, part, acc[2];
-    int parted = 0;
+    double total[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) total[i] = part[i] = 0.f;
+    for (int i = 0; i < 16; ++i) total[i] = 0.;
     // Stage k0 from LDS buffer `buf`; the next one goes from x to the other buffer, and x is filled with
     // the third.  Two stages are in flight because one stage's 1024 cycles of MFMA are shorter than
     // the memory latency.  steady: all of that exists and is whole, so there is no branch and the
@@ -102,23 +105,17 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
             xa[st] = L[slot(ks, b * 32 + (lane & 31), pc)];
             wa[st] = L[slot(ks, (NB + u) * 32 + (lane & 31), pc)];
         }
+        f32x16 acc[2];  // two chains of eight products per half stage
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
+        for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int st = 0; st < kPieces / 2; ++st)
+            for (int st = 2 * half; st < 2 * half + 2; ++st)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[j & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(WFIRST ? wa[st][j] : xa[st][j],
-                                                                  WFIRST ? xa[st][j] : wa[st][j], acc[j & 1], 0, 0, 0);
+                for (int j = 0; j < 4; ++j)
+                    acc[j & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(WFIRST ? wa[st][j] : xa[st][j], WFIRST ? xa[st][j] : wa[st][j],
+                                                                      st % 2 == 0 && j < 2 ? f32x16{} : acc[j & 1], 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) part[i] += acc[0][i] + acc[1][i];
-        if (++parted == 4) {
-            parted = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                total[i] += part[i];
-                part[i] = 0.f;
-            }
+            for (int i = 0; i < 16; ++i) total[i] += (double)(acc[0][i] + acc[1][i]);
         }
         __syncthreads();
     };
@@ -137,10 +134,8 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
         stage(xa, k0, 0, std::false_type{});
         if (k0 + kStageK < K) stage(xb, k0 + kStageK, 1, std::false_type{});  // uniform over the workgroup
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) total[i] += part[i];
     if (G::KS > 1) {  // the parts of the reduction are added in order (LDS: behind the last barrier)
-        float* red = reinterpret_cast<float*>(lds);
+        double* red = reinterpret_cast<double*>(lds);
         const int tile = wave % (NB * UN);
         if (ks > 0)
 #pragma unroll
@@ -152,7 +147,10 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) total[i] += red[((p * NB * UN + tile) * 16 + i) * 64 + lane];
     }
-    return total;
+    f32x16 sums;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sums[i] = (float)total[i];
+    return sums;
 }
 
 // Grid: (groups of output features, row parts, the parts beyond kGridY in z).  Features come first, so
@@ -220,7 +218,9 @@ __device__ __forceinline__ void up_rows(const float* __restrict__ x, const Shape
     }
 }
 
-__global__ __launch_bounds__(kThr) void ffn_up_f32_kernel(
+// Wavefronts per SIMD (launch bounds): what LDS leaves room for.  (Without the down projection's its
+// accumulators went to AGPRs: layer above 148 us instead of 143.)
+__global__ __launch_bounds__(kThr, 3) void ffn_up_f32_kernel(
     const float* __restrict__ x, Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
     const uint8_t* __restrict__ w_single, int only_expert, float* __restrict__ h) {
     __shared__ f32x4 lds[2 * Geo<1, kUpUnits>::STAGE];
@@ -256,7 +256,7 @@ __device__ __forceinline__ void down_rows(const Shape& s, const Part& w, const f
     }
 }
 
-__global__ __launch_bounds__(kThr) void ffn_down_f32_kernel(
+__global__ __launch_bounds__(kThr, 2) void ffn_down_f32_kernel(
     Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
     const uint8_t* __restrict__ w_single, int only_expert, const float* __restrict__ h,
     float* __restrict__ o) {

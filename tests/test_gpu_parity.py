@@ -423,6 +423,22 @@ def test_f32_tiles_steps_and_remainders(d, f, E, k, S, batches):
                         w_std=0.08 if d < 1024 else 0.02))
 
 
+@pytest.mark.parametrize("d,f,bound", [(64, 64, 1.42e-7), (256, 512, 1.58e-7), (1024, 256, 1.78e-7), (1024, 2048, 2.06e-7)])
+def test_f32_error_is_no_larger_than_that_of_sums_over_64_lanes(d, f, bound):
+    """Relative error of the layer against 64 bits (2-norm).  The bounds are what the plainest order gives:
+    64 lanes stride the reduction and meet in a tree.  An order with longer chains or more levels in fp32
+    exceeds them at the short reductions first (chains of 16 products: 1.59e-7, 1.78e-7, 1.91e-7, 2.04e-7)."""
+    w = I.Workload("f32_error", "f32", d, f, 8, 2, batch_tokens=(200, 56), seed=73, w_std=0.02)
+    data, _ = I.gen_layer(w, 0)
+    ctx = H.make_ctx(w)
+    H.place_layer(ctx, w, 0, data)
+    got = H.gpu_layer(ctx, w, 0, data.x, w.batch_offsets)
+    want = H.oracle_layer(w, data, w.batch_offsets)
+    err = np.linalg.norm(got["y"].astype(np.float64) - want.y) / np.linalg.norm(want.y)
+    assert err <= bound, f"{err:.3e}"
+    ctx.close()
+
+
 def test_f32_maximum_topk_and_many_experts():
     w = I.Workload("maxima_f32", "f32", 64, 128, 128, 8, n_shared=2, batch_tokens=(7, 0, 11, 2, 30),
                    w_std=0.1)
