@@ -136,11 +136,11 @@ struct XMap {
     }
 };
 
-// When PASSES * T fits one LDS buffer the stores need no guard.
 // Units of one LDS buffer: what the passes of a stage write, at most a whole tile's stage.
 template <int PASSES, int T>
 constexpr int buf_units() { return PASSES * T < kBufUnits ? PASSES * T : kBufUnits; }
 
+// When PASSES * T fits one LDS buffer the stores need no guard.
 template <int PASSES, int T>
 __device__ __forceinline__ void store_x(const TileCtx& c, const u32x4 (&xr)[PASSES], int buf) {
 #pragma unroll

@@ -16,14 +16,28 @@ constexpr int kMaxBatches = 64;
 
 // Tiles of two row blocks instead of eight: such a tile's accumulators and activation stages leave
 // room for two workgroups per compute unit, so that one streams weights while the other starts or
-// stores, and the last round of workgroups costs half as much.  For groups in which an expert rarely
-// has more than 64 rows (48 on average; a busier expert is several tiles that share its weights
-// through L2).  Shared experts have a row per token: beyond 512 they would be streamed too often.  With
-// few experts the tall tiles' deeper weight rings already stream at 6.4 TB/s.
-// (8 experts of 4096 x 14336, 4 tokens: tall 355 us a layer, short 366-379; 64 + 2 experts of
-// 2048 x 1408, 512 tokens: tall 370, short 330.)
-inline bool short_tiles(int64_t n_tokens, int k, int E, int S) {
-    return E >= 16 && n_tokens * k <= 48ll * E && (S == 0 || n_tokens <= 512);
+// stores, and the last round of workgroups costs half as much; but a workgroup's weight ring is half
+// as deep, and an expert of more than 64 rows is several tiles that share its weights through L2.
+//
+// Layer times, tall / short, over rows per expert r (even routing unless stated):
+//   bf16, no shared experts: 16 x 4096 x 14336: r 1 634 / 685 us, r 48 916 / 956, r 64 954 / 1340;
+//     64 x 2048 x 1408: r 4 230 / 233, r 48 254 / 262, r 64 272 / 331: never short.
+//   bf16, shared experts (a row per token: the tallest of an uneven launch), 64 + 2 x 2048 x 1408: 16
+//     tokens 172 / 178 us, 170 256 / 253, 341 288 / 285, 512 (r 48) 312 / 293, 682 (r 64) 362 / 342, 2048 463 / 714;
+//     skewed routing 128 tokens 261 / 255, 256 296 / 286, 512 376 / 330; 64 + 2 x 5120 x 1536: 341 tokens 673 /
+//     661, 512 761 / 690, 682 818 / 959; 160 + 2 x 2048 x 1408: 106 tokens 536 / 562, 853 (r 32) 669 / 673, 1280 (r
+//     48) 765 / 692, 2560 (r 96) 873 / 1055; 16 experts (4096 x 1792, top-4, 1 shared, skewed): 128 tokens 192 /
+//     207, 192 211 / 222: short from 256 tokens and 32 experts to r 48.
+//   4-bit (bound by the dequantisation, which two workgroups overlap): 8 x 4096 x 14336: r 1 222 / 178 us,
+//     r 16 289 / 223, r 48 299 / 282, r 64 344 / 394; 128 x 4096 x 1536: r 16 499 / 378, r 48 550 / 531, r 64 633 / 675;
+//     launches below a workgroup per compute unit gain nothing: 16 x 2048 x 1408 (176): r 16 63 / 65, r 48 68 / 75;
+//     16 x 1024 x 512 (68) r 16 66 / 85: short from 256 workgroups to r 48.
+inline bool short_tiles(int64_t n_tokens, int k, int E, int S, int f, bool q4) {
+    const int64_t A = n_tokens * k;
+    if (A > 48ll * E) return false;
+    if (!q4) return S > 0 && E >= 32 && n_tokens >= 256;
+    const int64_t rows = (int64_t)kTileBlks * kRowBlk, tiles = (A < E ? A : E) + S * ((n_tokens + rows - 1) / rows);
+    return tiles * ((f / 16 + 7) / 8) >= 256;
 }
 
 // Capacity of the tile tables for a context (either tile height).
@@ -33,7 +47,7 @@ inline int max_tiles_for(int max_rowblks, int E, int S, int max_tokens) {
     };
     const int short_rowblks = 48 * E / kRowBlk + 1 + E;
     const int tall = tiles(max_rowblks, max_tokens, kTileBlks);
-    const int low = tiles(max_rowblks < short_rowblks ? max_rowblks : short_rowblks, max_tokens < 512 ? max_tokens : 512, kShortBlks);
+    const int low = tiles(max_rowblks < short_rowblks ? max_rowblks : short_rowblks, max_tokens < 48 * E ? max_tokens : 48 * E, kShortBlks);
     return tall > low ? tall : low;
 }
 

@@ -302,7 +302,7 @@ Shape make_shape(const moe_ctx* c, int n_tokens) {
     s.S = c->cfg.n_shared;
     s.renorm = c->cfg.renormalize;
     s.max_rowblks = (int32_t)c->L.max_rowblks;
-    const bool low = c->cfg.dtype == MOE_BF16 && short_tiles(n_tokens, s.k, s.E, s.S);
+    const bool low = c->cfg.dtype == MOE_BF16 && short_tiles(n_tokens, s.k, s.E, s.S, s.f, c->cfg.weight_bits == 4);
     s.tile_lg = low ? kShortLg : kTileLg;
     return s;
 }

@@ -369,6 +369,8 @@ def test_prefill_size_outputs_permute_with_the_tokens_in_every_workgroup_order(m
     I.scaled(SMALL, name="shapes_full_tiles", n_experts=2, top_k=1, batch_tokens=(300, 300)),
     I.scaled(SMALL, name="shapes_many_tiles", d_model=192, d_ff=448, n_experts=3, top_k=1,
              batch_tokens=(700, 650, 300)),
+    I.scaled(SMALL, name="shapes_short_tiles", d_model=192, d_ff=448, n_experts=40, n_shared=1, top_k=3,
+             batch_tokens=(300, 130)),
 ], ids=lambda w: w.name)
 def test_every_launch_shape_gives_the_same_bits(w):
     """The launch shapes (8 or 7 wavefronts x 1 unit, 4 x 2 units) and, on full tiles, the order
@@ -562,16 +564,60 @@ def test_plan_at_the_edges_of_its_kernels(E, k, batches):
     ctx.close()
 
 
-@pytest.mark.parametrize("E,k,S,batches", [
-    (16, 8, 1, (33,)),    # 16 or 17 rows on average, 33 of the shared expert: a second block with one row
-    (16, 1, 2, (700, 68)),     # 48 rows on average, but more than 512 with shared experts: tall tiles
-    (16, 1, 0, (700, 68)),      # the most assignments of 16 experts that take short tiles
-    (16, 1, 0, (769,)),         # one more: tall tiles
-    (15, 2, 1, (120,)),         # too few experts: tall tiles
-    (40, 8, 1, (240,)),         # 48 rows on average, some experts beyond 64: two short tiles
-    (24, 2, 1, (512,)), (24, 2, 1, (513,))])   # with shared experts short tiles end at 512 tokens
-def test_short_tiles_of_two_row_blocks(E, k, S, batches):
-    run_case(I.Workload(f"short{E}x{k}", "bf16", 128, 192, E, k, n_shared=S, batch_tokens=batches, seed=31, w_std=0.1))
+def expert_launch(w, bits=16):
+    """(row blocks per tile, wavefronts per workgroup of the up projection) the library chooses for a
+    resident bf16 layer of this group whose tiles are not full, h_planes and variant at their defaults."""
+    N, A, E, S, units = w.n_tokens, w.n_tokens * w.top_k, w.n_experts, w.n_shared, w.d_ff // 16
+    cdiv = lambda a, b: -(-a // b)
+    if bits == 4:
+        short = A <= 48 * E and (min(E, A) + S * cdiv(N, 256)) * cdiv(units, 8) >= 256
+    else:
+        short = A <= 48 * E and S > 0 and E >= 32 and N >= 256
+    rows, slots = (64, 512) if short else (256, 256)
+    tiles = max(min(E, A), cdiv(A, rows)) + S * cdiv(N, rows)
+    cost = {v: cdiv(tiles * cdiv(units, v), slots) * v for v in (7, 8)}
+    return 2 if short else 8, 7 if cost[7] < cost[8] else 8
+
+
+@pytest.mark.parametrize("E,k,S,batches,blocks", [
+    (16, 8, 1, (33,), 8), (16, 1, 2, (700, 68), 8), (16, 1, 0, (700, 68), 8), (16, 1, 0, (769,), 8), (15, 2, 1, (120,), 8),
+    (24, 2, 1, (512,), 8), (24, 2, 1, (513,), 8), (40, 8, 1, (240,), 8),
+    (40, 1, 0, (700,), 8),      # no shared experts: tall tiles
+    (31, 2, 1, (300,), 8), (32, 2, 1, (255,), 8),  # an expert and a token too few
+    (32, 2, 1, (256,), 2),      # 16 rows on average, 256 of the shared expert
+    (32, 6, 1, (256,), 2), (32, 6, 1, (257,), 8),  # 48 rows on average, some beyond 64: two short tiles; one token more
+    (40, 2, 3, (700, 93), 2)])  # 25 blocks per shared expert, the last with 25 rows
+def test_short_tiles_of_two_row_blocks(E, k, S, batches, blocks):
+    w = I.Workload(f"short{E}x{k}", "bf16", 128, 192, E, k, n_shared=S, batch_tokens=batches, seed=31, w_std=0.1)
+    assert expert_launch(w)[0] == blocks
+    run_case(w)
+
+
+@pytest.mark.parametrize("d,f,E,k,S,batches,waves", [
+    (512, 1024, 48, 4, 1, (200, 56), 8),     # 52 tiles x 8 groups of units fit 512 workgroups, x 10 do not
+    (64, 1024, 48, 4, 1, (256,), 8),         # the reduction ends before the weight ring is full
+    (512, 448, 40, 4, 2, (300,), 7), (192, 1472, 32, 3, 1, (256,), 7)])
+@pytest.mark.parametrize("h_planes,scale", [(1, 1), (2, 1), (1, 64)])  # one plane, two, and two where rows ask for it
+def test_short_tiles_in_both_wavefront_shapes_and_precision_modes(d, f, E, k, S, batches, waves, h_planes, scale):
+    w = I.Workload("short_shapes", "bf16", d, f, E, k, n_shared=S, batch_tokens=batches, seed=79,
+                   w_std=float(1.1 / (d * f) ** 0.25))
+    assert expert_launch(w) == (2, waves)
+    data, _ = I.gen_layer(I.scaled(w, n_experts=8, n_shared=0, top_k=min(k, 8)), 0)
+    gate, _ = I.gen_layer(w, 0, with_experts=False)
+    pick = [(5 * e) % 8 for e in range(E + S)]                # eight sets of weights serve all experts
+    w2 = [I.to_storage(I.as_f32(t) * scale, "bf16") for t in data.w2]
+    data = I.LayerData(x=gate.x, wg=gate.wg, w1=[data.w1[i] for i in pick], w3=[data.w3[i] for i in pick], w2=[w2[i] for i in pick])
+    ctx = H.make_ctx(w)
+    H.place_layer(ctx, w, 0, data)
+    ctx.set_tuning(0, h_planes, 0)
+    ctx.reset_stats()
+    got = H.gpu_layer(ctx, w, 0, data.x, w.batch_offsets)
+    want = H.oracle_layer(w, data, w.batch_offsets)
+    H.check_routing(got, want, E)
+    H.check_output(got["y"], want.y, w.dtype)
+    if h_planes == 1:
+        assert (ctx.stats()["h_remainder_wgs"] > 0) == (scale > 1)
+    ctx.close()
 
 
 @pytest.mark.parametrize("batches,S", [((288,), 0), ((417, 1), 1), ((257,), 2), ((545,), 0)])

@@ -12,6 +12,7 @@ from paper_2502_06888_amd import binding as B
 from paper_2502_06888_amd import inputs as I
 
 import harness as H
+from test_gpu_parity import expert_launch
 
 pytestmark = pytest.mark.gpu
 
@@ -152,9 +153,9 @@ def test_seeded_sweep_of_q4_configurations(seed):
 
 
 @pytest.mark.parametrize("d,f,E,k,S,batches", [
-    (64, 64, 16, 2, 0, (5,)),          # short tiles, the reduction is one quad: drain only
+    (64, 64, 16, 2, 0, (5,)),          # the reduction is one quad: drain only
     (448, 192, 20, 4, 1, (100, 0, 9)),  # 28 and 12 steps: inside and just past the ring's look-ahead
-    (1024, 1088, 16, 1, 1, (500,)),    # long enough for the steady state, both row-block classes
+    (1024, 1088, 16, 1, 1, (500,)),    # long enough for the steady state
     (576, 1024, 3, 2, 0, (417,)),      # tall tiles of 4 to 7 blocks
 ])
 @pytest.mark.parametrize("h_planes", [1, 2])
@@ -167,6 +168,34 @@ def test_q4_steady_state_and_drain(d, f, E, k, S, batches, h_planes):
     place_q4(ctx, w, 0, data.wg, experts)
     got = H.gpu_layer(ctx, w, 0, data.x, w.batch_offsets)
     want = oracle_q4(w, data, experts)
+    H.check_routing(got, want, E)
+    H.check_output(got["y"], want.y, w.dtype)
+    ctx.close()
+
+
+@pytest.mark.parametrize("f,E,k,S,batches,launch", [
+    (2048, 16, 4, 0, (100, 93), (8, 8)),   # tall tiles, eight wavefronts: 16 tiles x 16 groups fit 256, x 19 do not
+    (1344, 16, 4, 0, (100, 93), (8, 7)),
+    (1344, 16, 2, 0, (100,), (8, 7)),      # few rows, but below 256 workgroups: tall
+    (2048, 32, 2, 0, (200,), (2, 8)),      # short tiles: 32 x 16 fit 512, x 19 do not
+    (1344, 32, 2, 1, (150,), (2, 7)),
+    (4096, 8, 2, 0, (150, 42), (2, 7)), (4096, 8, 2, 0, (193,), (8, 8))])  # 48 rows on average, and one token more
+@pytest.mark.parametrize("d", [64, 448, 576])  # drain only; inside the look-ahead of the weight ring; steady state
+@pytest.mark.parametrize("h_planes", [1, 2])
+def test_q4_in_both_tile_heights_and_wavefront_shapes(d, f, E, k, S, batches, launch, h_planes):
+    w = I.Workload("q4_shapes", "bf16", d, f, E, k, n_shared=S, batch_tokens=batches, seed=83,
+                   w_std=float(1.1 / (d * f) ** 0.25))
+    assert expert_launch(w, 4) == launch
+    data, _ = I.gen_layer(w, 0, with_experts=False)
+    base = [I.gen_expert_q4(w, 0, e) for e in range(3)]       # three sets of weights serve all experts
+    deq = [[ref.dequant_q4(q.numpy(), bits(s), bits(z), to_bf16=True) for q, s, z in q4] for q4 in base]
+    pick = [(2 * e) % 3 for e in range(E + S)]
+    ctx = make_ctx_q4(w)
+    ctx.set_tuning(0, h_planes, 0)
+    place_q4(ctx, w, 0, data.wg, [base[i] for i in pick])
+    got = H.gpu_layer(ctx, w, 0, data.x, w.batch_offsets)
+    want = ref.moe_layer(I.as_f32(data.x), I.as_f32(data.wg), *[[deq[i][j] for i in pick] for j in range(3)], w.top_k,
+                         w.batch_offsets, w.dtype, n_shared=S, tokens=None)
     H.check_routing(got, want, E)
     H.check_output(got["y"], want.y, w.dtype)
     ctx.close()
