@@ -424,18 +424,23 @@ __global__ __launch_bounds__(kWW * 64) void router_wide_kernel(
         }
     }
     __syncthreads();
-    for (int q = wave; q < MT && t0 + q < N; q += waves) {
+    auto select = [&](int q) {
         if (E <= 64 && renorm) {
             const float v = lane < E ? slog[q][lane] : 0.f;
             if (__ballot(v != v) == 0ull) {  // NaN has no place in the order of ranks: selected as everywhere else
                 rank_and_write(v, lane, t0 + q, E, k, out);
-                continue;
+                return;
             }
         }
         float mine[4];
 #pragma unroll
         for (int s4 = 0; s4 < 4; ++s4) mine[s4] = lane + 64 * s4 < E ? slog[q][lane + 64 * s4] : 0.f;
         select_and_write(mine, lane, t0 + q, E, k, renorm, out);
+    };
+    if (MT <= 2) {  // there are at least two wavefronts
+        if (wave < MT && t0 + wave < N) select(wave);
+    } else {
+        for (int q = wave; q < MT && t0 + q < N; q += waves) select(q);
     }
 }
 
@@ -525,12 +530,14 @@ void launch_router(hipStream_t st, int dtype, const void* x, const void* wg, con
     if (dtype != 0 && s.d % (8 * 64 * kMCB) == 0 && s.E % kEG == 0 && s.E > kEG) {
         const int mt = s.N < 256 ? 1 : s.N < 1024 ? 2 : 4;
         // Wavefronts per workgroup: no more than there are groups of experts (idle ones would only hold
-        // registers: 16 experts, width 4096, 8192 tokens 79 us with eight, 35 with two).  From 2048 tokens
-        // on the workgroups no longer run all at once, and up to four wavefronts that walk the groups in
-        // even passes use the chip better (64 experts, width 2048, eight against four: 1024 tokens 15 and
-        // 20 us, 2048 24 and 23, 8192 73 and 61).
+        // registers: 16 experts, width 4096, 8192 tokens 79 us with eight, 35 with two), but below 2048
+        // tokens one per token to select (1500 tokens 17.1 us with two, 15.9 with four, 23.3 with eight).
+        // From 2048 tokens on the workgroups no longer run all at once, and up to four wavefronts that walk
+        // the groups in even passes use the chip better (64 experts, width 2048, eight against four: 1024
+        // tokens 15 and 20 us, 2048 24 and 23, 8192 73 and 61).
         const int groups = s.E / kEG, most = s.N < 2048 ? kWW : kWW / 2, passes = (groups + most - 1) / most;
-        const int waves = s.N < 2048 ? (groups < most ? groups : most) : (groups + passes - 1) / passes;
+        const int few = groups < mt ? mt : groups < most ? groups : most;
+        const int waves = s.N < 2048 ? few : (groups + passes - 1) / passes;
         const dim3 grid((s.N + mt - 1) / mt), block(waves * 64);
 #define KMOE_WIDE(MT)                                                                                     \
     hipLaunchKernelGGL((router_wide_kernel<bf16raw, MT>), grid, block, 0, st, (const bf16raw*)x,            \
