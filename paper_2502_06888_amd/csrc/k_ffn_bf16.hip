@@ -1066,9 +1066,14 @@ static_assert(lds_bytes<8, kShortBlks>() <= 65536 && lds_bytes<7, kShortBlks>() 
 
 // Full tiles take the two-unit shape only for reductions at least this long: one wavefront per SIMD
 // has nothing to run while it fills its pipeline and stores its results, which two wavefronts share.
-// Reductions of 2048 and 1408 (4099 tokens over 64 + 2 experts): two units 407 + 278 us, one unit
-// 392 + 262; of 4096 and 14336 (1601 tokens over 8): two units 767 + 365, one unit 807 + 390.
-constexpr int kLongReduction = 3072;
+// One unit / two units, 8 experts, top-2, at 1024, 4096 and 16384 tokens.  Up projection to 4096 features:
+// d 1024 67 / 71, 158 / 167, 563 / 574 us; d 2048 108 / 112, 273 / 279, 956 / 965; d 3072 145 / 153, 387 / 391, 1372 /
+// 1372; d 4096 190 / 194, 499 / 495, 1792 / 1765; d 6144 280 / 279, 740 / 726, 2618 / 2561.  Down projection to
+// 4096: f 1408 44 / 47, 131 / 134, 418 / 426; f 2048 56 / 57, 176 / 170, 557 / 538 (the whole layer 349 / 350 at
+// 2048 tokens, 541 / 547, 1744 / 1736; of 1024 features 541 / 547 at 16384); f 2560 68 / 67, 213 / 204, 666 / 649
+// (layer of 2560 400 / 398, 1388 / 1374); f 4096 98 / 96, 310 / 293, 1001 / 988; f 14336 299 / 301, 1017 / 970, 3408 /
+// 3253.
+constexpr int kLongUp = 3072, kLongDown = 2560;
 
 // Launch shapes.  variant 1 / 2: eight / seven wavefronts per workgroup, one output unit each;
 // variant 3: four wavefronts with two units each (every activation fragment read from LDS feeds
@@ -1090,7 +1095,7 @@ void launch_ffn_up_bf16(hipStream_t st, const FfnArgs& a) {
             a.short_tiles ? launch_up_q4<8, kShortBlks>(st, a) : launch_up_q4<8, kTileBlks>(st, a);
         return;
     }
-    const int v = a.variant != 0 ? a.variant : !a.full_tiles ? by_rounds : a.d >= kLongReduction ? 3 : 1;
+    const int v = a.variant != 0 ? a.variant : !a.full_tiles ? by_rounds : a.d >= kLongUp ? 3 : 1;
     if (v == 3 && units >= 2)
         launch_up<4, 2, kTileBlks>(st, a);
     else if (v == 2)
@@ -1104,11 +1109,13 @@ void launch_ffn_down_bf16(hipStream_t st, const FfnArgs& a) {
         if (a.short_tiles) launch_down_q4<8, kShortBlks>(st, a); else launch_down_q4<8, kTileBlks>(st, a);
         return;
     }
-    // Two units per wavefront halve the LDS reads per MFMA: faster on full tiles (prefill layer)
-    // and whenever the remainder plane is multiplied too (twice the MFMAs per weight byte); with
-    // one plane on small tiles (decode layer) eight single-unit wavefronts are 2-3 % faster.
+    // Two units per wavefront halve the LDS reads per MFMA: faster on full tiles of long reductions
+    // and on tall tiles whenever the remainder plane is multiplied too (twice the MFMAs per weight byte);
+    // with one plane on small tiles (decode layer) eight single-unit wavefronts are 2-3 % faster.  Short
+    // tiles stay with one unit: both planes, 64 + 2 experts of 2048 x 1408, layer of 512 tokens 300 us (339 with
+    // tall tiles of two units), 256 tokens 266 (287); 64 + 2 of 5120 x 1536, 512 tokens 700 (847).
     const int units = a.d / 32;
-    const bool two = (a.variant == 3 || (a.variant == 0 && !a.short_tiles && ((a.full_tiles && a.f >= kLongReduction) || a.h_mode == 1))) && units >= 2;
+    const bool two = (a.variant == 3 || (a.variant == 0 && !a.short_tiles && ((a.full_tiles && a.f >= kLongDown) || a.h_mode == 1))) && units >= 2;
     if (two)
         launch_down<4, 2, kTileBlks>(st, a);
     else
