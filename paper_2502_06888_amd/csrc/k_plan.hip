@@ -135,9 +135,10 @@ __device__ __forceinline__ void scan2(int& a, int& b, int& total_a, int& total_b
 
 // First row block of tile j of an expert's n blocks (n for j = tiles).  Up to kEvenTiles tiles are cut
 // evenly (they differ by one block at most), more are full tiles and a rest: an uneven last tile of few
-// leaves the last workgroups of a launch uneven (13 blocks per expert as 8 + 5: layer of 1601 tokens
-// 1259 us, as 7 + 6: 1152), among many it does not matter and full tiles run slightly better (16 and 17
-// tiles per expert: 9.92 ms, cut evenly 10.00).
+// leaves the last workgroups of a launch uneven, among many it does not matter.  Uneven / even, 8 experts
+// of 4096 x 14336, top-2: two tiles 1300 tokens 1185 / 1023 us, 1800 1309 / 1251; three 2600 1919 / 1839; four 3300
+// 2260 / 2167, 3900 2417 / 2427; five to eight, between 4300 and 8100 tokens, from 2907 / 2801 (4300) to 4556 / 4660
+// (7700); 16 and 17 9.92 / 10.00 ms.
 constexpr int kEvenTiles = 4;
 __device__ __forceinline__ int tile_cut(int j, int tiles, int n, int lg) {
     return tiles <= kEvenTiles ? j * n / tiles : min(j << lg, n);
