@@ -588,15 +588,16 @@ void launch_proj(hipStream_t st, const void* a_frag, const void* w_frag, int row
         hipLaunchKernelGGL((proj_kernel<1, 1>), grid, block, 0, st, A, W, out, S, CB, splits, n_rt, n_out, split_stride);
 }
 
-// Heads per thread: few rows leave threads to spare, and one head each is done soonest; from 256 rows on
-// the chip is full and two share the angle.  (32/8 heads of 128: 16 rows 3.3 us with one head, 3.5 with
-// two, 4.0 with four; 512 rows 9.1, 7.7 and 7.2; 48/8 heads, 512 rows 11.9, 10.1 and 14.6; 32/8 heads of
-// 32, 64 rows 3.4, 3.6 and 5.1.)
+// Heads per thread: one, which is done soonest, while the chip holds all workgroups at once (eight of 256
+// threads per compute unit); then two, which share the angle.  (32/8 heads of 128: 16 rows 3.3 us with one
+// head, 3.5 with two, 4.0 with four; 512 rows 9.1, 7.7 and 7.2; 48/8 heads 128 rows 8.7, 6.2 and 10.4; 32/8
+// heads of 32, 64 rows 3.4, 3.6 and 5.1.)
 void launch_qkv_finish(hipStream_t st, const float* part, int splits, int64_t split_stride,
                        const Dims& dm, const GroupTab& tab, const double* inv_freq, float* q) {
-    const int rows = tab.row0[tab.n], FH = rows < 256 ? 1 : 2;
-    const int items = (dm.Hq + dm.Hkv + FH - 1) / FH * (dm.hd / 2) + dm.Hkv * dm.hd;
-    const dim3 grid((items + 255) / 256, rows), block(256);
+    const int rows = tab.row0[tab.n], heads = dm.Hq + dm.Hkv;
+    auto blocks = [&](int FH) { return ((heads + FH - 1) / FH * (dm.hd / 2) + dm.Hkv * dm.hd + 255) / 256; };
+    const int FH = rows * blocks(1) <= 256 * 8 ? 1 : 2;
+    const dim3 grid(blocks(FH), rows), block(256);
     if (FH == 1)
         hipLaunchKernelGGL(qkv_finish_kernel<1>, grid, block, 0, st, part, splits, split_stride, dm, tab, inv_freq, q);
     else

@@ -218,10 +218,11 @@ def test_ragged_rows_and_several_row_tiles():
     run_group(w, on_host=True)
 
 
-@pytest.mark.parametrize("rows,hq,hkv", [(255, 8, 1), (256, 8, 1), (257, 8, 2), (300, 4, 4)])
-def test_rotation_of_one_or_two_heads_per_thread(rows, hq, hkv):
+@pytest.mark.parametrize("rows,hq,hkv,hd", [(512, 8, 8, 64), (513, 8, 8, 64),    # 4 workgroups per row: 2048, and 2052
+                                            (682, 8, 1, 128), (683, 8, 1, 128)])  # 3: 2046, and 2049; nine heads in pairs
+def test_rotation_of_one_or_two_heads_per_thread(rows, hq, hkv, hd):
     """Around the line between one and two heads per thread; an odd number of heads leaves one alone."""
-    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], d_model=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=32,
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], d_model=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd,
                  batch_seqs=(rows - 2, 2), batch_pos=(5, 11), max_len=16, seed=71)
     run_group(w, on_host=False)
 
