@@ -110,8 +110,10 @@ moe_status moe_attn_set_weights(moe_attn_ctx* ctx, int32_t layer, const void* g,
  * the other staging buffer, compute b, then store b's new cache row and hidden state on the
  * store stream.  (A group that is entirely on the device and fits max_group_seqs needs no such
  * order and is computed in one pass, see moe_attn_config.)  Returns after enqueueing; results are valid once the compute stream is
- * synchronised (it is made to wait for the last store).  The batches array is read during the
- * call only.  Errors: MOE_ERR_INVALID_ARG (null, layer, pos or n_seq out of range), MOE_ERR_STATE
+ * synchronised (it is made to wait for the last store).  The bits of a sequence's output follow from
+ * its own inputs and the number of sequences computed with it (which sets how the reductions and long
+ * caches are split), not from what the others hold or how long their caches are.  The batches array is
+ * read during the call only.  Errors: MOE_ERR_INVALID_ARG (null, layer, pos or n_seq out of range), MOE_ERR_STATE
  * (the layer has no weights), MOE_ERR_NOT_PINNED (a host pointer that is not pinned), MOE_ERR_HIP.
  */
 moe_status moe_attn_forward_group(moe_attn_ctx* ctx, int32_t layer, int32_t n_batches,

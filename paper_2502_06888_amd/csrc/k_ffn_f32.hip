@@ -15,8 +15,8 @@
 //
 // What bounds it: the matrix instruction, and with few rows per expert the expert weights.  A
 // workgroup per row with a dot product per wavefront read every weight once per row: the layer of
-// 256 tokens, top-2 of 8 experts, 1024 x 2048 took 844 (up) + 774 us (down); in tiles it takes 75 + 54 us
-// (57 and 40 TFLOP/s, padding rows not counted).  Both operands pass through LDS (straight from the
+// 256 tokens, top-2 of 8 experts, 1024 x 2048 took 844 (up) + 774 us (down); in tiles it takes 71 + 53 us
+// (60 and 41 TFLOP/s, padding rows not counted).  Both operands pass through LDS (straight from the
 // row-major matrices, 32 bytes of 32 rows per load, they took twice as long): whole 128-byte lines from
 // memory, double buffered, the 16-byte pieces of a row permuted by the row's number so that the reads
 // of 16 rows spread over the 64 banks.
@@ -218,8 +218,8 @@ __device__ __forceinline__ void up_rows(const float* __restrict__ x, const Shape
     }
 }
 
-// Wavefronts per SIMD (launch bounds): what LDS leaves room for.  (Without the down projection's its
-// accumulators went to AGPRs: layer above 148 us instead of 143.)
+// Wavefronts per SIMD (launch bounds): what LDS leaves room for; a few dwords per lane go to scratch.
+// (Without the down projection's bound its accumulators went to AGPRs: layer above 148 us instead of 143.)
 __global__ __launch_bounds__(kThr, 3) void ffn_up_f32_kernel(
     const float* __restrict__ x, Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
     const uint8_t* __restrict__ w_single, int only_expert, float* __restrict__ h) {
