@@ -16,6 +16,7 @@ CUT = [
     (64, 20, 4, (3,), (2047,), True, (32,)),               # whole loop passes, caches streamed
     (32, 32, 4, (60,), (2999,), False, (2,)),              # two ranges
     (32, 4, 4, (1, 2, 1), (1500, 0, 255), False, (12, 1, 1)),  # cut and whole caches in one launch
+    (128, 8, 1, (2, 3), (900, 3000), False, (29, 94)),     # two numbers of ranges in one launch
     (128, 14, 2, (5, 2), (321, 350), True, (11, 11)),
 ]
 
