@@ -718,32 +718,39 @@ struct QCtx {
     gptr32 sz;    // (s | z << 16) of this wavefront's unit (+ lane & 31), 32 dwords per quad
 };
 
+// The eight weights of a lane and step, two at a time, so that the pieces can be placed between MFMAs.
 // HT = 0: the dequantised weights as bf16 (one hardware rounding of the fp32 fma).  HT = 1: the
 // same bf16 values handed over as fp16, for the down projection on the fp16 MFMA (exact: the
 // placement scales an expert's (s) by a power of two when its weights would leave the fp16 range).
 template <int HT>
-__device__ __forceinline__ bf16x8 dequant8(uint32_t codes, uint32_t sz) {
-    const float s = __uint_as_float(sz << 16);
-    const float z = __uint_as_float(sz & 0xffff0000u);
-    const float zs = -z * s;
-    // the codes of even and of odd columns, one byte each: a byte converts to float in one instruction
-    // (the empty statements keep the compiler from going back to a shift and a mask per code)
-    uint32_t even = codes & 0x0f0f0f0fu, odd = (codes >> 4) & 0x0f0f0f0fu;
-    asm("" : "+v"(even));
-    asm("" : "+v"(odd));
-    float v[8];
-#pragma unroll
-    for (int p = 0; p < 8; ++p)
-        v[p] = __builtin_fmaf((float)(((p & 1 ? odd : even) >> (8 * (p / 2))) & 0xffu), s, zs);
+struct Dequant {
+    uint32_t even, odd;  // the codes of even and of odd columns, one byte each: a byte converts to float in one instruction
+    float s, zs;
     uint32_t r[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p)  // two at once, round to nearest even
-        r[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v[2 * p], v[2 * p + 1]}), bf16x2));
-    if (HT == 1)
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
+    __device__ __forceinline__ void begin(uint32_t codes, uint32_t sz) {
+        s = __uint_as_float(sz << 16);
+        zs = -__uint_as_float(sz & 0xffff0000u) * s;
+        even = codes & 0x0f0f0f0fu;
+        odd = (codes >> 4) & 0x0f0f0f0fu;
+        asm("" : "+v"(even));  // keeps the compiler from going back to a shift and a mask per code
+        asm("" : "+v"(odd));
+    }
+    __device__ __forceinline__ void pair(int p) {
+        const float v0 = __builtin_fmaf((float)((even >> (8 * p)) & 0xffu), s, zs);
+        const float v1 = __builtin_fmaf((float)((odd >> (8 * p)) & 0xffu), s, zs);
+        r[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v0, v1}), bf16x2));  // nearest even
+        if (HT == 1)
             r[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{__uint_as_float(r[p] << 16), __uint_as_float(r[p] & 0xffff0000u)}), f16x2));
-    return __builtin_bit_cast(bf16x8, u32x4{r[0], r[1], r[2], r[3]});
+    }
+    __device__ __forceinline__ bf16x8 get() const { return __builtin_bit_cast(bf16x8, u32x4{r[0], r[1], r[2], r[3]}); }
+};
+template <int HT>
+__device__ __forceinline__ bf16x8 dequant8(uint32_t codes, uint32_t sz) {
+    Dequant<HT> d;
+    d.begin(codes, sz);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) d.pair(p);
+    return d.get();
 }
 
 template <int NB, int WAVES, int SX>
@@ -788,6 +795,10 @@ __device__ __forceinline__ void open_pass_q4(const TileCtx& c, const QCtx& q, Pi
 // stage's first fragment on entry and the next stage's on return.  A vector instruction takes four
 // cycles, an MFMA 32: with NS MFMAs per step the 24 (up) or 36 (down) instructions of a fragment hide
 // behind them from NS = 4 or 5 on; in one block ahead of the step they added up with the MFMAs.
+// A fence behind every fragment keeps that order (groups of vector instructions between MFMAs did not hold for
+// most heights of a tile: LDS reads were waited for right behind their issue and MFMAs of one accumulator
+// followed each other).  8 experts of 4096 x 14336, top-2, layer with groups / with fences: 300 tokens 376 / 363 us,
+// 512 470 / 461, 1024 1070 / 968, 2600 2252 / 1916, 4096 2926 / 2859; 64 + 2 of 2048 x 1408, 1024 tokens 446 / 428.
 // The quad of a step is reloaded once its last fragment has been taken, one step before its MFMAs.
 template <int MODE, int NB, int SX, int PL, int D, int HT, int PASSES, int T, int DX, int QS, int RS, int RQ>
 __device__ __forceinline__ void stage_mfma_q4(const u32x4* L, u32x4 (&wq)[RQ], uint32_t (&sz)[RQ], int g, const QCtx& q,
@@ -797,7 +808,6 @@ __device__ __forceinline__ void stage_mfma_q4(const u32x4* L, u32x4 (&wq)[RQ], u
     constexpr int NS = NB * PL, NF = NS * SX, DD = D < NF ? D : NF;
     constexpr int L1 = DX == 1 ? (NF / 4 > PASSES ? NF / 4 : PASSES) : NF;
     constexpr int S0 = DX == 1 ? NF / 2 : 0;
-    constexpr int kValu = ((HT == 1 ? 36 : 24) + NS - 1) / NS;  // vector instructions between two MFMAs
     static_assert(PASSES <= NF, "one pass per fragment at most");
     u32x4 win[DD];
 #define KMOE_FRAG_AT(t) L[(((t) % NS) * SX + (t) / NS) * 64]
@@ -805,48 +815,41 @@ __device__ __forceinline__ void stage_mfma_q4(const u32x4* L, u32x4 (&wq)[RQ], u
 #define KMOE_STORE_AT(p) (S0 + ((p) * (NF - S0)) / PASSES)
 #pragma unroll
     for (int t = 0; t < DD; ++t) win[t] = KMOE_FRAG_AT(t);
-    bf16x8 wn = wf;
 #pragma unroll
-    for (int t = 0; t < NF; ++t) {
-        const int j = t / NS, b = (t % NS) / PL;
-        acc[0][b] = mfma<MODE, HT>(wf, as_bf16x8(win[t % DD]), acc[0][b]);
-        if (t % NS == 0) {
-            const int slot = j + 1 < SX ? (g % RS) * QS + (j + 1) / 4 : ((g + 1) % RS) * QS;
-            wn = dequant8<HT>(wq[slot][(j + 1) % 4], sz[slot]);
-        }
-        if (t + DD < NF) win[t % DD] = KMOE_FRAG_AT(t + DD);
-        {
-            const int p = t < S0 ? PASSES : ((t - S0) * PASSES + (NF - S0) - 1) / (NF - S0);
-            if (p < PASSES && KMOE_STORE_AT(p) == t) {
-                const int u = (int)threadIdx.x + p * T;
-                if (PASSES * T <= kBufUnits || u < kBufUnits) next_buf[u] = xs[p];
-            }
-        }
-        {
-            const int p = (t * PASSES + L1 - 1) / L1;
-            if (p < PASSES && KMOE_LOAD_AT(p) == t) xl[p] = xm.template load<false>(c, p, kk + DX * SX);
-        }
-        if (t % NS == NS - 1) {
-            wf = wn;
-            if (j % 4 == 2) {  // step j + 1, the quad's last, has been taken: next ring turn
-                const int slot = (g % RS) * QS + j / 4;
-                const size_t quad = (size_t)((kk + RS * SX) / 4 + j / 4);
-                wq[slot] = load_stream(q.nib + quad * 64);
-                sz[slot] = q.sz[quad * 32];
-            }
-        }
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, DD, 0);
+    for (int j = 0; j < SX; ++j) {
+        Dequant<HT> dq;
+        const int next = j + 1 < SX ? (g % RS) * QS + (j + 1) / 4 : ((g + 1) % RS) * QS;
 #pragma unroll
-    for (int t = 0; t < NF; ++t) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
-        if (t + DD < NF) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        const int ps = t < S0 ? PASSES : ((t - S0) * PASSES + (NF - S0) - 1) / (NF - S0);
-        if (ps < PASSES && KMOE_STORE_AT(ps) == t) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        const int pl = (t * PASSES + L1 - 1) / L1;
-        if (pl < PASSES && KMOE_LOAD_AT(pl) == t) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-        if (t % NS == NS - 1 && t / NS % 4 == 2) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+        for (int i = 0; i < NS; ++i) {
+            const int t = j * NS + i, b = i / PL;
+            acc[0][b] = mfma<MODE, HT>(wf, as_bf16x8(win[t % DD]), acc[0][b]);
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                if (p * NS / (4) == i) {
+                    if (p == 0) dq.begin(wq[next][(j + 1) % 4], sz[next]);
+                    dq.pair(p);
+                }
+            if (t + DD < NF) win[t % DD] = KMOE_FRAG_AT(t + DD);
+            {
+                const int p = t < S0 ? PASSES : ((t - S0) * PASSES + (NF - S0) - 1) / (NF - S0);
+                if (p < PASSES && KMOE_STORE_AT(p) == t) {
+                    const int u = (int)threadIdx.x + p * T;
+                    if (PASSES * T <= kBufUnits || u < kBufUnits) next_buf[u] = xs[p];
+                }
+            }
+            {
+                const int p = (t * PASSES + L1 - 1) / L1;
+                if (p < PASSES && KMOE_LOAD_AT(p) == t) xl[p] = xm.template load<false>(c, p, kk + DX * SX);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wf = dq.get();
+        if (j % 4 == 2) {  // step j + 1, the quad's last, has been taken: next ring turn
+            const int slot = (g % RS) * QS + j / 4;
+            const size_t quad = (size_t)((kk + RS * SX) / 4 + j / 4);
+            wq[slot] = load_stream(q.nib + quad * 64);
+            sz[slot] = q.sz[quad * 32];
+        }
     }
 #undef KMOE_FRAG_AT
 #undef KMOE_LOAD_AT
