@@ -276,6 +276,10 @@ __device__ __forceinline__ void merge(Soft& a, float m2, float l2, const float (
 }
 
 constexpr float kEmpty = -1.0e30f;  // finite stand-in for "no position seen yet"
+// The reference of a running softmax follows the largest score only once a score exceeds it by this much
+// (base 2): the weights of a chunk stay below 2^kLag, far from any limit of fp32, and the sums are not
+// rescaled chunk by chunk.
+constexpr float kLag = 8.f;
 
 // Normalised output of 8 elements (16-byte chunk `chunk` of the row) as bf16 in fragment order.
 template <int HD>
@@ -292,13 +296,15 @@ __device__ __forceinline__ void write_head(u32x4* __restrict__ o_frag, int row, 
 // One workgroup (4 wavefronts) per (sequence, key-value head, part of the cached positions); G query
 // heads share the rows.  A row of HD elements is read by HD/8 lanes (16 bytes each); a wavefront
 // covers 512/HD rows per load, issues the K and V loads of kChunk such row groups together, and keeps
-// one running softmax per row slot (rescaled once per chunk), merged at the end.
+// one running softmax per row slot (rescaled when its reference moves, see kLag), merged at the end.
 //
 // Bound by the cache bytes as long as the chip has loads in flight.  A few sequences with long
 // caches do not fill it with one workgroup per (sequence, head): 4 sequences x 8 heads x 8000
 // positions (6 query heads each) ran 32 workgroups for 920 us (0.14 TB/s; 284 bytes of scratch per
 // lane came on top), so the positions of a batch's sequences are cut into equal ranges (attn_ranges):
-// 23 ranges take 36 us (3.6 TB/s) and 5 us for the merge.  A sequence of one range is written by its
+// 23 ranges took 36 us (3.6 TB/s) and 5 us for the merge.  With six query heads the vector instructions of a
+// row, not its bytes, are the limit: without the rescaling and the masks of chunk after chunk (a quarter of
+// them) the layer takes 109 us instead of 115, 512 sequences of 500 positions 346 instead of 368.  A sequence of one range is written by its
 // workgroup; with several each writes its unnormalised sums and attn_merge_kernel adds them up.  512
 // sequences x 8 heads x 513 positions keep one range: 173 us, 6.3 TB/s.
 template <int HD, int G>
@@ -353,7 +359,8 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
     int p0 = first + wave * RPW * kChunk;
     u32x4 kraw[kChunk], vraw[kChunk], knext[kChunk], vnext[kChunk];
     if (AHEAD && p0 < end) load(knext, vnext, p0);
-    for (; p0 < end; p0 += STEP) {
+    // whole: every row of the chunk is in the range, so nothing is masked
+    auto step = [&](auto whole) {
         if (AHEAD) {
 #pragma unroll
             for (int c = 0; c < kChunk; ++c) {
@@ -366,8 +373,8 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
         }
         bool valid[kChunk];
 #pragma unroll
-        for (int c = 0; c < kChunk; ++c) valid[c] = p0 + c * RPW + slot < end;
-        if (p0 + kChunk * RPW > end)  // weight 0 alone would make NaN of an infinite value
+        for (int c = 0; c < kChunk; ++c) valid[c] = decltype(whole)::value || p0 + c * RPW + slot < end;
+        if (!decltype(whole)::value)  // weight 0 alone would make NaN of an infinite value
 #pragma unroll
             for (int c = 0; c < kChunk; ++c)
                 if (!valid[c]) vraw[c] = u32x4{0u, 0u, 0u, 0u};
@@ -385,24 +392,35 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
                 sc[g][c] = valid[c] ? dot : kEmpty;
             }
         }
-        float pr[G][kChunk];
+        float over = 0.f;  // how far the chunk's scores exceed the reference
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            float mn = st[g].m;
+            float mn = sc[g][0];
 #pragma unroll
-            for (int c = 0; c < kChunk; ++c) mn = fmaxf(mn, sc[g][c]);
-            const float sa = __builtin_amdgcn_exp2f(st[g].m - mn);
-            float add = 0.f;
+            for (int c = 1; c < kChunk; ++c) mn = fmaxf(mn, sc[g][c]);
+            over = fmaxf(over, mn - st[g].m);
+        }
+        if (__any(over > kLag)) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                float mn = st[g].m;
+#pragma unroll
+                for (int c = 0; c < kChunk; ++c) mn = fmaxf(mn, sc[g][c]);
+                const float sa = __builtin_amdgcn_exp2f(st[g].m - mn);
+                st[g].l *= sa;
+                st[g].m = mn;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) st[g].acc[j] *= sa;
+            }
+        }
+        float pr[G][kChunk];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
 #pragma unroll
             for (int c = 0; c < kChunk; ++c) {
-                pr[g][c] = valid[c] ? __builtin_amdgcn_exp2f(sc[g][c] - mn) : 0.f;
-                add += pr[g][c];
+                pr[g][c] = valid[c] ? __builtin_amdgcn_exp2f(sc[g][c] - st[g].m) : 0.f;
+                st[g].l += pr[g][c];
             }
-            st[g].l = st[g].l * sa + add;
-            st[g].m = mn;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) st[g].acc[j] *= sa;
-        }
 #pragma unroll
         for (int c = 0; c < kChunk; ++c) {
             float vf[8];
@@ -412,7 +430,9 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
 #pragma unroll
                 for (int j = 0; j < 8; ++j) st[g].acc[j] = __builtin_fmaf(pr[g][c], vf[j], st[g].acc[j]);
         }
-    }
+    };
+    for (; p0 + kChunk * RPW <= end; p0 += STEP) step(std::true_type{});
+    if (p0 < end) step(std::false_type{});  // the wavefront's last rows
     // row slots of the wavefront
 #pragma unroll
     for (int off = LPR; off < 64; off <<= 1) {

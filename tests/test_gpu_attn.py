@@ -177,6 +177,30 @@ def test_every_range_of_a_cut_cache_counts(hd, hq, hkv, seqs, pos, on_host, n):
             assert moved >= 3 * limit, f"range {r} of batch {b} moves the result by {moved:.2e} only"
 
 
+@pytest.mark.parametrize("rising", [True, False])
+@pytest.mark.parametrize("hd,hq,hkv,seqs,pos", [(128, 6, 1, 3, 1500), (128, 4, 2, 2, 31), (64, 8, 1, 2, 257),
+                                                (32, 8, 4, 5, 700), (128, 8, 1, 1, 16)])
+def test_scores_that_rise_or_fall_along_the_cache(hd, hq, hkv, seqs, pos, rising):
+    """Scores of standard deviation 0 to 5 (base 2) along the positions: the running reference lags by up to
+    8, so a rising cache moves it late and a falling one not at all after the first rows.  The 2-norm bound of
+    the ranges' test, plus what an error of 2^-9 of a score does to its weight: scores reach 5 standard
+    deviations of 5, 25 * ln 2 * 2^-9 = 3.4e-2 of a single weight, less on average."""
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=hd, n_q_heads=hq, n_kv_heads=hkv, d_model=256,
+                 batch_seqs=(seqs,), batch_pos=(pos,), max_len=pos + 2, seed=71, rms_eps=1e-14)
+    ws, hs, caches = quiet(w)
+    h = hs[0].double()
+    q = (h / h.pow(2).mean(1, keepdim=True).sqrt() * ws["norm"].double()) @ ws["wq"].double().T
+    size = q.reshape(seqs, hq, hd).norm(dim=2).mean() * 1.4427 / hd ** 0.5  # of a score with unit normal keys
+    ramp = torch.linspace(0, 5, pos, dtype=torch.float64) if rising else torch.linspace(5, 0, pos, dtype=torch.float64)
+    k, v = caches[0]
+    gen = torch.Generator().manual_seed(73)
+    k = k.clone()
+    k[:, :, :pos] = (torch.randn(seqs, hkv, pos, hd, generator=gen).double() * (ramp / size)[:, None]).to(k.dtype)
+    want = oracle_group(w, ws, hs, [(k, v)])[0][0]
+    got = run_quiet(w, ws, hs, [(k, v)])[0].double().numpy()
+    assert np.linalg.norm(got - want) <= (2.0 ** -8 + 25 * np.log(2) * 2.0 ** -9) * np.linalg.norm(want)
+
+
 def test_a_sequence_does_not_depend_on_the_lengths_of_the_others():
     """The same first batch beside short and beside long caches, same number of rows: same bits."""
     outs = []
