@@ -404,6 +404,26 @@ def test_every_launch_shape_gives_the_same_bits(w):
     ctx.close()
 
 
+@pytest.mark.parametrize("k,S,d,tokens,splits", [
+    (1, 0, 64, (1,), (1, 2, 8)), (2, 0, 192, (3, 4), (1, 3)), (8, 0, 64, (9,), (1, 2)),   # 1 to 24 partial rows per token
+    (7, 1, 128, (5, 2), (1, 2)), (6, 3, 320, (4,), (1, 8)),                               # 8 to 72, slots of both kinds
+    (2, 1, 512, (1024,), (1,)), (2, 1, 512, (1024, 1), (2,)),    # one column per lane up to 1024 tokens of 512, then two
+])
+def test_combine_of_slots_and_splits(k, S, d, tokens, splits):
+    """Token sums where the requests of a pass (eight partial rows) end inside a slot, at its last split, in the
+    always-on experts' rows and past the last row."""
+    w = I.Workload("combine", "bf16", d, 512, 12, k, n_shared=S, batch_tokens=tokens, w_std=0.06)
+    data, _ = I.gen_layer(w, 0)
+    ctx = H.make_ctx(w)
+    H.place_layer(ctx, w, 0, data)
+    want = H.oracle_layer(w, data, w.batch_offsets)
+    for split in splits:
+        ctx.set_tuning(split, 0, 0)
+        got = H.gpu_layer(ctx, w, 0, data.x, w.batch_offsets)
+        H.check_output(got["y"], want.y, w.dtype)
+    ctx.close()
+
+
 def test_maximum_experts_topk_shared_and_batches():
     """The configured maxima at once: 256 routed experts, top-8, 8 shared experts, 64 batches (some
     empty), more assignments than one plan chunk, most experts with a handful of tokens and many
