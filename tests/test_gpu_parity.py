@@ -424,6 +424,13 @@ def test_combine_of_slots_and_splits(k, S, d, tokens, splits):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,f,tokens", [(64, 2048, 128), (64, 2048, 160), (64, 2052, 128), (260, 2052, 300), (36, 2080, 256)])
+def test_f32_additions_between_and_behind_the_products(d, f, tokens):
+    """Up projections of 512 workgroups and a few more than expected (additions between the MFMAs), and of more
+    than 512 (behind them), reductions of whole and of broken stages."""
+    run_case(I.Workload("f32_up", "f32", d, f, 8, 2, batch_tokens=(tokens,), w_std=0.06))
+
+
 def test_maximum_experts_topk_shared_and_batches():
     """The configured maxima at once: 256 routed experts, top-8, 8 shared experts, 64 batches (some
     empty), more assignments than one plan chunk, most experts with a handful of tokens and many
