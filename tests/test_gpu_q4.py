@@ -199,3 +199,30 @@ def test_q4_in_both_tile_heights_and_wavefront_shapes(d, f, E, k, S, batches, la
     H.check_routing(got, want, E)
     H.check_output(got["y"], want.y, w.dtype)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,f,E,tokens", [(64, 2048, 32, 1536), (576, 1344, 40, 1920)])
+def test_q4_short_tiles_end_at_96_rows_per_expert_with_shared_experts(d, f, E, tokens):
+    """Top-2 and one shared expert: 96 rows on average (short tiles) and one token more (tall): right, and with
+    both planes and one split the same bits for the tokens they have in common."""
+    ys = []
+    for n in (tokens, tokens + 1):
+        w = I.Workload("q4_rule", "bf16", d, f, E, 2, n_shared=1, batch_tokens=(n,), seed=89,
+                       w_std=float(1.1 / (d * f) ** 0.25))
+        if n == tokens:
+            data, _ = I.gen_layer(I.scaled(w, batch_tokens=(tokens + 1,)), 0, with_experts=False)
+            base = [I.gen_expert_q4(w, 0, e) for e in range(3)]
+            deq = [[ref.dequant_q4(q.numpy(), bits(s), bits(z), to_bf16=True) for q, s, z in q4] for q4 in base]
+            pick = [(2 * e) % 3 for e in range(E + 1)]
+        ctx = make_ctx_q4(w)
+        ctx.set_tuning(1, 2, 0)
+        place_q4(ctx, w, 0, data.wg, [base[i] for i in pick])
+        x = data.x[:n]
+        got = H.gpu_layer(ctx, w, 0, x, w.batch_offsets)
+        want = ref.moe_layer(I.as_f32(x), I.as_f32(data.wg), *[[deq[i][j] for i in pick] for j in range(3)], 2,
+                             w.batch_offsets, w.dtype, n_shared=1, tokens=None)
+        H.check_routing(got, want, E)
+        H.check_output(got["y"], want.y, w.dtype)
+        ys.append(got["y"])
+        ctx.close()
+    assert np.array_equal(ys[0], ys[1][:tokens])
