@@ -11,6 +11,7 @@
 // 16*ks + 8*(i/4) + 4*hi + i%4, which is exactly how those values fall in the up kernel's
 // accumulator registers, so H never needs a shuffle between the two GEMMs.
 #include <algorithm>
+#include <type_traits>
 
 #include "../../include/moe.h"
 #include "kernels.h"
@@ -334,15 +335,14 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float v) {
 typedef float f32x4 __attribute__((ext_vector_type(4)));  // first-class 16-byte value for streaming loads
 
 // A wavefront item is one token x COLS float4 columns per lane.  Lane j looks up the row and the weight
-// of the token's slot j, all slots at once, and the partial rows of the item are requested kCombineAhead
+// of the token's slot j, all slots at once, and the partial rows of the item are requested AHEAD
 // at a time before the first of them is added.  O is read exactly once: streaming loads.
 //
 // Bound by memory on large groups (64 + 2 experts, width 2048, top-6, 4099 tokens: 49 us, 5.9 TB/s; 512
 // tokens 9.1 us) and by latency on small ones (4 tokens, eight splits: 5.4 us).  Slot after slot and split after
 // split, each waiting for its look-up and its loads, took 60, 17.3 and 21 us.
-constexpr int kCombineAhead = 8;
 static_assert(kMaxTopK + MOE_MAX_SHARED <= 64, "a lane per slot");
-template <bool kBf16Out, int COLS>
+template <bool kBf16Out, int COLS, int AHEAD>
 __global__ __launch_bounds__(kThreads) void combine_kernel(Shape s, PlanPtrs p,
                                                            const float* __restrict__ o, int split_k,
                                                            int64_t split_stride,
@@ -374,9 +374,10 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(Shape s, PlanPtrs p,
         }
         int lj = 0, lsp = 0, aj = 0, asp = 0;  // (slot, split) of the next partial row to request, to add
         while (aj < slots) {
-            f32x4 q[kCombineAhead][COLS];
+            f32x4 q[AHEAD][COLS];
 #pragma unroll
-            for (int i = 0; i < kCombineAhead; ++i) {  // past the last one: the last one again, unused
+            for (int i = 0; i < AHEAD; ++i) {
+                if (lj >= slots) break;  // uniform over the wavefront, as all of (slot, split)
                 const float4* src = reinterpret_cast<const float4*>(
                     o + (size_t)lsp * split_stride + (size_t)__builtin_amdgcn_readlane(row, lj) * s.d);
 #pragma unroll
@@ -384,11 +385,11 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(Shape s, PlanPtrs p,
                     q[i][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + min(col[u], d4 - 1)));
                 if (lsp + 1 < split_k)
                     ++lsp;
-                else if (lj + 1 < slots)
+                else
                     ++lj, lsp = 0;
             }
 #pragma unroll
-            for (int i = 0; i < kCombineAhead; ++i) {
+            for (int i = 0; i < AHEAD; ++i) {
                 if (aj >= slots) break;
                 const bool last = asp + 1 == split_k;
                 if (aj < s.k) {  // splits in order, then the routing weight
@@ -506,18 +507,24 @@ void launch_gather_bf16(hipStream_t st, const void* x, const Shape& s, const Pla
 void launch_combine(hipStream_t st, int out_dtype, const Shape& s, const PlanPtrs& p,
                     const float* o, int split_k, int64_t o_split_stride, void* y) {
     if (s.N <= 0) return;
-    // one wavefront per (token, 64 * COLS float4 columns): one column per lane until that gives two wavefronts per
-    // SIMD, two columns, whose look-ups are shared, beyond
+    // One wavefront per (token, 64 * COLS float4 columns): one column per lane until that gives two wavefronts per
+    // SIMD, two columns, whose look-ups are shared, beyond.  Tokens of up to four partial rows ask for four at a
+    // time, which leaves registers for twice the wavefronts (16384 tokens of two, width 4096: 125 us, with eight 136).
     auto launch = [&](auto kernel, int cols) {
         const int chunks = (s.d / 4 + 64 * cols - 1) / (64 * cols);
         hipLaunchKernelGGL(kernel, dim3(grid_for((size_t)s.N * chunks * 64, 8192)), dim3(kThreads), 0, st, s, p, o,
                            split_k, o_split_stride, y);
     };
-    const bool few = (int64_t)s.N * s.d <= 2048 * 4 * 64;
-    if (out_dtype == 1)
-        few ? launch(combine_kernel<true, 1>, 1) : launch(combine_kernel<true, 2>, 2);
-    else
-        few ? launch(combine_kernel<false, 1>, 1) : launch(combine_kernel<false, 2>, 2);
+    auto pick = [&](auto bf16) {
+        constexpr bool kBf16 = decltype(bf16)::value;
+        if ((int64_t)s.N * s.d <= 2048 * 4 * 64)
+            launch(combine_kernel<kBf16, 1, 8>, 1);
+        else if ((s.k + s.S) * split_k <= 4)
+            launch(combine_kernel<kBf16, 2, 4>, 2);
+        else
+            launch(combine_kernel<kBf16, 2, 8>, 2);
+    };
+    out_dtype == 1 ? pick(std::true_type{}) : pick(std::false_type{});
 }
 
 }  // namespace kmoe
