@@ -277,9 +277,10 @@ __device__ __forceinline__ void merge(Soft& a, float m2, float l2, const float (
 
 constexpr float kEmpty = -1.0e30f;  // finite stand-in for "no position seen yet"
 // The reference of a running softmax follows the largest score only once a score exceeds it by this much
-// (base 2): the weights of a chunk stay below 2^kLag, far from any limit of fp32, and the sums are not
-// rescaled chunk by chunk.
-constexpr float kLag = 8.f;
+// (base 2): the sums are not rescaled chunk by chunk, and the weights stay below 2^kLag instead of 1.  Sums of
+// values that reach kWide so (or are not finite) are formed again without the lag, by weights up to 1; below
+// it the sums of all slots, wavefronts and ranges together stay finite.
+constexpr float kLag = 8.f, kWide = 0x1p100f;
 
 // Normalised output of 8 elements (16-byte chunk `chunk` of the row) as bf16 in fragment order.
 template <int HD>
@@ -304,9 +305,9 @@ __device__ __forceinline__ void write_head(u32x4* __restrict__ o_frag, int row, 
 // lane came on top), so the positions of a batch's sequences are cut into equal ranges (attn_ranges):
 // 23 ranges took 36 us (3.6 TB/s) and 5 us for the merge.  With six query heads the vector instructions of a
 // row, not its bytes, are the limit: without the rescaling and the masks of chunk after chunk (a quarter of
-// them) the layer takes 109 us instead of 115, 512 sequences of 500 positions 346 instead of 368.  A sequence of one range is written by its
-// workgroup; with several each writes its unnormalised sums and attn_merge_kernel adds them up.  512
-// sequences x 8 heads x 513 positions keep one range: 173 us, 6.3 TB/s.
+// them) the layer takes 109 us instead of 115, 512 sequences of 500 positions 346 instead of 368.  A
+// sequence of one range is written by its workgroup; with several each writes its unnormalised sums and
+// attn_merge_kernel adds them up.  512 sequences x 8 heads x 513 positions keep one range: 173 us, 6.3 TB/s.
 template <int HD, int G>
 __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_decode_kernel(
     const float* __restrict__ q, Dims dm, GroupTab tab, int all, RangeTab rt, float* __restrict__ part_acc,
@@ -339,13 +340,6 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
     const u32x4* K = (const u32x4*)tab.kc[bt] + base;
     const u32x4* V = (const u32x4*)tab.vc[bt] + base;
     Soft st[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        st[g].m = kEmpty;
-        st[g].l = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) st[g].acc[j] = 0.f;
-    }
     // rows past the end re-read the range's last row (in bounds and at hand) and count as zeros
     auto load = [&](u32x4(&kr)[kChunk], u32x4(&vr)[kChunk], int p0) {
 #pragma unroll
@@ -356,11 +350,10 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
         }
     };
     constexpr int STEP = kAttnWaves * RPW * kChunk;
-    int p0 = first + wave * RPW * kChunk;
+    int p0;
     u32x4 kraw[kChunk], vraw[kChunk], knext[kChunk], vnext[kChunk];
-    if (AHEAD && p0 < end) load(knext, vnext, p0);
     // whole: every row of the chunk is in the range, so nothing is masked
-    auto step = [&](auto whole) {
+    auto step = [&](auto whole, float lag) {
         if (AHEAD) {
 #pragma unroll
             for (int c = 0; c < kChunk; ++c) {
@@ -400,7 +393,7 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
             for (int c = 1; c < kChunk; ++c) mn = fmaxf(mn, sc[g][c]);
             over = fmaxf(over, mn - st[g].m);
         }
-        if (__any(over > kLag)) {
+        if (__any(over > lag)) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float mn = st[g].m;
@@ -431,8 +424,32 @@ __global__ __launch_bounds__(kAttnWaves * 64, attn_waves_per_simd(G)) void attn_
                 for (int j = 0; j < 8; ++j) st[g].acc[j] = __builtin_fmaf(pr[g][c], vf[j], st[g].acc[j]);
         }
     };
-    for (; p0 + kChunk * RPW <= end; p0 += STEP) step(std::true_type{});
-    if (p0 < end) step(std::false_type{});  // the wavefront's last rows
+    auto begin = [&] {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            st[g].m = kEmpty;
+            st[g].l = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) st[g].acc[j] = 0.f;
+        }
+        p0 = first + wave * RPW * kChunk;
+    };
+    begin();
+    if (AHEAD && p0 < end) load(knext, vnext, p0);
+    for (; p0 + kChunk * RPW <= end; p0 += STEP) step(std::true_type{}, kLag);
+    if (p0 < end) step(std::false_type{}, kLag);  // the wavefront's last rows
+    float size = 0.f;  // a sum, so that NaN stays
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) size += fabsf(st[g].acc[j]);
+    if (!__all(size < kWide)) {
+        begin();
+        for (; p0 < end; p0 += STEP) {
+            if (AHEAD) load(knext, vnext, p0);
+            step(std::false_type{}, 0.f);
+        }
+    }
     // row slots of the wavefront
 #pragma unroll
     for (int off = LPR; off < 64; off <<= 1) {

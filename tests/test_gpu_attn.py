@@ -13,7 +13,7 @@ from oracle import attn_ref as R
 from paper_2502_06888_amd import attn_binding as A
 from paper_2502_06888_amd import inputs as I
 
-from test_attn_ranges import CUT
+from test_attn_ranges import CUT, ranges  # noqa: F401 (a fixture)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -181,8 +181,9 @@ def test_every_range_of_a_cut_cache_counts(hd, hq, hkv, seqs, pos, on_host, n):
 @pytest.mark.parametrize("hd,hq,hkv,seqs,pos", [(128, 6, 1, 3, 1500), (128, 4, 2, 2, 31), (64, 8, 1, 2, 257),
                                                 (32, 8, 4, 5, 700), (128, 8, 1, 1, 16)])
 def test_scores_that_rise_or_fall_along_the_cache(hd, hq, hkv, seqs, pos, rising):
-    """Scores of standard deviation 0 to 5 (base 2) along the positions: the running reference lags by up to
-    8, so a rising cache moves it late and a falling one not at all after the first rows.  The 2-norm bound of
+    """Scores of standard deviation 0 to 5 (base 2) along the positions: a rising cache moves the running reference
+    again and again, a falling one not after the first rows (where a wavefront has several passes: 257 and
+    700 positions; the lag itself is tested below, pass by pass).  The 2-norm bound of
     the ranges' test, plus what an error of 2^-9 of a score does to its weight: scores reach 5 standard
     deviations of 5, 25 * ln 2 * 2^-9 = 3.4e-2 of a single weight, less on average."""
     w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=hd, n_q_heads=hq, n_kv_heads=hkv, d_model=256,
@@ -199,6 +200,79 @@ def test_scores_that_rise_or_fall_along_the_cache(hd, hq, hkv, seqs, pos, rising
     want = oracle_group(w, ws, hs, [(k, v)])[0][0]
     got = run_quiet(w, ws, hs, [(k, v)])[0].double().numpy()
     assert np.linalg.norm(got - want) <= (2.0 ** -8 + 25 * np.log(2) * 2.0 ** -9) * np.linalg.norm(want)
+
+
+def group_queries(w, ws, h):
+    """The first batch's rotated queries in 64 bits: [sequences, kv heads, queries of the group, head_dim]."""
+    norm, wq = (I.as_f32(ws[n]).astype(np.float64) for n in ("norm", "wq"))
+    q = np.stack([R.rmsnorm(r, norm, w.rms_eps) for r in I.as_f32(h)]) @ wq.T
+    q = np.stack([R.rope(v, w.batch_pos[0], w.rope_theta) for v in q.reshape(-1, w.head_dim)])
+    return q.reshape(h.shape[0], w.n_kv_heads, -1, w.head_dim)
+
+
+# Score (base 2) of every position of a loop pass over the cache, pass by pass
+LEVELS = {"late": lambda p: np.array([0, 6, 9.5])[np.minimum(p, 2)],        # 6 below the lag of 8, then past it
+          "far": lambda p: np.where(p == 0, 0, 140.0),                      # a reference left behind overflows
+          "falling": lambda p: np.array([0, -5, -9])[np.minimum(p, 2)],
+          "saw": lambda p: 9.5 * (p % 3),
+          "limit": lambda p: np.where(p == 0, 0, 7.0)}                      # values near the limit of fp32, see below
+
+
+@pytest.mark.parametrize("mode", list(LEVELS))
+@pytest.mark.parametrize("hd,hq,hkv,seqs,pos,cut", [
+    (128, 6, 1, 3, 200, False), (128, 8, 2, 2, 150, False), (128, 5, 1, 1, 97, False), (64, 8, 1, 2, 257, False),
+    (32, 4, 4, 2, 600, False), (128, 12, 2, 20, 2500, True), (128, 4, 1, 70, 2500, True)])
+def test_scores_that_step_from_pass_to_pass(ranges, hd, hq, hkv, seqs, pos, cut, mode):  # noqa: F811
+    """Keys along the queries' pseudo-inverse give all positions of a loop pass one score, which rises below the
+    lag of the running reference, past it, far past it, falls, or both.  Every wavefront has three passes or
+    more, whole caches and cut ones.  With values of 2^119 to 2^120 the sums of weights of 2^7 leave fp32 in a
+    slot of a wavefront (four rows or more: 2^(7 + 119 + 2)), with the 2^115 of longer caches where slots and
+    wavefronts meet (124 rows or more); those of weights up to 1 do neither.  Bound: the ranges' test's, plus
+    the weights' error: 2^-9 of the largest score that is weighed against another one."""
+    step = 4 * (512 // hd) * 2
+    n = ranges(pos + 1, seqs * hkv, hq // hkv, hd)
+    assert (n > 1) == cut and (pos + 1) // n >= 3 * step
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=hd, n_q_heads=hq, n_kv_heads=hkv, d_model=256,
+                 batch_seqs=(seqs,), batch_pos=(pos,), max_len=pos + 2, seed=71, rms_eps=1e-14)
+    ws, hs, caches = quiet(w)
+    unit = np.linalg.pinv(group_queries(w, ws, hs[0])).sum(-1) * hd ** 0.5 * np.log(2)                  # scores 1 with every query of the group
+    level = LEVELS[mode](np.arange(pos) // step)
+    k, v = (t.clone() for t in caches[0])
+    k[:, :, :pos] = torch.from_numpy(unit[:, :, None] * level[:, None]).to(k.dtype)
+    if mode == "limit":
+        gen = torch.Generator().manual_seed(79)
+        v[:, :, :pos] = ((1 + torch.rand(v[:, :, :pos].shape, generator=gen)) * 2.0 ** (119 if pos <= 200 else 115)).to(v.dtype)
+    want = oracle_group(w, ws, hs, [(k, v)])[0][0]
+    got = run_quiet(w, ws, hs, [(k, v)])[0].double().numpy()
+    finite = bool(np.isfinite(got).all())
+    assert finite
+    weighed = {"far": 0, "limit": 0, "saw": 19}.get(mode, 9.5)
+    err = float(np.linalg.norm(got - want) / np.linalg.norm(want))
+    assert err <= 2.0 ** -8 + weighed * np.log(2) * 2.0 ** -9
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("hd,hq,hkv,seqs,pos", [(128, 4, 1, 3, 200), (128, 6, 1, 2, 200), (32, 4, 4, 2, 600)])
+def test_an_infinite_score_behind_the_first_pass(hd, hq, hkv, seqs, pos, sign):
+    """-inf is a position without weight; +inf makes its sequence NaN and no other.  Bound: the ranges' test's,
+    plus 2^-9 of the largest score's distance (5 standard deviations of about 2 around the mean)."""
+    w = I.scaled(I.ATTN_WORKLOADS["attn_tiny"], head_dim=hd, n_q_heads=hq, n_kv_heads=hkv, d_model=256,
+                 batch_seqs=(seqs,), batch_pos=(pos,), max_len=pos + 2, seed=71, rms_eps=1e-14)
+    ws, hs, caches = quiet(w)
+    q = group_queries(w, ws, hs[0])[0, 0]                   # of sequence 0's first key-value head: [queries, hd]
+    j = int(np.argmax(np.abs(np.sign(q).sum(0))))           # the element most of them agree on the sign of
+    if abs(np.sign(q[:, j]).sum()) < len(q):
+        pytest.skip("no element with one sign")
+    k, v = (t.clone() for t in caches[0])
+    k[0, 0, pos * 2 // 3, j] = float("inf") * float(np.sign(q[0, j])) * sign
+    got = run_quiet(w, ws, hs, [(k, v)])[0].double().numpy()
+    if sign > 0:
+        assert bool(np.isnan(got[0]).all())
+        k = caches[0][0]
+    want = oracle_group(w, ws, hs, [(k, v)])[0][0]
+    first = 1 if sign > 0 else 0
+    err = float(np.linalg.norm(got[first:] - want[first:]) / np.linalg.norm(want[first:]))
+    assert err <= 2.0 ** -8 + 10 * np.log(2) * 2.0 ** -9
 
 
 def test_a_sequence_does_not_depend_on_the_lengths_of_the_others():
