@@ -20,7 +20,6 @@
 // row-major matrices, 32 bytes of 32 rows per load, they took twice as long): whole 128-byte lines from
 // memory, double buffered, the 16-byte pieces of a row permuted by the row's number so that the reads
 // of 16 rows spread over the 64 banks.
-#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -53,11 +52,7 @@ struct Geo {
 // row r (activations 0 .. NB*32-1, then weights).  Valid on return for wavefronts with ks == 0:
 // register i holds, of the wavefront's unit and row block, weight row 8 (i / 4) + 4 (lane / 32) + i % 4
 // and activation row lane % 32 (WFIRST) or the other way round.
-// BETWEEN: where the additions of a half stage go (two chains of eight products, an MFMA takes 64 cycles).
-// Between the MFMAs of the next half stage they cost nothing, but the second pair of accumulators leaves
-// room for two wavefronts per SIMD only; behind their own MFMAs they hold the wavefront for as long again,
-// which a third wavefront hides.  The sums have the same bits.
-template <int NB, int UN, bool WFIRST, bool BETWEEN, typename RowFn>
+template <int NB, int UN, bool WFIRST, typename RowFn>
 __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
     using G = Geo<NB, UN>;
     static_assert(NB * UN * G::KS == kWaves && G::ROWS * kPieces * G::KS % kThr == 0, "geometry");
@@ -99,24 +94,9 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
     // the third.  Two stages are in flight because one stage's 1024 cycles of MFMA are shorter than
     // the memory latency.  steady: all of that exists and is whole, so there is no branch and the
     // wait before the stores leaves the younger loads in flight.
-    f32x16 acc[BETWEEN ? 2 : 1][2];  // [half stage][chain]
-    if (BETWEEN) acc[BETWEEN][0] = acc[BETWEEN][1] = f32x16{};
-    auto fold = [&](const f32x16 (&chains)[2], int i0, int i1) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (i >= i0 && i < i1) total[i] += (double)(chains[0][i] + chains[1][i]);
-    };
     auto stage = [&](Regs& x, int k0, int buf, auto steady) {
-        auto put = [&] {
-            if (decltype(steady)::value || k0 + kStageK < K) store(x, k0 + kStageK, buf ^ 1, steady);
-        };
-        auto get = [&] {
-            if (decltype(steady)::value || k0 + 3 * kStageK < K) load(x, k0 + 3 * kStageK, steady);
-        };
-        if (!BETWEEN) {
-            put();
-            get();
-        }
+        if (decltype(steady)::value || k0 + kStageK < K) store(x, k0 + kStageK, buf ^ 1, steady);
+        if (decltype(steady)::value || k0 + 3 * kStageK < K) load(x, k0 + 3 * kStageK, steady);
         const f32x4* L = lds + buf * G::STAGE;
         f32x4 xa[kPieces / 2], wa[kPieces / 2];
 #pragma unroll
@@ -125,22 +105,17 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
             xa[st] = L[slot(ks, b * 32 + (lane & 31), pc)];
             wa[st] = L[slot(ks, (NB + u) * 32 + (lane & 31), pc)];
         }
+        f32x16 acc[2];  // two chains of eight products per half stage
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-            f32x16(&now)[2] = acc[BETWEEN ? half : 0];
 #pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const int st = 2 * half + m / 4, j = m % 4;
-                now[j & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(WFIRST ? wa[st][j] : xa[st][j], WFIRST ? xa[st][j] : wa[st][j],
-                                                                  m < 2 ? f32x16{} : now[j & 1], 0, 0, 0);
-                if (BETWEEN) {
-                    if (m > 0) fold(acc[BETWEEN ? half ^ 1 : 0], (m - 1) * 16 / 7, m * 16 / 7);
-                    if (half == 0 && m == 2) put();
-                    if (half == 0 && m == 5) get();
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (!BETWEEN) fold(now, 0, 16);
+            for (int st = 2 * half; st < 2 * half + 2; ++st)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[j & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(WFIRST ? wa[st][j] : xa[st][j], WFIRST ? xa[st][j] : wa[st][j],
+                                                                      st % 2 == 0 && j < 2 ? f32x16{} : acc[j & 1], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) total[i] += (double)(acc[0][i] + acc[1][i]);
         }
         __syncthreads();
     };
@@ -159,7 +134,6 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
         stage(xa, k0, 0, std::false_type{});
         if (k0 + kStageK < K) stage(xb, k0 + kStageK, 1, std::false_type{});  // uniform over the workgroup
     }
-    if (BETWEEN) fold(acc[BETWEEN], 0, 16);
     if (G::KS > 1) {  // the parts of the reduction are added in order (LDS: behind the last barrier)
         double* red = reinterpret_cast<double*>(lds);
         const int tile = wave % (NB * UN);
@@ -181,8 +155,7 @@ __device__ __forceinline__ f32x16 reduce_tile(RowFn row, int K, f32x4* lds) {
 
 // Grid: (groups of output features, row parts, the parts beyond kGridY in z).  Features come first, so
 // that the workgroups of a row part spread over all XCDs and those that share weight rows (the parts of
-// an expert) tend to meet on one: parts first left half of the XCDs without live workgroups (a tile
-// has four parts, of which one or two exist) and took 1.8 times as long.
+// an expert) tend to meet on one: parts first took 1.8 times as long.
 constexpr int kGridY = 32768;
 
 struct Part {
@@ -190,17 +163,44 @@ struct Part {
     int xblk;           // first row block in the token space of the expert
 };
 
-// Which expert and row blocks does this workgroup serve?
-__device__ __forceinline__ Part locate(const PlanPtrs& p, int only_expert) {
+// Which expert and row blocks does this workgroup serve?  Only the parts that exist are numbered, tile by
+// tile (sums over the tile table, a tile per lane).  A tile has up to four parts, mostly one or two, and
+// workgroups go to the compute units in turn whatever these hold already: with all four numbered some units
+// held three live workgroups and others none, by the multiples of the feature groups.  Layers, four
+// numbered / those that exist, top-2: 8 experts of 1024 x 2048, 8 tokens 92 / 72 us, 128 139 / 92, 256 141 /
+// 140, 512 222 / 228, 4096 1118 / 1123; 12 of 256 x 1536, 264 tokens 84 / 69; 128 + 2 of 512 x 256, top-6, 512 tokens 225 / 133.
+// (Two wavefronts per SIMD, the additions between the MFMAs of the next half stage, evened the placement out
+// by accident and helped or hurt by the same multiples; with the parts in a row three wavefronts are
+// as fast or faster at every size.)
+__device__ __forceinline__ Part locate(const PlanPtrs& p, int only_expert, int max_tiles) {
+    static_assert(kPairsPerTile < 8, "three bits per tile");
     Part w{0, 0, 0, 0};
-    const int part = (int)blockIdx.z * kGridY + (int)blockIdx.y;
-    const int i = part / kPairsPerTile, pair = part % kPairsPerTile;
-    if (i >= (only_expert >= 0 ? p.exp_ntiles[only_expert] : p.meta[1])) return w;
-    const int tile = only_expert >= 0 ? p.exp_tile0[only_expert] + i : i;
-    w.e = p.tile_expert[tile];
-    w.hblk = p.tile_hblk[tile] + pair * kPairBlks;
-    w.xblk = p.tile_xblk[tile] + pair * kPairBlks;
-    w.nblk = max(0, min(kPairBlks, p.tile_nblk[tile] - pair * kPairBlks));
+    const int lane = threadIdx.x & 63;
+    const int tile0 = only_expert >= 0 ? p.exp_tile0[only_expert] : 0;
+    const int tiles = min(only_expert >= 0 ? p.exp_ntiles[only_expert] : p.meta[1], max_tiles);
+    int part = (int)blockIdx.z * kGridY + (int)blockIdx.y;
+    for (int t0 = 0; t0 < tiles; t0 += 64) {
+        const int tile = tile0 + min(t0 + lane, max_tiles - 1);  // all loads at once, `tiles` included
+        const int e = p.tile_expert[tile], hblk = p.tile_hblk[tile], xblk = p.tile_xblk[tile], nblk = p.tile_nblk[tile];
+        const int n = t0 + lane < tiles ? (nblk + kPairBlks - 1) / kPairBlks : 0;
+        const uint64_t ones = __ballot(n & 1), twos = __ballot(n & 2), fours = __ballot(n & 4);
+        auto sum = [&](uint64_t lanes) {
+            return __popcll(ones & lanes) + 2 * __popcll(twos & lanes) + 4 * __popcll(fours & lanes);
+        };
+        const int total = sum(~0ull);
+        if (part < total) {
+            const int pair = part - sum((1ull << lane) - 1);  // of this lane's tile, if it has as many
+            const int l = __ffsll((unsigned long long)__ballot(pair >= 0 && pair < n)) - 1;
+            auto of = [&](int v) { return __builtin_amdgcn_readlane(v, l); };
+            const int first = of(pair) * kPairBlks;
+            w.e = of(e);
+            w.hblk = of(hblk) + first;
+            w.xblk = of(xblk) + first;
+            w.nblk = min(kPairBlks, of(nblk) - first);
+            break;
+        }
+        part -= total;
+    }
     return w;
 }
 
@@ -216,7 +216,7 @@ __device__ __forceinline__ int token_of(const Shape& s, const PlanPtrs& p, const
 
 // h[row, n] = silu(W1[n,:] . x) * (W3[n,:] . x)
 constexpr int kUpUnits = 2, kUpFeat = 16 * kUpUnits;
-template <int NB, bool BETWEEN>
+template <int NB>
 __device__ __forceinline__ void up_rows(const float* __restrict__ x, const Shape& s, const PlanPtrs& p,
                                         const Part& w, const float* blob, f32x4* lds, float* __restrict__ h) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -226,7 +226,7 @@ __device__ __forceinline__ void up_rows(const float* __restrict__ x, const Shape
         const int i = (r - NB * 32) % 32, n = min(n0 + (r - NB * 32) / 32 * 16 + i % 16, s.f - 1);
         return blob + ((size_t)(i / 16) * s.f + n) * s.d;
     };
-    const f32x16 acc = reduce_tile<NB, kUpUnits, true, BETWEEN>(row, s.d, lds);
+    const f32x16 acc = reduce_tile<NB, kUpUnits, true>(row, s.d, lds);
     if (wave / (NB * kUpUnits) != 0) return;
     const int r = wave % NB * 32 + (lane & 31), f0 = n0 + wave / NB % kUpUnits * 16 + 4 * (lane >> 5);
     if (token_of(s, p, w, r) < 0) return;
@@ -246,19 +246,18 @@ __device__ __forceinline__ void up_rows(const float* __restrict__ x, const Shape
 
 // Wavefronts per SIMD (launch bounds): what LDS leaves room for; a few dwords per lane go to scratch.
 // (Without the down projection's bound its accumulators went to AGPRs: layer above 148 us instead of 143.)
-template <bool BETWEEN>
-__global__ __launch_bounds__(kThr, BETWEEN ? 2 : 3) void ffn_up_f32_kernel(
+__global__ __launch_bounds__(kThr, 3) void ffn_up_f32_kernel(
     const float* __restrict__ x, Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
-    const uint8_t* __restrict__ w_single, int only_expert, float* __restrict__ h) {
+    const uint8_t* __restrict__ w_single, int only_expert, int max_tiles, float* __restrict__ h) {
     __shared__ f32x4 lds[2 * Geo<1, kUpUnits>::STAGE];
     static_assert(Geo<1, kUpUnits>::STAGE >= Geo<2, kUpUnits>::STAGE, "LDS of the larger stage");
-    const Part w = locate(p, only_expert);
+    const Part w = locate(p, only_expert, max_tiles);
     if (w.nblk == 0) return;
     const float* blob = reinterpret_cast<const float*>(w_single ? w_single : wtab[w.e]);
     if (w.nblk == 1)
-        up_rows<1, BETWEEN>(x, s, p, w, blob, lds, h);
+        up_rows<1>(x, s, p, w, blob, lds, h);
     else
-        up_rows<2, BETWEEN>(x, s, p, w, blob, lds, h);
+        up_rows<2>(x, s, p, w, blob, lds, h);
 }
 
 // o[row, m] = W2[m,:] . h[row,:]
@@ -272,7 +271,7 @@ __device__ __forceinline__ void down_rows(const Shape& s, const Part& w, const f
         if (r < NB * 32) return h + ((size_t)w.hblk * kRowBlk + r) * s.f;
         return w2 + (size_t)min(m0 + r - NB * 32, s.d - 1) * s.f;
     };
-    const f32x16 acc = reduce_tile<NB, kDownUnits, false, false>(row, s.f, lds);
+    const f32x16 acc = reduce_tile<NB, kDownUnits, false>(row, s.f, lds);
     if (wave / (NB * kDownUnits) != 0) return;
     const int col = m0 + wave / NB % kDownUnits * 32 + (lane & 31);
     if (col >= s.d) return;
@@ -285,11 +284,11 @@ __device__ __forceinline__ void down_rows(const Shape& s, const Part& w, const f
 
 __global__ __launch_bounds__(kThr, 2) void ffn_down_f32_kernel(
     Shape s, PlanPtrs p, const uint8_t* const* __restrict__ wtab,
-    const uint8_t* __restrict__ w_single, int only_expert, const float* __restrict__ h,
+    const uint8_t* __restrict__ w_single, int only_expert, int max_tiles, const float* __restrict__ h,
     float* __restrict__ o) {
     __shared__ f32x4 lds[2 * Geo<1, kDownUnits>::STAGE];
     static_assert(Geo<1, kDownUnits>::STAGE >= Geo<2, kDownUnits>::STAGE, "LDS of the larger stage");
-    const Part w = locate(p, only_expert);
+    const Part w = locate(p, only_expert, max_tiles);
     if (w.nblk == 0) return;
     const float* w2 = reinterpret_cast<const float*>(w_single ? w_single : wtab[w.e]) + 2 * (size_t)s.f * s.d;
     if (w.nblk == 1)
@@ -308,19 +307,10 @@ void launch_ffn_f32(hipStream_t st, const float* x, const Shape& s, const PlanPt
         const int parts = max_tiles * kPairsPerTile;
         return dim3((features + per_group - 1) / per_group, parts < kGridY ? parts : kGridY, (parts + kGridY - 1) / kGridY);
     };
-    // Up projection: additions between the MFMAs while the chip is expected to hold all workgroups at two per
-    // compute unit.  Rows per expert r: one part up to 32, then r / 64 and half a part for the uneven rest.
-    // Kernel times behind / between, 8 experts of 1024 x 2048, top-2: 64 tokens
-    // (320 to 512 workgroups) 42.3 / 33.8 us, 128 (512 and some) 69.7 / 53.6, 256 (768) 70.6 / 82.2, 512 (1280) 113.8 /
-    // 123.8.  The down projection gains nothing from it (32.1 / 31.7, 51.8 / 51.9, 52.0 / 52.4, 68.1 / 68.9).
-    const int64_t assigned = (int64_t)s.N * s.k, served = std::min<int64_t>(s.E, assigned);
-    const int64_t halves = std::max<int64_t>(2, assigned / (32 * s.E) + 1);
-    const int64_t live = only_expert >= 0 ? (int64_t)max_tiles * kPairsPerTile
-                                          : served * halves / 2 + (int64_t)s.S * ((s.N + 63) / 64);
-    auto* up = live * ((s.f + kUpFeat - 1) / kUpFeat) <= 512 ? ffn_up_f32_kernel<true> : ffn_up_f32_kernel<false>;
-    hipLaunchKernelGGL(up, grid(s.f, kUpFeat), dim3(kThr), 0, st, x, s, p, wtab, w_single, only_expert, h);
+    hipLaunchKernelGGL(ffn_up_f32_kernel, grid(s.f, kUpFeat), dim3(kThr), 0, st, x, s, p, wtab, w_single,
+                       only_expert, max_tiles, h);
     hipLaunchKernelGGL(ffn_down_f32_kernel, grid(s.d, kDownFeat), dim3(kThr), 0, st, s, p, wtab, w_single,
-                       only_expert, h, o);
+                       only_expert, max_tiles, h, o);
 }
 
 }  // namespace kmoe

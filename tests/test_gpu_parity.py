@@ -425,10 +425,21 @@ def test_combine_of_slots_and_splits(k, S, d, tokens, splits):
 
 
 @pytest.mark.parametrize("d,f,tokens", [(64, 2048, 128), (64, 2048, 160), (64, 2052, 128), (260, 2052, 300), (36, 2080, 256)])
-def test_f32_additions_between_and_behind_the_products(d, f, tokens):
-    """Up projections of 512 workgroups and a few more than expected (additions between the MFMAs), and of more
-    than 512 (behind them), reductions of whole and of broken stages."""
+def test_f32_up_projections_of_many_workgroups(d, f, tokens):
+    """512 to 1000 workgroups with rows, reductions of whole and of broken stages."""
     run_case(I.Workload("f32_up", "f32", d, f, 8, 2, batch_tokens=(tokens,), w_std=0.06))
+
+
+@pytest.mark.parametrize("E,k,S,batches", [
+    (1, 1, 1, (16700,)),        # 66 tiles of each kind: the tile table is read in three pieces
+    (70, 1, 0, (300,)),         # 64 tiles of one or two row blocks and a few more
+    (3, 2, 2, (545, 33)),       # tiles of 5 to 8 row blocks: two to four pairs, the last one single or not
+    (64, 8, 0, (9,)), (130, 2, 1, (700,))])
+def test_f32_every_pair_of_row_blocks_is_served_once(E, k, S, batches):
+    """Workgroups number the pairs of row blocks that exist, tile by tile: pieces of 64 tiles, tiles of one to
+    four pairs, experts without tokens, shared experts in front."""
+    run_case(I.Workload("f32_pairs", "f32", 256, 36, E, k, n_shared=S, batch_tokens=batches, zipf_s=1.1 if E > 3 else 0.0,
+                        corr=0.0, seed=97, w_std=0.08))
 
 
 def test_maximum_experts_topk_shared_and_batches():

@@ -163,8 +163,9 @@ def test_window_too_small_reports_oom_and_context_survives():
     ctx.close()
 
 
-def test_f32_streamed_equals_resident():
-    w = I.Workload("f32_stream", "f32", 64, 128, 4, 2, n_layers=2, batch_tokens=(9, 14),
+@pytest.mark.parametrize("batches", [(9, 14), (700, 33)])     # one row part per expert; several tiles
+def test_f32_streamed_equals_resident(batches):
+    w = I.Workload("f32_stream", "f32", 64, 128, 4, 2, n_layers=2, batch_tokens=batches,
                    streamed=True, window_layers=2)
     layers = gen_stack(w)
     want = resident_reference(w, layers)
