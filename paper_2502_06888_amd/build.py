@@ -25,7 +25,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     headers = [os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "attn_kernels.h"),
-               os.path.join(CSRC, "attn_ranges.h"),
+               os.path.join(CSRC, "attn_ranges.h"), os.path.join(CSRC, "tile_rules.h"),
                os.path.join(HERE, "..", "include", "moe.h"), os.path.join(HERE, "..", "include", "moe_attn.h")]
     jobs = []
     for name in SOURCES:

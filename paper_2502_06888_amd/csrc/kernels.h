@@ -3,58 +3,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tile_rules.h"
+
 namespace kmoe {
 
 constexpr int kLanes = 64;
-constexpr int kRowBlk = 32;        // rows (tokens) per MFMA block
-constexpr int kTileLg = 3, kTileBlks = 1 << kTileLg;     // row blocks per tile (256 rows), at most
-constexpr int kShortLg = 1, kShortBlks = 1 << kShortLg;  // the same for small batch groups (see short_tiles)
 constexpr int kPlanChunk = 1024;   // assignments per block of the dispatch kernels
 constexpr int kMaxExperts = 256;
 constexpr int kMaxTopK = 8;
 constexpr int kMaxBatches = 64;
-
-// Tiles of two row blocks instead of eight: such a tile's accumulators and activation stages leave
-// room for two workgroups per compute unit, so that one streams weights while the other starts or
-// stores, and the last round of workgroups costs half as much; but a workgroup's weight ring is half
-// as deep, and an expert of more than 64 rows is several tiles that share its weights through L2.
-//
-// Layer times, tall / short, over rows per expert r (even routing unless stated):
-//   bf16, no shared experts: 16 x 4096 x 14336: r 1 634 / 685 us, r 48 916 / 956, r 64 954 / 1340;
-//     64 x 2048 x 1408: r 4 230 / 233, r 48 254 / 262, r 64 272 / 331: never short.
-//   bf16, shared experts (a row per token: the tallest of an uneven launch), 64 + 2 x 2048 x 1408: 16
-//     tokens 172 / 178 us, 170 256 / 253, 341 288 / 285, 512 (r 48) 312 / 293, 682 (r 64) 362 / 342, 2048 463 / 714;
-//     skewed routing 128 tokens 261 / 255, 256 296 / 286, 512 376 / 330; 64 + 2 x 5120 x 1536: 341 tokens 673 /
-//     661, 512 761 / 690, 682 818 / 959; 160 + 2 x 2048 x 1408: 106 tokens 536 / 562, 853 (r 32) 669 / 673, 1280 (r
-//     48) 765 / 692, 2560 (r 96) 873 / 1055; 16 experts (4096 x 1792, top-4, 1 shared, skewed): 128 tokens 192 /
-//     207, 192 211 / 222: short from 256 tokens and 32 experts to r 48.
-//   4-bit (two workgroups overlap dequantisation and MFMAs), no shared experts: 8 x 4096 x 14336: r 1 218 /
-//     176 us, r 16 288 / 226, r 48 301 / 291, r 64 336 / 403; 128 x 4096 x 1536: r 16 509 / 389, r 48 578 / 553, r 64
-//     667 / 712; 64 x 2048 x 1408: r 48 161 / 174, r 64 186 / 198.  Shared experts: 64 + 2 x 2048 x 1408: r 48 248 /
-//     178, r 96 371 / 292, r 128 399 / 365, r 160 425 / 435; skewed 512 tokens 338 / 210, 1024 (r 96) 433 / 290, 1365
-//     460 / 366, 2730 638 / 701; 64 + 2 x 5120 x 1536: r 48 542 / 394, r 96 777 / 706, r 128 865 / 925; 160 + 2 x 2048 x
-//     1408: r 48 569 / 412, r 96 788 / 719; 8 + 1 x 4096 x 4096: r 48 234 / 160, r 96 266 / 244;
-//     launches below a workgroup per compute unit gain nothing: 16 x 2048 x 1408 (176): r 16 63 / 65, r 48 68 / 75;
-//     16 x 1024 x 512 (68) r 16 66 / 85: short from 256 workgroups to r 48, with shared experts to r 96.
-inline int64_t most_short_rows(int E, int S, bool q4) { return (q4 && S > 0 ? 96ll : 48ll) * E; }
-inline bool short_tiles(int64_t n_tokens, int k, int E, int S, int f, bool q4) {
-    const int64_t A = n_tokens * k;
-    if (A > most_short_rows(E, S, q4)) return false;
-    if (!q4) return S > 0 && E >= 32 && n_tokens >= 256;
-    const int64_t rows = (int64_t)kTileBlks * kRowBlk, tiles = (A < E ? A : E) + S * ((n_tokens + rows - 1) / rows);
-    return tiles * ((f / 16 + 7) / 8) >= 256;
-}
-
-// Capacity of the tile tables for a context (either tile height).
-inline int max_tiles_for(int max_rowblks, int E, int S, int max_tokens) {
-    auto tiles = [&](int rowblks, int tokens, int blks) {
-        return rowblks / blks + E + S * ((tokens + blks * kRowBlk - 1) / (blks * kRowBlk) + 1) + 1;
-    };
-    const int short_rows = (int)most_short_rows(E, S, true), short_rowblks = short_rows / kRowBlk + 1 + E;
-    const int tall = tiles(max_rowblks, max_tokens, kTileBlks);
-    const int low = tiles(max_rowblks < short_rowblks ? max_rowblks : short_rowblks, max_tokens < short_rows ? max_tokens : short_rows, kShortBlks);
-    return tall > low ? tall : low;
-}
 
 struct BatchOffsets {
     int32_t n;

@@ -608,7 +608,7 @@ def expert_launch(w, bits=16):
     N, A, E, S, units = w.n_tokens, w.n_tokens * w.top_k, w.n_experts, w.n_shared, w.d_ff // 16
     cdiv = lambda a, b: -(-a // b)
     if bits == 4:
-        short = A <= 48 * E and (min(E, A) + S * cdiv(N, 256)) * cdiv(units, 8) >= 256
+        short = A <= ((96 if E >= 16 else 64) if S else 48) * E and (min(E, A) + S * cdiv(N, 256)) * cdiv(units, 8) >= 256
     else:
         short = A <= 48 * E and S > 0 and E >= 32 and N >= 256
     rows, slots = (64, 512) if short else (256, 256)

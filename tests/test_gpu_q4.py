@@ -179,7 +179,9 @@ def test_q4_steady_state_and_drain(d, f, E, k, S, batches, h_planes):
     (1344, 16, 2, 0, (100,), (8, 7)),      # few rows, but below 256 workgroups: tall
     (2048, 32, 2, 0, (200,), (2, 8)),      # short tiles: 32 x 16 fit 512, x 19 do not
     (1344, 32, 2, 1, (150,), (2, 7)),
-    (4096, 8, 2, 0, (150, 42), (2, 7)), (4096, 8, 2, 0, (193,), (8, 8))])  # 48 rows on average, and one token more
+    (4096, 8, 2, 0, (150, 42), (2, 7)), (4096, 8, 2, 0, (193,), (8, 8)),   # 48 rows on average, and one token more
+    (2048, 32, 2, 1, (1100, 100), (2, 8)), (1344, 32, 2, 1, (1200,), (2, 7)),  # shared experts, 75 rows on average
+    (4096, 8, 2, 1, (256,), (2, 7)), (4096, 8, 2, 1, (257,), (8, 7))])     # fewer than 16 experts: 64 rows, one token more
 @pytest.mark.parametrize("d", [64, 448, 576])  # drain only; inside the look-ahead of the weight ring; steady state
 @pytest.mark.parametrize("h_planes", [1, 2])
 def test_q4_in_both_tile_heights_and_wavefront_shapes(d, f, E, k, S, batches, launch, h_planes):
@@ -201,14 +203,15 @@ def test_q4_in_both_tile_heights_and_wavefront_shapes(d, f, E, k, S, batches, la
     ctx.close()
 
 
-@pytest.mark.parametrize("d,f,E,tokens", [(64, 2048, 32, 1536), (576, 1344, 40, 1920)])
+@pytest.mark.parametrize("d,f,E,tokens", [(64, 2048, 32, 1536), (576, 1344, 40, 1920), (64, 2048, 16, 768), (64, 3072, 15, 480)])
 def test_q4_short_tiles_end_at_96_rows_per_expert_with_shared_experts(d, f, E, tokens):
-    """Top-2 and one shared expert: 96 rows on average (short tiles) and one token more (tall): right, and with
-    both planes and one split the same bits for the tokens they have in common."""
+    """Top-2 and one shared expert: 96 rows on average (64 with fewer than 16 experts), short tiles, and one token
+    more, tall ones: right, and with both planes and one split the same bits for the tokens they have in common."""
     ys = []
     for n in (tokens, tokens + 1):
         w = I.Workload("q4_rule", "bf16", d, f, E, 2, n_shared=1, batch_tokens=(n,), seed=89,
                        w_std=float(1.1 / (d * f) ** 0.25))
+        assert expert_launch(w, 4)[0] == (2 if n == tokens else 8)
         if n == tokens:
             data, _ = I.gen_layer(I.scaled(w, batch_tokens=(tokens + 1,)), 0, with_experts=False)
             base = [I.gen_expert_q4(w, 0, e) for e in range(3)]
