@@ -84,7 +84,7 @@ void compute_layout(const moe_config& c, Layout& L) {
     L.x_rows16 = L.max_rowblks + (S > 0 ? L.tok_rows16 : 0);
     L.h_rows16 = L.max_rowblks + S * L.tok_rows16;
     L.nchunks = (int32_t)((L.A + kPlanChunk - 1) / kPlanChunk);
-    L.max_tiles = max_tiles_for((int)L.max_rowblks, (int)E, (int)S, c.max_tokens);
+    L.max_tiles = max_tiles_for((int)L.max_rowblks, (int)E, (int)S, c.max_tokens, c.weight_bits == 4);
     L.split_cap = (c.dtype == MOE_BF16 && L.A <= 8192) ? 8 : 1;
     L.expert_bytes = c.weight_bits == 4 ? d * f * 27 / 16 : 3 * d * f * elt;  // q4: codes + (s, z) pairs
     int64_t off = 0;
@@ -1563,7 +1563,7 @@ moe_status moe_route_static(void* stream, int32_t dtype, const void* x_dev, cons
     const int64_t E = n_experts, A = (int64_t)n_tokens * top_k;
     const int64_t max_rowblks = (A + kRowBlk - 1) / kRowBlk + E;
     const int64_t nchunks = (A + kPlanChunk - 1) / kPlanChunk;
-    const int max_tiles = max_tiles_for((int)max_rowblks, (int)E, 0, n_tokens);
+    const int max_tiles = max_tiles_for((int)max_rowblks, (int)E, 0, n_tokens, false);
     unsigned char* base = nullptr;
     moe_status rs = static_scratch(&base);
     if (rs != MOE_OK) return rs;

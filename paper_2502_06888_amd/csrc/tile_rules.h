@@ -46,12 +46,12 @@ inline bool short_tiles(int64_t n_tokens, int k, int E, int S, int f, bool q4) {
     return tiles * ((f / 16 + 7) / 8) >= 256;
 }
 
-// Capacity of the tile tables for a context (either tile height).
-inline int max_tiles_for(int max_rowblks, int E, int S, int max_tokens) {
+// Capacity of the tile tables for a context (either tile height its weights may take).
+inline int max_tiles_for(int max_rowblks, int E, int S, int max_tokens, bool q4) {
     auto tiles = [&](int rowblks, int tokens, int blks) {
         return rowblks / blks + E + S * ((tokens + blks * kRowBlk - 1) / (blks * kRowBlk) + 1) + 1;
     };
-    const int short_rows = (int)most_short_rows(E, S, true), short_rowblks = short_rows / kRowBlk + 1 + E;
+    const int short_rows = (int)most_short_rows(E, S, q4), short_rowblks = short_rows / kRowBlk + 1 + E;
     const int tall = tiles(max_rowblks, max_tokens, kTileBlks);
     const int low = tiles(max_rowblks < short_rowblks ? max_rowblks : short_rowblks,
                           max_tokens < short_rows ? max_tokens : short_rows, kShortBlks);

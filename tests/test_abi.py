@@ -72,6 +72,18 @@ def test_plan_sizes_for_the_named_workloads():
     assert B.moe_plan(cfg, 64).expert_bytes == 1572864
 
 
+def test_tile_tables_follow_the_format_of_the_weights():
+    """Tall tiles and short ones up to 48 rows per expert for bf16 and fp32; 4-bit experts beside shared ones are cut
+    into short tiles further on, and only their contexts pay for the longer tables."""
+    def workspace(*cfg):
+        return B.moe_plan(B.make_config(*cfg), cfg[7]).workspace_bytes
+    assert workspace(2048, 1408, 64, 6, 2, 1, 0, 4096, 32, B.MOE_BF16, 1, 0) == 607949312
+    assert workspace(2048, 1408, 160, 6, 2, 1, 0, 8192, 32, B.MOE_BF16, 1, 16) == 1234402048
+    assert workspace(256, 512, 256, 8, 8, 1, 0, 4096, 64, B.MOE_F32, 1, 0) == 228169728
+    assert workspace(2048, 1408, 64, 6, 0, 1, 0, 4096, 32, B.MOE_BF16, 1, 4) == 477858304
+    assert workspace(2048, 1408, 64, 6, 2, 1, 0, 4096, 32, B.MOE_BF16, 1, 4) > 607949312
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(d_model=4100), B.MOE_ERR_SHAPE), (dict(d_ff=100), B.MOE_ERR_SHAPE),
     (dict(n_experts=0), B.MOE_ERR_SHAPE), (dict(n_experts=257), B.MOE_ERR_SHAPE),

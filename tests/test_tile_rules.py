@@ -16,7 +16,7 @@ def rules(tmp_path_factory):
     src, so = d / "shim.cpp", d / "shim.so"
     src.write_text('#include "tile_rules.h"\n'
                    'extern "C" int low(long n, int k, int E, int S, int f, int q4) { return kmoe::short_tiles(n, k, E, S, f, q4 != 0); }\n'
-                   'extern "C" int most(int rowblks, int E, int S, int tokens) { return kmoe::max_tiles_for(rowblks, E, S, tokens); }\n')
+                   'extern "C" int most(int rowblks, int E, int S, int tokens, int q4) { return kmoe::max_tiles_for(rowblks, E, S, tokens, q4 != 0); }\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", "-o", str(so), str(src)], check=True)
     lib = C.CDLL(str(so))
     lib.low.argtypes = [C.c_long] + [C.c_int] * 5
@@ -51,4 +51,4 @@ def test_tile_tables_hold_every_plan(rules):
         tall = 2 if rules.low(n, k, E, S, f, q4) else 8
         blocks = -(-counts // 32)
         tiles = int((-(-blocks // tall)).sum()) + S * -(-(-(-n // 32)) // tall)
-        assert tiles <= rules.most(-(-room * k // 32) + E, E, S, room), (E, S, k, n, room, q4)
+        assert tiles <= rules.most(-(-room * k // 32) + E, E, S, room, q4), (E, S, k, n, room, q4)
