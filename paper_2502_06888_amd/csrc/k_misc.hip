@@ -508,8 +508,11 @@ void launch_combine(hipStream_t st, int out_dtype, const Shape& s, const PlanPtr
                     const float* o, int split_k, int64_t o_split_stride, void* y) {
     if (s.N <= 0) return;
     // One wavefront per (token, 64 * COLS float4 columns): one column per lane until that gives two wavefronts per
-    // SIMD, two columns, whose look-ups are shared, beyond.  Tokens of up to four partial rows ask for four at a
-    // time, which leaves registers for twice the wavefronts (16384 tokens of two, width 4096: 125 us, with eight 136).
+    // SIMD, two columns, whose look-ups are shared, beyond.  There tokens of up to two or four partial rows ask for
+    // two or four at a time instead of eight: 56, 72 or 107 registers, eight, seven or four wavefronts per SIMD.  Slot
+    // after slot / two / four / eight at a time, width 4096, us: one row, 1024 tokens 7.0 / 6.8 / 8.3 / 8.5, 16384 tokens
+    // 69 / 68 / 76 / 102; two rows, 1024 9.9 / 9.1 / 10.5 / 11.0, 16384 122 / 115 / 118 / 129; two and a shared one of
+    // 2048, 8192 44 / 41 / 40 / 43; four, 8192 118 / 106 / 105 / 108.
     auto launch = [&](auto kernel, int cols) {
         const int chunks = (s.d / 4 + 64 * cols - 1) / (64 * cols);
         hipLaunchKernelGGL(kernel, dim3(grid_for((size_t)s.N * chunks * 64, 8192)), dim3(kThreads), 0, st, s, p, o,
@@ -519,6 +522,8 @@ void launch_combine(hipStream_t st, int out_dtype, const Shape& s, const PlanPtr
         constexpr bool kBf16 = decltype(bf16)::value;
         if ((int64_t)s.N * s.d <= 2048 * 4 * 64)
             launch(combine_kernel<kBf16, 1, 8>, 1);
+        else if ((s.k + s.S) * split_k <= 2)
+            launch(combine_kernel<kBf16, 2, 2>, 2);
         else if ((s.k + s.S) * split_k <= 4)
             launch(combine_kernel<kBf16, 2, 4>, 2);
         else

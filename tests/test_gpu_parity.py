@@ -424,6 +424,14 @@ def test_combine_of_slots_and_splits(k, S, d, tokens, splits):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,d,tokens", [("f32", 260, 2100), ("f32", 512, 1025), ("bf16", 320, 1700)])
+@pytest.mark.parametrize("k,S", [(1, 0), (2, 0), (2, 1), (3, 1), (4, 1), (8, 2)])
+def test_combine_of_two_columns_per_lane(dtype, d, tokens, k, S):
+    """Large groups: one to two, three to four and more partial rows per token; widths whose second column ends
+    inside a wavefront (65 and 80 vectors of four) or at its end."""
+    run_case(I.Workload("combine_wide", dtype, d, 64, 8, k, n_shared=S, batch_tokens=(tokens - 9, 9), w_std=0.08, seed=101))
+
+
 @pytest.mark.parametrize("d,f,tokens", [(64, 2048, 128), (64, 2048, 160), (64, 2052, 128), (260, 2052, 300), (36, 2080, 256)])
 def test_f32_up_projections_of_many_workgroups(d, f, tokens):
     """512 to 1000 workgroups with rows, reductions of whole and of broken stages."""
